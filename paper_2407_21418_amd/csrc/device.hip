@@ -358,14 +358,30 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         if (e != hipSuccess) return hip_fail(e);
     }
     int rc;
+    // A reduce axis of fewer k-tiles than the ring has stages never touches the others: the launch asks only for
+    // the stages it uses, so that more workgroups fit a CU.  Measured: Q K^T and P V of 96 heads of 131 rows (one and
+    // three k-tiles) 11.6 -> 10.6 us.
+    uint32_t lds_fast = plan->st.lds_bytes;
+    if (fast && !plan->two_teams) {
+        const uint32_t nk = a.k_parts > 1 ? a.k_part_tiles : std::max<uint32_t>((a.K + FT_TK - 1) / FT_TK, 1);
+        lds_fast = 0;
+        for (int i = 0; i < 4; ++i) {
+            const int code = (int)a.slot_code[i];
+            const bool splitk = ft_is_splitk_code(code);
+            const uint32_t tiles = splitk ? (nk + 3) / 4 : nk;
+            a.slot_stages[i] = std::max(2u, std::min(a.slot_stages[i], tiles));
+            const uint32_t used = splitk ? 4 * a.slot_stages[i] : std::min(a.slot_stages[i], tiles);
+            lds_fast = std::max(lds_fast, used * ft_stage_bytes_of_code(code));
+        }
+    }
     if (plan->op.b_layout == FT_B_NK) {
         if (plan->two_teams) return FT_ERR_UNSUPPORTED;      // (such an operator derives none)
-        rc = kLaunchNK[plan->op.dtype][plan->st.kernel_class](&a, plan->st.lds_bytes, hip_stream);
+        rc = kLaunchNK[plan->op.dtype][plan->st.kernel_class](&a, lds_fast, hip_stream);
     } else if (fast && plan->two_teams) {
         if (plan->st.kernel_class > 1) return FT_ERR_UNSUPPORTED;
         rc = kLaunchTwoTeams[plan->op.dtype][plan->st.kernel_class](&a, plan->st.lds_bytes, hip_stream);
     } else if (fast) {
-        rc = (ragged ? kLaunchRagged : kLaunch)[plan->op.dtype][plan->st.kernel_class](&a, plan->st.lds_bytes, hip_stream);
+        rc = (ragged ? kLaunchRagged : kLaunch)[plan->op.dtype][plan->st.kernel_class](&a, lds_fast, hip_stream);
     } else {
         // the general bodies stage through registers into two LDS stages, whatever ring depth the
         // uKernel has on the LDS-DMA path

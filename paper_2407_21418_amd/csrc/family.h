@@ -109,6 +109,13 @@ static inline int ft_is_w8_code(int code) {
 #undef FT_X
     return 0;
 }
+// a split-k wave grid body
+static inline int ft_is_splitk_code(int code) {
+#define FT_X(c, TM, TN, TWIN) if (code == c) return 1;
+    FT_FAMILY_SPLITK(FT_X)
+#undef FT_X
+    return 0;
+}
 // body the general path runs for a given code (split-k codes map to their standard-grid twin)
 static inline int ft_general_code(int code) {
 #define FT_X(c, WM, WN, GM, GN, TWIN) if (code == c) return TWIN;

@@ -1340,7 +1340,10 @@ static ft_status plan_create_grouped_impl(const ft_op *op, ft_ukset *set, const 
             const int twin = ft_general_code(code);          // what the general bodies run for it
             pl->grp_stage_bytes = std::max(pl->grp_stage_bytes, ft_stage_bytes_of_code(twin));
             pl->grp_acc = std::max(pl->grp_acc, (uint32_t)ft_acc_of_code(twin));
-            pl->grp_fast_lds = std::max(pl->grp_fast_lds, u.lds_bytes);
+            // (a reduce axis of fewer k-tiles than the ring has stages never touches the others)
+            const uint64_t used = ft_is_splitk_code(code) ? u.gk * u.stages
+                                                          : std::min<uint64_t>(u.stages, std::max<uint64_t>(ceil_div(rec.k, FT_TK), 1));
+            pl->grp_fast_lds = std::max(pl->grp_fast_lds, (uint32_t)used * ft_stage_bytes_of_code(code));
             pl->grp_fast_acc = std::max(pl->grp_fast_acc, u.acc_regs);
         }
         // LDS-DMA bodies, B stored [K][N]: rows of at least one 16-byte chunk (the reduce axis: see below)
