@@ -8,6 +8,7 @@
 #include "ft_internal.h"
 #include "gemm_body.h"
 #include "launch_iface.h"
+#include "row_runs.h"
 
 // Workspace of ft_launch_noalloc: the fp32 partial tiles and arrival counters of a reduce-axis split,
 // which ft_plan_create otherwise allocates per plan.  One copy per GPU, held until the process ends and
@@ -297,6 +298,30 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         a.arrive = reinterpret_cast<uint32_t *>(base);
         a.ws = reinterpret_cast<float *>(base + FT_NOALLOC_COUNTER_BYTES);
     }
+    const bool even = (reinterpret_cast<uintptr_t>(A) % 2 == 0) && (reinterpret_cast<uintptr_t>(B) % 2 == 0);
+    // Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in
+    // address order (row_runs.hip has the measurements), as long as they make a workgroup per CU.  Rows on 64-byte
+    // blocks stay with the tile bodies, which write them at the same rate and read B less often (160 columns: 20.7
+    // against 24.7 us); so do launches of few rows, which tiles spread over more CUs (12 x 300 x 300: 4.2 against 5.4 us).
+    const uint32_t es_c = a.out_kind == ftk::OUT_F32 ? 4 : 2;
+    if (plan->row_runs && even && ((uint64_t)a.N * es_c % 64 != 0 || reinterpret_cast<uintptr_t>(C) % 64 != 0)) {
+        ftk::RunArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.A = a.A; r.B = a.B; r.C = C; r.bias = bias;
+        r.out16 = es_c == 2;
+        r.num_xcds = plan->num_xcds;
+        r.M = a.M; r.N = a.N; r.K = a.K;
+        r.rb_log2 = ftk::run_rb_log2(a.M, a.N, plan->st.batch, plan->num_cus);
+        r.runs = (a.M + (32u << r.rb_log2) - 1) / (32u << r.rb_log2);
+        const uint64_t n_runs = (uint64_t)plan->st.batch * r.runs;
+        if (n_runs >= plan->num_cus && n_runs < (1u << 31)) {
+            const bool nk = plan->op.b_layout == FT_B_NK;
+            r.n_runs = (uint32_t)n_runs;
+            const int rc = ft_launch_runs(&r, (int)plan->op.dtype, nk, ftk::run_lds(a.N, r.rb_log2, es_c, nk), hip_stream);
+            if (rc != 0) return hip_fail((hipError_t)rc);
+            return FT_OK;
+        }
+    }
     if (!plan->groups.empty()) {
         // grouped launch: the dispatcher takes shape, pitches and operand bases from the group records
         if (!plan->d_groups) return FT_ERR_INVALID_ARG;
@@ -326,7 +351,6 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
     // chunk from inside the row and fix it up in LDS (gemm_fast.h); that needs rows of at least one chunk.  Convolution: c_in a multiple of 64, c_out of 8, 16-byte aligned operands.  Everything
     // else takes the general bodies.
     const bool aligned = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0);
-    const bool even = (reinterpret_cast<uintptr_t>(A) % 2 == 0) && (reinterpret_cast<uintptr_t>(B) % 2 == 0);
     const bool nk = plan->op.b_layout == FT_B_NK;
     const bool ragged = !a.is_conv && (a.K % 8 != 0 || (!nk && a.N % 8 != 0));
     bool fast = a.is_conv ? (aligned && a.Cin % 64 == 0 && a.N % 8 == 0)

@@ -60,6 +60,8 @@ struct ft_plan {
     bool grp_rows_on_blocks;                // every group's rows of C start on 64-byte blocks (given such a C)
     bool grp_aligned;                       // every group fits the LDS-DMA bodies (given 16-byte aligned A, B)
     uint32_t grp_fast_lds, grp_fast_acc;    // LDS bytes and accumulator registers the LDS-DMA bodies need
+    bool row_runs;                          // a launch may execute whole rows of C instead of tiles (row_runs.hip)
+    uint32_t num_cus;
 };
 
 // device.hip

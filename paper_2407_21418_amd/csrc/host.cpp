@@ -8,6 +8,7 @@
 
 #include "family.h"
 #include "ft_internal.h"
+#include "row_runs.h"
 #include "tile_order.h"
 
 namespace {
@@ -905,6 +906,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     pl->d_groups = nullptr;
     pl->grp_stage_bytes = 0; pl->grp_acc = 0; pl->grp_k_min = 0; pl->grp_rows_on_blocks = false;
     pl->grp_aligned = false; pl->grp_fast_lds = 0; pl->grp_fast_acc = 0;
+    pl->row_runs = false; pl->num_cus = set->hw.num_cus;
     pl->ws_tile_stride = 0;
     pl->device = -1;
     pl->num_xcds = set->hw.num_xcds ? set->hw.num_xcds : 1;
@@ -1209,6 +1211,8 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
         if (!ok) pl->table_order = true;
     }
     if (flags & FT_PLAN_TABLE_ORDER) pl->table_order = true;
+    // A batched product of one k-tile may be executed in whole rows of C, unless the caller asked for particular tiles
+    pl->row_runs = op->d.kind == FT_OP_BMM && mode == FT_PLAN_PATCHWORK && !pl->table_order && ftk::run_shape_ok((uint32_t)r.N, (uint32_t)r.K);
     s.table_order = pl->table_order ? 1u : 0u;
 
     if (!(flags & FT_PLAN_HOST_ONLY)) {

@@ -1,0 +1,38 @@
+"""Batched products of one k-tile executed in whole rows of C (odd row lengths, enough rows for every CU):
+edges of the 32-row and 32-column blocks, the limits of the row length, short reduce axes, both layouts of B, both
+output types, fused bias; against the CPU oracle.  Every launch here has at least 256 workgroups' worth of rows
+(the batch sees to it), which is what sends it down this path."""
+import numpy as np
+import pytest
+
+import paper_2407_21418_amd as ft
+import synth_inputs as si
+from oracle import contraction as oc
+from oracle import epilogue as oe
+from gpu_util import check_epilogue, run_epilogue
+
+pytestmark = pytest.mark.gpu
+
+#       M,   N,  K, batch
+SHAPES = [(1, 9, 64, 260), (31, 33, 64, 256), (33, 31, 8, 256), (64, 65, 64, 257), (65, 127, 56, 256), (129, 129, 64, 256),
+          (100, 100, 64, 1100), (33, 191, 64, 256), (70, 257, 24, 256), (40, 319, 64, 256), (131, 8, 64, 256)]
+
+
+@pytest.mark.parametrize("layout", [ft.FT_B_KN, ft.FT_B_NK], ids=["kn", "nk"])
+@pytest.mark.parametrize("M,N,K,batch", SHAPES)
+def test_whole_rows(M, N, K, batch, layout):
+    dtype = (M + N) % 2
+    out16 = None if (N + K) % 3 else dtype
+    g = np.random.default_rng([M, N, K, layout])
+    A = si.normal_bits(g, (batch, M, K), 1.0, dtype)
+    B = si.normal_bits(g, (batch, K, N) if layout == ft.FT_B_KN else (batch, N, K), 0.2, dtype)
+    bias = g.standard_normal(N).astype(np.float32) if M % 2 else None
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_BMM, dtype=dtype, k=K, m_lo=0, m_hi=512, n_lo=0, n_hi=512, batch_hi=1200, b_layout=layout,
+                                         out_dtype=ft.FT_OUT_F32 if out16 is None else ft.FT_OUT_SAME,
+                                         epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(batch=batch, m=M, n=N))
+    ref, refabs = (oc.bmm if layout == ft.FT_B_KN else oc.bmm_nk)(A, B, dtype, want_abs=True)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    got = run_epilogue(plan, A, B, batch * M * N, bias, out16)
+    check_epilogue(got, ref, refabs, bias, out16, f"{batch}x{M}x{N}x{K}")
