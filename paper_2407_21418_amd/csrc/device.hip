@@ -9,6 +9,7 @@
 #include "gemm_body.h"
 #include "launch_iface.h"
 #include "row_runs.h"
+#include "big_gemm.h"
 
 // Workspace of ft_launch_noalloc: the fp32 partial tiles and arrival counters of a reduce-axis split,
 // which ft_plan_create otherwise allocates per plan.  One copy per GPU, held until the process ends and
@@ -342,6 +343,19 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         }
         const int rc = fast ? kLaunchGroupedFast[plan->op.dtype][ft_class_of_acc((int)plan->grp_fast_acc)](&a, plan->grp_fast_lds, hip_stream)
                             : kLaunchGrouped[plan->op.dtype][plan->grp_acc <= 64 ? 0 : 1](&a, 2 * plan->grp_stage_bytes, hip_stream);
+        if (rc != 0) return hip_fail((hipError_t)rc);
+        return FT_OK;
+    }
+    if (plan->big && even && reinterpret_cast<uintptr_t>(C) % 16 == 0) {
+        ftk::BigArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.A = a.A; r.B = a.B; r.C = C; r.bias = bias;
+        r.out16 = es_c == 2;
+        r.M = a.M; r.N = a.N; r.K = a.K;
+        r.rows = plan->big_rows; r.cols = plan->big_cols; r.group = 4;
+        r.n_full = plan->big_full; r.n_half = plan->big_half;
+        r.num_xcds = plan->num_xcds;
+        const int rc = ft_launch_big(&r, (int)plan->op.dtype, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }

@@ -62,6 +62,9 @@ struct ft_plan {
     uint32_t grp_fast_lds, grp_fast_acc;    // LDS bytes and accumulator registers the LDS-DMA bodies need
     bool row_runs;                          // a launch may execute whole rows of C instead of tiles (row_runs.hip)
     uint32_t num_cus;
+    // large products (big_gemm.hip): a launch executes blocks of 256 x 256, some of them as halves of 128 rows
+    bool big;
+    uint32_t big_rows, big_cols, big_full, big_half;
 };
 
 // device.hip

@@ -564,6 +564,45 @@ bool better(const Program &a, const Program &b) {      // Top-1 order: SIA, then
     return a.k2 < b.k2;          // (strip variants of one program that tie: the first listed stays)
 }
 
+// Large products are executed in blocks of 256 x 256, one per CU at a time, whatever tiles the program has
+// (big_gemm.hip); a strip of at most 128 rows below the grid of blocks is executed in halves.  A block is a CU's work for a
+// whole round, so blocks may also be dealt as two halves of 128 rows: of the numbers of halved blocks the one with the
+// shortest schedule is taken.  A half takes 0.55 of a block (measured at K = 4096: 48 against 87 us).
+// Taken where the device is busy for at least 60 % of that schedule and 45 % of what it computes is wanted; below
+// that the program's smaller tiles are faster (K = 4096, blocks against tiles: 403 x 11008 54 against 61 us at 67 % busy,
+// 1200 x 4096 53 against 54 at 62 %; 1100 x 4096 53 against 49 at 56 %, 700 x 11008 86 against 84 at 50 %), and from twelve
+// k-tiles on (8192 x 3072 x 768: 43 against 52 us), so that the first copies and the stores of a block do not dominate;
+// halves alone want 32 (2048 x 3072 x 768: 17.6 against 15.7 us, x 2048: 29 against 32).
+void big_schedule(ft_plan *pl) {
+    const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
+    if (K % 64 || K < 12 * 64 || N % 8 || P == 0) return;
+    const uint64_t below = M % 256, rows = M / 256 + (below > 128), cols = ceil_div(N, 256);
+    const uint64_t blocks = rows * cols, strip = below && below <= 128 ? cols : 0;
+    if (blocks + strip > (1u << 20)) return;
+    constexpr uint32_t kBlock = 20, kHalf = 11;
+    if ((blocks * 2 + strip) * 10 < 6 * P) return;                    // (not worth a look: less than 60 % of one round of halves)
+    // shortest time for f blocks, dealt evenly, and h halves on top of them
+    auto makespan = [&](uint32_t f, uint32_t h) -> uint32_t {
+        const uint32_t p = (uint32_t)P, q = f / p, r = f % p;         // r CUs have q + 1 blocks
+        uint32_t t = std::max(kBlock * (q + (r ? 1u : 0u)), (f * kBlock + h * kHalf + p - 1) / p);
+        for (;; ++t)
+            if ((p - r) * ((t - kBlock * q) / kHalf) + (r ? r * ((t - kBlock * (q + 1)) / kHalf) : 0) >= h) return t;
+    };
+    uint32_t best = ~0u, halved = 0;
+    const uint32_t last_round = (uint32_t)(blocks % P);
+    for (uint32_t i = 0; i <= 16; ++i) {                              // none .. all blocks of the last round, in sixteenths
+        const uint32_t c = last_round * i / 16, t = makespan((uint32_t)blocks - c, (uint32_t)strip + 2 * c);
+        if (t < best) { best = t; halved = c; }
+    }
+    const uint64_t full = blocks - halved, half = strip + 2 * halved;
+    if ((full * kBlock + half * kHalf) * 10 < 6 * best * P) return;
+    if (full == 0 && K < 2048) return;
+    if (M * N * 20 < 9 * (full * 2 + half) * 256 * 128) return;
+    pl->big = true;
+    pl->big_rows = (uint32_t)rows; pl->big_cols = (uint32_t)cols;
+    pl->big_full = (uint32_t)full; pl->big_half = (uint32_t)half;
+}
+
 int level_of(const Program &p) { return p.in_bound ? 0 : 1; }
 
 ftk::LaunchOrder launch_order_of(const ft_plan &plan) {
@@ -907,6 +946,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     pl->grp_stage_bytes = 0; pl->grp_acc = 0; pl->grp_k_min = 0; pl->grp_rows_on_blocks = false;
     pl->grp_aligned = false; pl->grp_fast_lds = 0; pl->grp_fast_acc = 0;
     pl->row_runs = false; pl->num_cus = set->hw.num_cus;
+    pl->big = false; pl->big_rows = pl->big_cols = pl->big_full = pl->big_half = 0;
     pl->ws_tile_stride = 0;
     pl->device = -1;
     pl->num_xcds = set->hw.num_xcds ? set->hw.num_xcds : 1;
@@ -1211,6 +1251,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
         if (!ok) pl->table_order = true;
     }
     if (flags & FT_PLAN_TABLE_ORDER) pl->table_order = true;
+    if (op->d.kind == FT_OP_MATMUL && op->d.b_layout == FT_B_KN && mode == FT_PLAN_PATCHWORK && !pl->table_order) big_schedule(pl);
     // A batched product of one k-tile may be executed in whole rows of C, unless the caller asked for particular tiles
     pl->row_runs = op->d.kind == FT_OP_BMM && mode == FT_PLAN_PATCHWORK && !pl->table_order && ftk::run_shape_ok((uint32_t)r.N, (uint32_t)r.K);
     s.table_order = pl->table_order ? 1u : 0u;

@@ -1,0 +1,50 @@
+"""Large products executed in 256 x 256 blocks and halves of 128 rows: edges of blocks and of the strip below them, columns
+that end inside a block, the shortest reduce axis taken and longer ones with every remainder of the rings, both output
+types, fused bias; sampled rows against the CPU oracle (all rows next to a block edge among them)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_21418_amd as ft
+import synth_inputs as si
+from oracle import contraction as oc
+from oracle import epilogue as oe
+from gpu_util import GUARD, check_epilogue, dev_bits, stream
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): each has enough blocks for the 256 CUs it is planned for
+SHAPES = [(4096, 4096, 768), (3073, 4104, 832), (3200, 4088, 896), (3201, 5000, 960), (2049, 8192, 1024), (8191, 2056, 768),
+          (1400, 11008, 768), (600, 11008, 2048), (130, 70000, 768)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_blocks(M, N, K):
+    dtype = (M + N // 8) % 2
+    out16 = dtype if K % 128 else None
+    bias = np.random.default_rng(N).standard_normal(N).astype(np.float32) if M % 2 else None
+    g = np.random.default_rng([M, N, K])
+    A = si.normal_bits(g, (M, K), 1.0, dtype)
+    B = si.normal_bits(g, (K, N), 0.02, dtype)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_MATMUL, dtype=dtype, n=N, k=K, m_lo=1, m_hi=8192,
+                                         out_dtype=ft.FT_OUT_F32 if out16 is None else ft.FT_OUT_SAME,
+                                         epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(m=M))
+    dA, dB = dev_bits(A), dev_bits(B)
+    db = torch.from_numpy(bias).cuda() if bias is not None else None
+    tdt = torch.float32 if out16 is None else torch.float16 if out16 == ft.FT_F16 else torch.bfloat16
+    C = torch.full((M * N + 2 * GUARD,), float("nan"), dtype=tdt, device="cuda")
+    C[:GUARD] = 7.0
+    C[-GUARD:] = 7.0
+    ft.ft_launch_epilogue(plan, dA.data_ptr(), dB.data_ptr(), C.data_ptr() + GUARD * C.element_size(), db.data_ptr() if db is not None else 0, stream())
+    torch.cuda.synchronize()
+    assert bool((C[:GUARD] == 7.0).all()) and bool((C[-GUARD:] == 7.0).all()), "write outside C"
+    body = C[GUARD:-GUARD].view(M, N)
+    assert bool(torch.isfinite(body).all()), "uncovered outputs"
+    edges = {r for e in range(0, M + 1, 128) for r in (e - 1, e) if 0 <= r < M}
+    rows = np.array(sorted(set(list(edges)[:40]) | {0, M - 1} | {int(x) for x in g.integers(0, M, 24)}))
+    ref, refabs = oc.matmul(A, B, dtype, rows=rows, want_abs=True)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    got = body[torch.from_numpy(rows).cuda()].float().cpu().numpy().astype(np.float64)
+    check_epilogue(got, ref, refabs, bias, out16, f"{M}x{N}x{K}")
