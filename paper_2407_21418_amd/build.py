@@ -121,7 +121,7 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
                 gen.append((obj, cmd))
     gen.sort(key=lambda oc: "_c2" not in oc[0])   # the 512-register kernels take longest: start them first
     steps = gen + steps
-    for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip"):
+    for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip", "conv_patch.hip"):
         obj = os.path.join(OUT, src.replace(".", "_") + ".o")
         steps.append((obj, [HIPCC] + COMMON + ["-c", os.path.join(CSRC, src), "-o", obj]))
     jobs = jobs or min(8, len(steps))

@@ -10,6 +10,7 @@
 #include "launch_iface.h"
 #include "row_runs.h"
 #include "big_gemm.h"
+#include "conv_patch.h"
 
 // Workspace of ft_launch_noalloc: the fp32 partial tiles and arrival counters of a reduce-axis split,
 // which ft_plan_create otherwise allocates per plan.  One copy per GPU, held until the process ends and
@@ -343,6 +344,22 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         }
         const int rc = fast ? kLaunchGroupedFast[plan->op.dtype][ft_class_of_acc((int)plan->grp_fast_acc)](&a, plan->grp_fast_lds, hip_stream)
                             : kLaunchGrouped[plan->op.dtype][plan->grp_acc <= 64 ? 0 : 1](&a, 2 * plan->grp_stage_bytes, hip_stream);
+        if (rc != 0) return hip_fail((hipError_t)rc);
+        return FT_OK;
+    }
+    if (plan->conv_th && even && reinterpret_cast<uintptr_t>(C) % 16 == 0) {
+        ftk::ConvArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.X = a.A; r.Wt = a.B; r.Y = C; r.bias = bias;
+        r.H = a.H; r.W = a.W; r.P = a.P; r.Q = a.Q; r.pad = a.cpad; r.N = a.N;
+        r.th = plan->conv_th; r.tw = plan->conv_tw;
+        r.tiles_y = (a.P + r.th - 1) / r.th; r.tiles_x = (a.Q + r.tw - 1) / r.tw;
+        r.tiles = a.M / (a.P * a.Q) * r.tiles_y * r.tiles_x;
+        r.cols = (a.N + 63) / 64;
+        r.walkers = plan->num_cus / r.cols < r.tiles ? plan->num_cus / r.cols : r.tiles;
+        r.num_xcds = plan->num_xcds;
+        const uint32_t lds = 9 * ftk::kConvTap + ftk::conv_patch_bytes(ftk::conv_patch_rows(r.th, r.tw)) * (r.tiles > r.walkers ? 2 : 1);
+        const int rc = ft_launch_conv(&r, (int)plan->op.dtype, es_c == 2, (int)plan->conv_bm, lds, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "family.h"
+#include "conv_patch.h"
 #include "ft_internal.h"
 #include "row_runs.h"
 #include "tile_order.h"
@@ -603,6 +604,47 @@ void big_schedule(ft_plan *pl) {
     pl->big_full = (uint32_t)full; pl->big_half = (uint32_t)half;
 }
 
+// The tile of at most `pixels` output pixels whose patch fits `lds` bytes and that needs the fewest tiles per image (then
+// the smallest patch); 0 if there is none.
+uint64_t conv_tile(uint32_t P, uint32_t Q, uint32_t pixels, uint32_t lds, uint32_t *th, uint32_t *tw) {
+    uint64_t best = 0, best_rows = 0;
+    for (uint32_t nx = 1, last = 0; nx <= Q; ++nx) {                  // tiles across; equal widths
+        const uint32_t w = (uint32_t)ceil_div(Q, nx);
+        if (w == last || w > pixels) continue;
+        last = w;
+        const uint32_t most = std::min(P, pixels / w);
+        for (uint32_t ny = (uint32_t)ceil_div(P, most), tries = 0; ny <= P && tries < 3; ++ny, ++tries) {
+            const uint32_t h = (uint32_t)ceil_div(P, ny), rows = ftk::conv_patch_rows(h, w);
+            const uint64_t tiles = ceil_div(P, h) * ceil_div(Q, w);
+            if (ftk::conv_patch_bytes(rows) > lds) continue;
+            if (best == 0 || tiles < best || (tiles == best && rows < best_rows)) { best = tiles; best_rows = rows; *th = h; *tw = w; }
+            break;
+        }
+        if (w <= 4) break;
+    }
+    return best;
+}
+// 3 x 3 filters over 64 channels, stride 1 (conv_patch.hip).  Its taps are unrolled and its patch rows are one pixel's 64
+// channels; with a stride the patch holds stride^2 pixels per output (8 x 112 x 112, stride 2: 11.3 us against the gather's
+// 11.2).  Every workgroup walks the same number of tiles, so a tile of 64 * bm pixels costs rounds * (0.6 + bm): measured on
+// 8 x 224 x 224 1.9, 2.9, 4.2 and 5.7 us per round for bm = 1 .. 4.  In time against the gather (us, fp32 results): 28^2
+// 5.2 / 6.6, 45^2 8.2 / 8.1, 56^2 9.9 / 10.8, 91^2 16 / 23, 150^2 37 / 41, 224^2 74 / 89: no size is left to the gather.
+void conv_schedule(ft_plan *pl) {
+    const ft_op_desc &d = pl->op;
+    const uint64_t P = pl->out_p, Q = pl->out_q, cols = ceil_div(d.c_out, 64);
+    if (d.c_in != 64 || d.c_out % 8 || d.r != 3 || d.s != 3 || d.stride != 1 || cols > pl->num_cus) return;
+    if (P == 0 || Q == 0 || P > 32000 || Q > 32000 || P * Q * d.c_out >= (1u << 29)) return;     // 16-bit coordinates; results of an image below 2^31 bytes
+    const uint64_t images = pl->st.m / (P * Q), walkers = pl->num_cus / cols;
+    double best = 0;
+    for (uint32_t bm = 1; bm <= 4; ++bm) {
+        uint32_t th = 0, tw = 0;
+        const uint64_t tiles = images * conv_tile((uint32_t)P, (uint32_t)Q, 64 * bm, ftk::kConvPatchRoom, &th, &tw);
+        if (tiles == 0 || tiles >= (1u << 31)) continue;
+        const double cost = (double)ceil_div(tiles, walkers) * (0.6 + bm);
+        if (best == 0 || cost < best) { best = cost; pl->conv_th = th; pl->conv_tw = tw; pl->conv_bm = bm; }
+    }
+}
+
 int level_of(const Program &p) { return p.in_bound ? 0 : 1; }
 
 ftk::LaunchOrder launch_order_of(const ft_plan &plan) {
@@ -946,6 +988,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     pl->grp_stage_bytes = 0; pl->grp_acc = 0; pl->grp_k_min = 0; pl->grp_rows_on_blocks = false;
     pl->grp_aligned = false; pl->grp_fast_lds = 0; pl->grp_fast_acc = 0;
     pl->row_runs = false; pl->num_cus = set->hw.num_cus;
+    pl->conv_th = pl->conv_tw = pl->conv_bm = 0;
     pl->big = false; pl->big_rows = pl->big_cols = pl->big_full = pl->big_half = 0;
     pl->ws_tile_stride = 0;
     pl->device = -1;
@@ -1252,6 +1295,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     }
     if (flags & FT_PLAN_TABLE_ORDER) pl->table_order = true;
     if (op->d.kind == FT_OP_MATMUL && op->d.b_layout == FT_B_KN && mode == FT_PLAN_PATCHWORK && !pl->table_order) big_schedule(pl);
+    if (op->d.kind == FT_OP_CONV2D && mode == FT_PLAN_PATCHWORK && !pl->table_order) conv_schedule(pl);
     // A batched product of one k-tile may be executed in whole rows of C, unless the caller asked for particular tiles
     pl->row_runs = op->d.kind == FT_OP_BMM && mode == FT_PLAN_PATCHWORK && !pl->table_order && ftk::run_shape_ok((uint32_t)r.N, (uint32_t)r.K);
     s.table_order = pl->table_order ? 1u : 0u;

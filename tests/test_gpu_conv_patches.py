@@ -1,0 +1,51 @@
+"""3 x 3 convolutions over 64 channels, executed from image patches in LDS: images smaller than a tile and many tiles per
+workgroup, tiles that overhang on either side, one-pixel and one-row images, padding 0 to 3, output channels that end inside a
+block of 64, both output types, fused bias; every pixel (large images: sampled ones) against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_21418_amd as ft
+import synth_inputs as si
+from oracle import contraction as oc
+from oracle import epilogue as oe
+from gpu_util import GUARD, check_epilogue, dev_bits, stream
+
+pytestmark = pytest.mark.gpu
+
+# (images, height, width, output channels, padding)
+SHAPES = [(1, 1, 1, 8, 1), (1, 3, 3, 64, 0), (3, 1, 40, 72, 1), (2, 67, 2, 136, 1), (2, 9, 31, 264, 2), (1, 16, 16, 64, 1),
+          (5, 17, 33, 128, 0), (1, 64, 300, 192, 3), (8, 75, 75, 128, 1), (3, 131, 257, 200, 1), (2, 40, 40, 8200, 1)]
+
+
+@pytest.mark.parametrize("n,h,w,co,pad", SHAPES)
+def test_patches(n, h, w, co, pad):
+    dtype = (h + co // 8) % 2
+    out16 = dtype if w % 2 == 0 else None
+    g = np.random.default_rng([n, h, w, co])
+    bias = g.standard_normal(co).astype(np.float32) if n % 2 else None
+    X = si.normal_bits(g, (n, h, w, 64), 1.0, dtype)
+    Wt = si.normal_bits(g, (3, 3, 64, co), 0.04, dtype)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_CONV2D, dtype=dtype, c_in=64, c_out=co, r=3, s=3, stride=1, pad=pad, m_lo=1, m_hi=1 << 22,
+                                         out_dtype=ft.FT_OUT_F32 if out16 is None else ft.FT_OUT_SAME,
+                                         epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(img_n=n, img_h=h, img_w=w))
+    M = n * (h + 2 * pad - 2) * (w + 2 * pad - 2)
+    dX, dW = dev_bits(X), dev_bits(Wt)
+    db = torch.from_numpy(bias).cuda() if bias is not None else None
+    tdt = torch.float32 if out16 is None else torch.float16 if out16 == ft.FT_F16 else torch.bfloat16
+    Y = torch.full((M * co + 2 * GUARD,), float("nan"), dtype=tdt, device="cuda")
+    Y[:GUARD] = 7.0
+    Y[-GUARD:] = 7.0
+    ft.ft_launch_epilogue(plan, dX.data_ptr(), dW.data_ptr(), Y.data_ptr() + GUARD * Y.element_size(), db.data_ptr() if db is not None else 0, stream())
+    torch.cuda.synchronize()
+    assert bool((Y[:GUARD] == 7.0).all()) and bool((Y[-GUARD:] == 7.0).all()), "write outside Y"
+    body = Y[GUARD:-GUARD].view(M, co)
+    assert bool(torch.isfinite(body).all()), "uncovered outputs"
+    pix = np.arange(M) if M * co < 1 << 20 else np.array(sorted({0, M - 1} | {int(x) for x in g.integers(0, M, 400 if co < 1024 else 40)}))
+    ref, refabs = oc.conv2d_nhwc(X, Wt, dtype, pad=pad, pixels=pix, want_abs=True)
+    ref, refabs = ref.reshape(len(pix), co), refabs.reshape(len(pix), co)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    got = body[torch.from_numpy(pix).cuda()].float().cpu().numpy().astype(np.float64)
+    check_epilogue(got, ref, refabs, bias, out16, f"{n}x{h}x{w} -> {co}, padding {pad}")
