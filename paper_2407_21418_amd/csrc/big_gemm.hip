@@ -15,7 +15,7 @@
 // 8192 x 11008 x 4096 bf16: 650 -> 562 us; 4096^3: 113 -> 97; 8192^3: 883 -> 744.
 //
 // A block is a CU's work for 60-90 us, so a last round of few blocks is expensive: the host deals the blocks that
-// would make it as halves of 128 rows (see big_schedule in device.hip), a shorter body of the same design.
+// would make it as halves of 128 rows (see big_schedule in host.cpp), a shorter body of the same design.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
