@@ -6,12 +6,14 @@
  * uKernel tiles (Sec. 3; Fig. 4(c)): each workgroup computes one tile of the output with
  * fp16/bf16 MFMA and fp32 accumulation, and the tiles of one or two uKernel shapes cover
  * the output exactly once with no padding on the main axis beyond the 16-row MFMA granule.
+ * Three kinds of work are launched in another form than their plan's tiles (FT_FORM_* below).
  *
  * The four stages follow the paper's problem statement:
  *   (a) ft_op_register      operator template + every possible shape        (Sec. 3, Sec. 4)
  *   (b) ft_ukernels_derive  uKernel set from the hardware model             (Sec. 4, Alg. 1)
  *   (c) ft_plan             uKernel-based program for one runtime shape     (Sec. 5, Alg. 2, Eq. 1)
  *   (d) ft_launch           one launch over the tile-descriptor table       (Sec. 3: uKernel = thread block)
+ *                           (ft_plan_launch_form: or over row runs, large blocks, image patches)
  *
  * Conventions
  *   - Plain C, no exceptions cross the boundary; every call returns ft_status (0 = FT_OK).
@@ -225,7 +227,10 @@ enum {
     FT_PLAN_HOST_ONLY = 16u,       /* no device table; the plan cannot be launched           */
     FT_PLAN_TABLE_ORDER = 32u      /* workgroups read their descriptors from the table even where
                                       the closed form of the tile grids would do (ft_plan_stats.
-                                      table_order); same results, for debugging and comparison  */
+                                      table_order), for debugging and comparison.  Such a plan always
+                                      launches its tiles (FT_FORM_TILES): the same results as the tiles in
+                                      closed form, bit for bit; the other forms add a sum's terms in
+                                      another order                                               */
 };
 
 /* Program to build when the mode is FT_PLAN_FORCED (used to measure every program of the
@@ -250,6 +255,8 @@ typedef struct ft_tile_desc {
     uint32_t flags;                /* bit 0: edge tile (some rows/columns predicated off)    */
 } ft_tile_desc;
 
+/* The program the planner chose.  A launch in another form than FT_FORM_TILES does not run it: what such a
+ * launch computes and asks for is in ft_plan_launch_form. */
 typedef struct ft_plan_stats {
     uint32_t struct_size;
     uint32_t tau;                  /* main axis: 0 rows (M), 1 columns (N)                   */
@@ -261,15 +268,18 @@ typedef struct ft_plan_stats {
     uint32_t pool_size;            /* programs in uProg                                      */
     uint32_t level;                /* 0: Top-1 among programs within block.bound, 1: none was      */
     uint32_t pad_q20, occ_q20, cmr_q20;   /* Eq. 2, Eq. 3, normalised Eq. 6; floor(x * 2^20) */
-    uint32_t lds_bytes;            /* dynamic LDS of the launch                              */
-    uint32_t kernel_class;         /* which dispatcher kernel runs the plan                  */
+    uint32_t lds_bytes;            /* LDS of the uKernels with their whole rings: the most a launch of the
+                                      tiles asks for (it leaves out stages that its reduce axis is too
+                                      short to use)                                          */
+    uint32_t kernel_class;         /* which dispatcher kernel runs the tiles                 */
     uint64_t sia_q20;              /* Eq. 1                                                  */
     uint64_t n_tiles;
     uint64_t useful_elems;         /* batch*M*N                                              */
-    uint64_t covered_elems;        /* sum of tm*tn over all tiles                            */
+    uint64_t covered_elems;        /* sum of tm*tn over all tiles of the program              */
     uint32_t k_parts;              /* workgroups per tile along the reduce axis (1 = no split)*/
     uint32_t k_part_tiles;         /* k-tiles (of tk) per part; the last part may get fewer  */
-    uint64_t workspace_bytes;      /* device memory the plan owns for the partial tiles      */
+    uint64_t workspace_bytes;      /* device memory the plan owns for the partial tiles (a plan that may
+                                      launch blocks keeps it: its tiles run where C is not 16-byte aligned) */
     /* Second-axis strips (operators with two dynamic space axes, Fig. 4(d)): part i places
      * main_tiles[i] tiles of its own uKernel across the other axis and, if strip_ukernel_id[i] is not
      * UINT32_MAX, strip_tiles[i] tiles of that narrower uKernel (same extent along tau) after them. */
@@ -331,7 +341,7 @@ ft_status ft_plan_group_layout(const ft_plan *plan, uint32_t group, uint64_t *of
 
 /* *descs: host pointer to library-owned memory, valid until ft_plan_destroy. */
 ft_status ft_plan_descriptors(const ft_plan *plan, const ft_tile_desc **descs, uint64_t *n);
-/* Which descriptor each workgroup of the launch takes (Sec. 3: one uKernel = one thread block):
+/* Which descriptor each workgroup of a launch of the tiles (FT_FORM_TILES) takes (Sec. 3: one uKernel = one thread block):
  * order[b] = index into the descriptor table of workgroup b, for b < min(*n, cap); *n receives
  * the number of workgroups (= tiles).  The order is a permutation of the table: every XCD (a
  * group of CUs with its own L2; workgroup b runs on XCD b % num_xcds) takes a contiguous slice of
@@ -344,6 +354,27 @@ ft_status ft_plan_descriptors(const ft_plan *plan, const ft_tile_desc **descs, u
 ft_status ft_plan_launch_order(const ft_plan *plan, uint32_t *order, uint64_t cap, uint64_t *n);
 ft_status ft_plan_stats_get(const ft_plan *plan, ft_plan_stats *out);
 void ft_plan_destroy(ft_plan *plan);
+
+/* How a launch of the plan executes.  Plans made by the planner (FT_PLAN_PATCHWORK, in closed form) whose shape
+ * one of these serves better are not launched as tiles:
+ *   FT_FORM_ROWS     whole rows of C (batched products of one k-tile whose rows of C do not lie on 64-byte blocks)
+ *   FT_FORM_BLOCKS   blocks of 256 x 256 and halves of 128 x 256 (large Matmuls; C 16-byte aligned)
+ *   FT_FORM_PATCHES  image patches (3 x 3 Conv2d of 64 input channels; C 16-byte aligned)
+ * Forced programs, pad baselines, grouped plans and FT_PLAN_TABLE_ORDER always launch tiles.  Every form keeps
+ * fp32 sums; the order of a sum's terms, and with it the last bits of a result, depends on the form. */
+enum { FT_FORM_TILES = 0, FT_FORM_ROWS = 1, FT_FORM_BLOCKS = 2, FT_FORM_PATCHES = 3 };
+typedef struct ft_launch_form {
+    uint32_t struct_size;
+    uint32_t form;                 /* FT_FORM_*                                              */
+    uint64_t workgroups;           /* TILES: tiles x parts (a grid may be rounded up beyond) */
+    uint32_t lds_bytes;            /* dynamic LDS of a workgroup; TILES: the most it can be  */
+    uint32_t reserved;             /* 0                                                      */
+    uint64_t computed_elems;       /* output elements computed, those never stored included: against
+                                      ft_plan_stats.useful_elems the launch's padding        */
+} ft_launch_form;
+/* A, B, C: the operands of the launch in question; only their alignment is looked at (NULL: aligned), so this
+ * works without a GPU and with host-only plans.  out: host pointer. */
+ft_status ft_plan_launch_form(const ft_plan *plan, const void *A, const void *B, const void *C, ft_launch_form *out);
 
 /* Scores of every program of the pool for one shape (Sec. 5.1 pool, Sec. 5.2 evaluation):
  * fills up to cap entries of out (host pointer) and stores the pool size in *n. */
@@ -358,7 +389,8 @@ ft_status ft_plan_pool(const ft_op *op, const ft_ukset *set, const ft_shape *sha
                        ft_pool_entry *out, uint32_t cap, uint32_t *n);
 
 /* ---------------------------------------------------------------------------------------
- * (d) Launch: ONE kernel launch; workgroup i runs the uKernel body named by descriptor i.
+ * (d) Launch: ONE kernel launch.  Workgroup i runs the uKernel body named by its descriptor, or its share of the
+ * form that ft_plan_launch_form names.
  *   Matmul: A [M,K], B [K,N] row-major 16-bit; C [M,N] row-major fp32 (or 16-bit, see out_dtype).
  *   BMM:    A [batch,M,K], B [batch,K,N], C [batch,M,N], densely packed.
  *   Conv2d: A = X [n,H,W,c_in], B = W [r,s,c_in,c_out], C = Y [n,P,Q,c_out] fp32.

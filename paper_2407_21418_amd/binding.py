@@ -21,6 +21,7 @@ FT_EPI_NONE, FT_EPI_BIAS = 0, 1
 FT_B_KN, FT_B_NK = 0, 1
 FT_PLAN_PATCHWORK, FT_PLAN_PAD_BASELINE, FT_PLAN_FORCED, FT_PLAN_HOST_ONLY, FT_PLAN_TABLE_ORDER = 0, 1, 2, 16, 32
 FT_SIA_LINEAR, FT_SIA_PRODUCT = 0, 1
+FT_FORM_TILES, FT_FORM_ROWS, FT_FORM_BLOCKS, FT_FORM_PATCHES = 0, 1, 2, 3
 
 u32, u64, u16 = C.c_uint32, C.c_uint64, C.c_uint16
 
@@ -87,6 +88,10 @@ class ft_plan_stats(_S):
                 ("workspace_bytes", u64), ("main_tiles", u32 * 2), ("strip_ukernel_id", u32 * 2), ("strip_tiles", u32 * 2), ("table_order", u32)]
 
 
+class ft_launch_form(_S):
+    _fields_ = [("struct_size", u32), ("form", u32), ("workgroups", u64), ("lds_bytes", u32), ("reserved", u32), ("computed_elems", u64)]
+
+
 class ft_pool_entry(C.Structure):
     _fields_ = [("k1", u32), ("count1", u32), ("k2", u32), ("count2", u32), ("pad_q20", u32),
                 ("occ_q20", u32), ("cmr_q20", u32), ("flags", u32), ("sia_q20", u64), ("n_tiles", u64)]
@@ -121,6 +126,7 @@ SYMBOLS = {
     "ft_plan_descriptors": (C.c_int32, [_P, C.POINTER(C.POINTER(ft_tile_desc)), C.POINTER(u64)]),
     "ft_plan_launch_order": (C.c_int32, [_P, C.POINTER(u32), u64, C.POINTER(u64)]),
     "ft_plan_stats_get": (C.c_int32, [_P, C.POINTER(ft_plan_stats)]),
+    "ft_plan_launch_form": (C.c_int32, [_P, _P, _P, _P, C.POINTER(ft_launch_form)]),
     "ft_plan_destroy": (None, [_P]),
     "ft_plan_pool": (C.c_int32, [_P, _P, C.POINTER(ft_shape), C.POINTER(ft_pool_entry), u32, C.POINTER(u32)]),
     "ft_launch": (C.c_int32, [_P, _P, _P, _P, _P]),
@@ -300,6 +306,13 @@ def ft_plan_stats_get(p: Plan) -> ft_plan_stats:
     st = ft_plan_stats()
     _check(lib().ft_plan_stats_get(p.ptr, C.byref(st)), "ft_plan_stats_get")
     return st
+
+
+def ft_plan_launch_form(p: Plan, A: int = 0, B: int = 0, Cptr: int = 0) -> ft_launch_form:
+    """How a launch of the plan on operands at these addresses executes (only their alignment matters)."""
+    f = ft_launch_form()
+    _check(lib().ft_plan_launch_form(p.ptr, A or None, B or None, Cptr or None, C.byref(f)), "ft_plan_launch_form")
+    return f
 
 
 def ft_plan_pool(op: Op, s: UkSet, shape: ft_shape):

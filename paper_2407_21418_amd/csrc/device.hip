@@ -300,29 +300,21 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         a.arrive = reinterpret_cast<uint32_t *>(base);
         a.ws = reinterpret_cast<float *>(base + FT_NOALLOC_COUNTER_BYTES);
     }
-    const bool even = (reinterpret_cast<uintptr_t>(A) % 2 == 0) && (reinterpret_cast<uintptr_t>(B) % 2 == 0);
-    // Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in
-    // address order (row_runs.hip has the measurements), as long as they make a workgroup per CU.  Rows on 64-byte
-    // blocks stay with the tile bodies, which write them at the same rate and read B less often (160 columns: 20.7
-    // against 24.7 us); so do launches of few rows, which tiles spread over more CUs (12 x 300 x 300: 4.2 against 5.4 us).
-    const uint32_t es_c = a.out_kind == ftk::OUT_F32 ? 4 : 2;
-    if (plan->row_runs && even && ((uint64_t)a.N * es_c % 64 != 0 || reinterpret_cast<uintptr_t>(C) % 64 != 0)) {
+    const bool out16 = a.out_kind != ftk::OUT_F32, nk = plan->op.b_layout == FT_B_NK;
+    const ft_form_choice form = ft_choose_form(plan, A, B, C);
+    if (form.form == FT_FORM_ROWS) {
         ftk::RunArgs r;
         std::memset(&r, 0, sizeof(r));
         r.A = a.A; r.B = a.B; r.C = C; r.bias = bias;
-        r.out16 = es_c == 2;
+        r.out16 = out16;
         r.num_xcds = plan->num_xcds;
         r.M = a.M; r.N = a.N; r.K = a.K;
-        r.rb_log2 = ftk::run_rb_log2(a.M, a.N, plan->st.batch, plan->num_cus);
-        r.runs = (a.M + (32u << r.rb_log2) - 1) / (32u << r.rb_log2);
-        const uint64_t n_runs = (uint64_t)plan->st.batch * r.runs;
-        if (n_runs >= plan->num_cus && n_runs < (1u << 31)) {
-            const bool nk = plan->op.b_layout == FT_B_NK;
-            r.n_runs = (uint32_t)n_runs;
-            const int rc = ft_launch_runs(&r, (int)plan->op.dtype, nk, ftk::run_lds(a.N, r.rb_log2, es_c, nk), hip_stream);
-            if (rc != 0) return hip_fail((hipError_t)rc);
-            return FT_OK;
-        }
+        r.rb_log2 = form.run_rb_log2;
+        r.runs = form.run_shares;
+        r.n_runs = plan->st.batch * form.run_shares;
+        const int rc = ft_launch_runs(&r, (int)plan->op.dtype, nk, ftk::run_lds(a.N, r.rb_log2, out16 ? 2 : 4, nk), hip_stream);
+        if (rc != 0) return hip_fail((hipError_t)rc);
+        return FT_OK;
     }
     if (!plan->groups.empty()) {
         // grouped launch: the dispatcher takes shape, pitches and operand bases from the group records
@@ -330,13 +322,12 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         a.groups = static_cast<const ftk::GroupRec *>(plan->d_groups);
         a.table_order = 1;
         a.k_parts = 1;
-        const bool out16 = a.out_kind != ftk::OUT_F32;
         const bool on_blocks = plan->grp_rows_on_blocks && reinterpret_cast<uintptr_t>(C) % 64 == 0;
         a.c_stream = (on_blocks || out16 || plan->grp_k_min > 64) ? 1u : 0u;     // as for a plain launch
         // every group aligned and the buffers too: the LDS-DMA bodies; else the general ones
         // (the LDS-DMA bodies take any 2-byte aligned operand; grp_aligned: every group's rows hold a chunk)
         const bool fast = plan->grp_aligned && reinterpret_cast<uintptr_t>(A) % 2 == 0 && reinterpret_cast<uintptr_t>(B) % 2 == 0;
-        if (plan->op.b_layout == FT_B_NK) {
+        if (nk) {
             if (!fast) return FT_ERR_UNSUPPORTED;       // no general bodies for this layout
             const int rc = kLaunchGroupedNK[plan->op.dtype][ft_class_of_acc((int)plan->grp_fast_acc)](&a, plan->grp_fast_lds, hip_stream);
             if (rc != 0) return hip_fail((hipError_t)rc);
@@ -347,27 +338,25 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }
-    if (plan->conv_th && even && reinterpret_cast<uintptr_t>(C) % 16 == 0) {
+    if (form.form == FT_FORM_PATCHES) {
+        const ft_patch_grid g = ft_patch_grid_of(plan);
         ftk::ConvArgs r;
         std::memset(&r, 0, sizeof(r));
         r.X = a.A; r.Wt = a.B; r.Y = C; r.bias = bias;
         r.H = a.H; r.W = a.W; r.P = a.P; r.Q = a.Q; r.pad = a.cpad; r.N = a.N;
         r.th = plan->conv_th; r.tw = plan->conv_tw;
-        r.tiles_y = (a.P + r.th - 1) / r.th; r.tiles_x = (a.Q + r.tw - 1) / r.tw;
-        r.tiles = a.M / (a.P * a.Q) * r.tiles_y * r.tiles_x;
-        r.cols = (a.N + 63) / 64;
-        r.walkers = plan->num_cus / r.cols < r.tiles ? plan->num_cus / r.cols : r.tiles;
+        r.tiles_y = g.tiles_y; r.tiles_x = g.tiles_x; r.tiles = g.tiles;
+        r.cols = g.cols; r.walkers = g.walkers;
         r.num_xcds = plan->num_xcds;
-        const uint32_t lds = 9 * ftk::kConvTap + ftk::conv_patch_bytes(ftk::conv_patch_rows(r.th, r.tw)) * (r.tiles > r.walkers ? 2 : 1);
-        const int rc = ft_launch_conv(&r, (int)plan->op.dtype, es_c == 2, (int)plan->conv_bm, lds, hip_stream);
+        const int rc = ft_launch_conv(&r, (int)plan->op.dtype, out16, (int)plan->conv_bm, g.lds_bytes, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }
-    if (plan->big && even && reinterpret_cast<uintptr_t>(C) % 16 == 0) {
+    if (form.form == FT_FORM_BLOCKS) {
         ftk::BigArgs r;
         std::memset(&r, 0, sizeof(r));
         r.A = a.A; r.B = a.B; r.C = C; r.bias = bias;
-        r.out16 = es_c == 2;
+        r.out16 = out16;
         r.M = a.M; r.N = a.N; r.K = a.K;
         r.rows = plan->big_rows; r.cols = plan->big_cols; r.group = 4;
         r.n_full = plan->big_full; r.n_half = plan->big_half;
@@ -382,7 +371,7 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
     // chunk from inside the row and fix it up in LDS (gemm_fast.h); that needs rows of at least one chunk.  Convolution: c_in a multiple of 64, c_out of 8, 16-byte aligned operands.  Everything
     // else takes the general bodies.
     const bool aligned = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0);
-    const bool nk = plan->op.b_layout == FT_B_NK;
+    const bool even = (reinterpret_cast<uintptr_t>(A) % 2 == 0) && (reinterpret_cast<uintptr_t>(B) % 2 == 0);
     const bool ragged = !a.is_conv && (a.K % 8 != 0 || (!nk && a.N % 8 != 0));
     bool fast = a.is_conv ? (aligned && a.Cin % 64 == 0 && a.N % 8 == 0)
                           : (even && a.K >= 8 && (nk || a.N >= 8) && !(ragged && plan->two_teams));
@@ -418,18 +407,18 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
     // three k-tiles) 11.6 -> 10.6 us.
     uint32_t lds_fast = plan->st.lds_bytes;
     if (fast && !plan->two_teams) {
-        const uint32_t nk = a.k_parts > 1 ? a.k_part_tiles : std::max<uint32_t>((a.K + FT_TK - 1) / FT_TK, 1);
+        const uint32_t k_tiles = a.k_parts > 1 ? a.k_part_tiles : std::max<uint32_t>((a.K + FT_TK - 1) / FT_TK, 1);
         lds_fast = 0;
         for (int i = 0; i < 4; ++i) {
             const int code = (int)a.slot_code[i];
             const bool splitk = ft_is_splitk_code(code);
-            const uint32_t tiles = splitk ? (nk + 3) / 4 : nk;
+            const uint32_t tiles = splitk ? (k_tiles + 3) / 4 : k_tiles;
             a.slot_stages[i] = std::max(2u, std::min(a.slot_stages[i], tiles));
             const uint32_t used = splitk ? 4 * a.slot_stages[i] : std::min(a.slot_stages[i], tiles);
             lds_fast = std::max(lds_fast, used * ft_stage_bytes_of_code(code));
         }
     }
-    if (plan->op.b_layout == FT_B_NK) {
+    if (nk) {
         if (plan->two_teams) return FT_ERR_UNSUPPORTED;      // (such an operator derives none)
         rc = kLaunchNK[plan->op.dtype][plan->st.kernel_class](&a, lds_fast, hip_stream);
     } else if (fast && plan->two_teams) {

@@ -70,6 +70,19 @@ struct ft_plan {
     uint32_t conv_th, conv_tw, conv_bm;
 };
 
+// How a launch of a plan executes with these operands (FT_FORM_*; only the addresses' alignment matters): one decision for
+// the launch itself and for ft_plan_launch_form.
+struct ft_form_choice {
+    uint32_t form;
+    uint32_t run_rb_log2, run_shares;       // FT_FORM_ROWS: 32 << run_rb_log2 rows a share, run_shares of them per batch entry
+};
+ft_form_choice ft_choose_form(const ft_plan *plan, const void *A, const void *B, const void *C);
+// FT_FORM_PATCHES: what the launch makes of the plan's tile
+struct ft_patch_grid {
+    uint32_t tiles_y, tiles_x, tiles, cols, walkers, lds_bytes;
+};
+ft_patch_grid ft_patch_grid_of(const ft_plan *plan);
+
 // device.hip
 ft_status ftd_upload(ft_plan *p);
 void ftd_release(ft_plan *p);

@@ -695,6 +695,39 @@ constexpr size_t kPlanCacheMax = 65536;      // plans a uKernel set keeps for ft
 
 void ftd_set_hip_error(int e) { g_last_hip_error = e; }
 
+ft_patch_grid ft_patch_grid_of(const ft_plan *pl) {
+    ft_patch_grid g;
+    g.tiles_y = (uint32_t)ceil_div(pl->out_p, pl->conv_th);
+    g.tiles_x = (uint32_t)ceil_div(pl->out_q, pl->conv_tw);
+    g.tiles = pl->st.m / (pl->out_p * pl->out_q) * g.tiles_y * g.tiles_x;
+    g.cols = (uint32_t)ceil_div(pl->st.n, 64);
+    g.walkers = std::min(pl->num_cus / g.cols, g.tiles);
+    g.lds_bytes = 9 * ftk::kConvTap + ftk::conv_patch_bytes(ftk::conv_patch_rows(pl->conv_th, pl->conv_tw)) * (g.tiles > g.walkers ? 2 : 1);
+    return g;
+}
+
+ft_form_choice ft_choose_form(const ft_plan *pl, const void *A, const void *B, const void *C) {
+    ft_form_choice f = {FT_FORM_TILES, 0, 0};
+    const uintptr_t a = reinterpret_cast<uintptr_t>(A), b = reinterpret_cast<uintptr_t>(B), c = reinterpret_cast<uintptr_t>(C);
+    if (a % 2 || b % 2) return f;                                     // the general bodies
+    const uint32_t es = pl->op.out_dtype == FT_OUT_SAME ? 2 : 4;
+    // Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in
+    // address order (row_runs.hip has the measurements), as long as they make a workgroup per CU.  Rows on 64-byte
+    // blocks stay with the tile bodies, which write them at the same rate and read B less often (160 columns: 20.7
+    // against 24.7 us); so do launches of few rows, which tiles spread over more CUs (12 x 300 x 300: 4.2 against 5.4 us).
+    if (pl->row_runs && ((uint64_t)pl->st.n * es % 64 || c % 64)) {
+        const uint32_t rb = ftk::run_rb_log2(pl->st.m, pl->st.n, pl->st.batch, pl->num_cus);
+        const uint32_t shares = (pl->st.m + (32u << rb) - 1) / (32u << rb);
+        const uint64_t n = (uint64_t)pl->st.batch * shares;
+        if (n >= pl->num_cus && n < (1u << 31)) { f.form = FT_FORM_ROWS; f.run_rb_log2 = rb; f.run_shares = shares; }
+        return f;
+    }
+    if (c % 16) return f;                                             // blocks and patches store 16 bytes per lane
+    if (pl->conv_th) f.form = FT_FORM_PATCHES;
+    else if (pl->big) f.form = FT_FORM_BLOCKS;
+    return f;
+}
+
 extern "C" {
 
 const char *ft_status_string(ft_status s) {
@@ -1531,6 +1564,36 @@ ft_status ft_plan_launch_order(const ft_plan *plan, uint32_t *order, uint64_t ca
 ft_status ft_plan_stats_get(const ft_plan *plan, ft_plan_stats *out) {
     if (!plan || !out) return FT_ERR_INVALID_ARG;
     *out = plan->st;
+    return FT_OK;
+}
+
+ft_status ft_plan_launch_form(const ft_plan *plan, const void *A, const void *B, const void *C, ft_launch_form *out) {
+    if (!plan || !out || out->struct_size != sizeof(ft_launch_form)) return FT_ERR_INVALID_ARG;
+    const ft_plan_stats &s = plan->st;
+    std::memset(out, 0, sizeof(*out));
+    out->struct_size = sizeof(*out);
+    out->form = FT_FORM_TILES;
+    if (s.n_tiles == 0) return FT_OK;
+    const ft_form_choice f = ft_choose_form(plan, A, B, C);
+    out->form = f.form;
+    if (f.form == FT_FORM_ROWS) {
+        out->workgroups = (uint64_t)s.batch * f.run_shares;
+        out->lds_bytes = ftk::run_lds(s.n, f.run_rb_log2, plan->op.out_dtype == FT_OUT_SAME ? 2 : 4, plan->op.b_layout == FT_B_NK);
+        out->computed_elems = (uint64_t)s.batch * ceil_by(s.m, 32) * ceil_by(s.n, 32);
+    } else if (f.form == FT_FORM_BLOCKS) {
+        out->workgroups = (uint64_t)plan->big_full + plan->big_half;
+        out->lds_bytes = 163840;
+        out->computed_elems = ((uint64_t)plan->big_full * 2 + plan->big_half) * (128 * 256);
+    } else if (f.form == FT_FORM_PATCHES) {
+        const ft_patch_grid g = ft_patch_grid_of(plan);
+        out->workgroups = (uint64_t)g.walkers * g.cols;
+        out->lds_bytes = g.lds_bytes;
+        out->computed_elems = (uint64_t)g.tiles * (64 * plan->conv_bm) * g.cols * 64;
+    } else {
+        out->workgroups = s.n_tiles * std::max<uint32_t>(s.k_parts, 1);
+        out->lds_bytes = plan->groups.empty() ? s.lds_bytes : std::max(plan->grp_fast_lds, s.lds_bytes);
+        out->computed_elems = s.covered_elems;
+    }
     return FT_OK;
 }
 

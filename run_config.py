@@ -60,7 +60,9 @@ def main():
             st = ft.ft_plan_stats_get(plan)
             ft.ft_launch_timed(plan, pa, pb, pc, stream, 2)
             ms = ft.ft_launch_timed(plan, pa, pb, pc, stream, a.iters)
-            out[name] = dict(ms=ms, covered=st.covered_elems, useful=st.useful_elems, tiles=st.n_tiles)
+            # (padding of what the launch computes, which is not the program's tiles in every form)
+            covered = ft.ft_plan_launch_form(plan, pa[0], pb[0], pc[0]).computed_elems
+            out[name] = dict(ms=ms, covered=covered, useful=st.useful_elems, tiles=st.n_tiles)
         del A, B, Cs
         torch.cuda.empty_cache()
         return dict(flops=flops, bytes=bytes_alg, **{k + "_" + kk: vv for k, v in out.items() for kk, vv in v.items()})

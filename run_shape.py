@@ -74,8 +74,11 @@ def main():
     ms = ft.ft_launch_timed(plan, pa, pb, pc, s, a.iters)
     prog = [(ft.ft_ukset_get(uks, st.ukernel_id[i]), st.count_tau[i]) for i in range(st.n_ukernels)]
     desc = " + ".join("%dx(%dx%d w%dx%d gk%d s%d)" % (c, u.tm, u.tn, u.wm, u.wn, u.gk, u.stages) for u, c in prog)
+    form = ft.ft_plan_launch_form(plan, pa[0], pb[0], pc[0])
+    if form.form != ft.FT_FORM_TILES:
+        desc = "%s (launched as %s: %d workgroups)" % (desc, ("", "rows", "blocks", "patches")[form.form], form.workgroups)
     print("%dx%dx%d %s: %s, %d tiles x %d parts, class %d, lds %d: %.2f us, %.1f TFLOP/s, %.0f GB/s" % (
-        a.m, a.n, a.k, a.dtype, desc, st.n_tiles, st.k_parts, st.kernel_class, st.lds_bytes, ms * 1e3,
+        a.m, a.n, a.k, a.dtype, desc, st.n_tiles, st.k_parts, st.kernel_class, form.lds_bytes, ms * 1e3,
         2.0 * a.m * a.n * a.k / ms / 1e9, bytes_alg / ms / 1e6), flush=True)
 
 

@@ -1,0 +1,100 @@
+"""Which form a launch takes, as ft_plan_launch_form reports it (the launch itself asks the same function): every form is
+reached by the shapes it is meant for, falls back to the tiles where an operand's alignment does not allow it, is never
+taken by plans that name their tiles, and reports what it computes."""
+import pytest
+
+import paper_2407_21418_amd as ft
+
+C0 = 1 << 20                              # an address on every alignment asked for
+
+
+def plan_of(shape, flags=ft.FT_PLAN_PATCHWORK, **desc):
+    op = ft.ft_op_register(ft.ft_op_desc(**desc))
+    uks = ft.ft_ukernels_derive(op)
+    return op, uks, ft.ft_plan_create(op, uks, shape, flags | ft.FT_PLAN_HOST_ONLY)
+
+
+def matmul(m, n, k, flags=0, **kw):
+    return plan_of(ft.ft_shape(m=m), flags, kind=ft.FT_OP_MATMUL, n=n, k=k, m_lo=1, m_hi=8192, **kw)
+
+
+def scores(b, m, n, k=64, flags=0, **kw):
+    return plan_of(ft.ft_shape(batch=b, m=m, n=n), flags, kind=ft.FT_OP_BMM, k=k, m_lo=0, m_hi=512, n_lo=0, n_hi=512, batch_hi=1200, **kw)
+
+
+def conv(n, h, w, co, flags=0, ci=64, pad=1, stride=1, **kw):
+    return plan_of(ft.ft_shape(img_n=n, img_h=h, img_w=w), flags, kind=ft.FT_OP_CONV2D, c_in=ci, c_out=co, r=3, s=3, stride=stride, pad=pad,
+                   m_lo=1, m_hi=1 << 22, **kw)
+
+
+def form(p, a=C0, b=C0, c=C0):
+    return ft.ft_plan_launch_form(p[2], a, b, c)
+
+
+@pytest.mark.parametrize("make,want", [
+    (lambda f: matmul(4096, 4096, 4096, f), ft.FT_FORM_BLOCKS),
+    (lambda f: scores(768, 131, 131, flags=f), ft.FT_FORM_ROWS),
+    (lambda f: conv(8, 224, 224, 128, f), ft.FT_FORM_PATCHES),
+], ids=["blocks", "rows", "patches"])
+def test_a_form_is_taken_by_planned_plans_only(make, want):
+    assert form(make(0)).form == want
+    assert form(make(ft.FT_PLAN_PAD_BASELINE)).form == ft.FT_FORM_TILES
+    assert form(make(ft.FT_PLAN_TABLE_ORDER)).form == ft.FT_FORM_TILES
+    op, uks, plan = make(0)
+    st = ft.ft_plan_stats_get(plan)
+    forced = ft.ft_forced_program(k1=st.ukernel_id[0], count1=st.count_tau[0], k2=st.ukernel_id[1], count2=st.count_tau[1] if st.n_ukernels > 1 else 0)
+    d = op.desc
+    shape = ft.ft_shape(batch=st.batch, m=0 if d.kind == ft.FT_OP_CONV2D else st.m, n=st.n if d.kind == ft.FT_OP_BMM else 0)
+    if d.kind == ft.FT_OP_CONV2D:
+        shape = ft.ft_shape(img_n=8, img_h=224, img_w=224)
+    same = ft.ft_plan_create(op, uks, shape, ft.FT_PLAN_FORCED | ft.FT_PLAN_HOST_ONLY, forced)
+    assert form((op, uks, same)).form == ft.FT_FORM_TILES
+    # operands at 2-byte alignment are taken, at an odd address they are not
+    assert form(make(0), C0 + 2, C0 + 6).form == want
+    assert form(make(0), C0 + 1).form == ft.FT_FORM_TILES
+    assert form(make(0), b=C0 + 3).form == ft.FT_FORM_TILES
+
+
+def test_alignment_of_c():
+    for p in (matmul(4096, 4096, 4096), conv(8, 224, 224, 128)):
+        assert form(p, c=C0 + 16).form != ft.FT_FORM_TILES
+        assert form(p, c=C0 + 8).form == ft.FT_FORM_TILES
+        assert form(p, c=C0 + 4).form == ft.FT_FORM_TILES
+    # whole rows take any C; rows on 64-byte blocks are left to the tiles as long as C is on one
+    assert form(scores(768, 131, 131), c=C0 + 4).form == ft.FT_FORM_ROWS
+    assert form(scores(768, 160, 160)).form == ft.FT_FORM_TILES
+    assert form(scores(768, 160, 160), c=C0 + 4).form == ft.FT_FORM_ROWS
+
+
+def test_what_a_form_computes():
+    """Padding is counted on what runs, not on the program that does not."""
+    p = matmul(3073, 4104, 832)
+    f, st = form(p), ft.ft_plan_stats_get(p[2])
+    assert f.form == ft.FT_FORM_BLOCKS and st.useful_elems == 3073 * 4104
+    # 12 x 17 blocks of 256 x 256 and the strip of 17 halves for the row below them, whatever the blocks of the last round become
+    assert f.computed_elems == 12 * 17 * 65536 + 17 * 32768 and f.workgroups >= 12 * 17 + 17 and f.lds_bytes == 163840
+    assert f.computed_elems > 1.09 * st.useful_elems > 1.09 * st.covered_elems * 0.99
+    f = form(scores(768, 131, 131))
+    assert f.form == ft.FT_FORM_ROWS and f.computed_elems == 768 * 160 * 160 and f.workgroups == 768 * 3
+    f = form(conv(8, 224, 224, 128))
+    st = ft.ft_plan_stats_get(conv(8, 224, 224, 128)[2])
+    assert f.form == ft.FT_FORM_PATCHES and f.workgroups == 256 and st.useful_elems <= f.computed_elems < 1.2 * st.useful_elems
+    assert 9 * 8192 < f.lds_bytes <= 163840
+    p = matmul(77, 768, 768)
+    f, st = form(p), ft.ft_plan_stats_get(p[2])
+    assert f.form == ft.FT_FORM_TILES and f.computed_elems == st.covered_elems and f.workgroups == st.n_tiles * st.k_parts and f.lds_bytes == st.lds_bytes
+
+
+def test_empty_grouped_and_bad_arguments():
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_BMM, k=64, m_lo=0, m_hi=512, n_lo=0, n_hi=512, batch_hi=768))
+    uks = ft.ft_ukernels_derive(op)
+    empty = ft.ft_plan_create(op, uks, ft.ft_shape(batch=0, m=5, n=5), ft.FT_PLAN_HOST_ONLY)
+    f = ft.ft_plan_launch_form(empty)
+    assert (f.form, f.workgroups, f.computed_elems) == (ft.FT_FORM_TILES, 0, 0)
+    g = ft.ft_plan_create_grouped(op, uks, [ft.ft_shape(batch=384, m=131, n=131), ft.ft_shape(batch=12, m=33, n=33)], ft.FT_PLAN_HOST_ONLY)
+    f, st = ft.ft_plan_launch_form(g, C0, C0, C0), ft.ft_plan_stats_get(g)
+    assert f.form == ft.FT_FORM_TILES and f.workgroups == st.n_tiles and f.computed_elems == st.covered_elems
+    out = ft.ft_launch_form()
+    out.struct_size = 4
+    assert ft.lib().ft_plan_launch_form(empty.ptr, None, None, None, out) == ft.FT_ERR_INVALID_ARG
+    assert ft.lib().ft_plan_launch_form(None, None, None, None, ft.ft_launch_form()) == ft.FT_ERR_INVALID_ARG
