@@ -19,10 +19,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <mutex>
-
 #include "big_gemm.h"
 #include "gemm_body.h"
+#include "lds_limit.h"
 
 namespace ftk {
 
@@ -276,21 +275,8 @@ __global__ __launch_bounds__(512, 2) void ft_big(BigArgs g) {
 
 template <int DT>
 static int launch(const ftk::BigArgs *g, void *stream) {
-    // the attribute is kept per device: set it once on each device this kernel is launched on
-    static std::mutex mu;
-    static bool done[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = ftk::raise_lds_limit<&ftk::ft_big<DT>>();
     if (e != hipSuccess) return (int)e;
-    if (dev < 0 || dev >= 64) return (int)hipErrorInvalidDevice;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        if (!done[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ftk::ft_big<DT>), hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
-            if (e != hipSuccess) return (int)e;
-            done[dev] = true;
-        }
-    }
     hipLaunchKernelGGL(ftk::ft_big<DT>, dim3(g->n_full + g->n_half), dim3(512), 163840, static_cast<hipStream_t>(stream), *g);
     return (int)hipGetLastError();
 }

@@ -22,10 +22,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <mutex>
-
 #include "conv_patch.h"
 #include "gemm_body.h"
+#include "lds_limit.h"
 
 namespace ftk {
 
@@ -287,21 +286,8 @@ __global__ __launch_bounds__(512, 1) void ft_conv_patch(ConvArgs g) {
 
 template <int DT, bool OUT16, int BM>
 static int launch(const ftk::ConvArgs *g, uint32_t lds_bytes, void *stream) {
-    // the attribute is kept per device: set it once on each device this kernel is launched on
-    static std::mutex mu;
-    static bool done[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = ftk::raise_lds_limit<&ftk::ft_conv_patch<DT, OUT16, BM>>();
     if (e != hipSuccess) return (int)e;
-    if (dev < 0 || dev >= 64) return (int)hipErrorInvalidDevice;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        if (!done[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ftk::ft_conv_patch<DT, OUT16, BM>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ftk::kConvLds);
-            if (e != hipSuccess) return (int)e;
-            done[dev] = true;
-        }
-    }
     hipLaunchKernelGGL((ftk::ft_conv_patch<DT, OUT16, BM>), dim3(g->walkers * g->cols), dim3(512), lds_bytes, static_cast<hipStream_t>(stream), *g);
     return (int)hipGetLastError();
 }

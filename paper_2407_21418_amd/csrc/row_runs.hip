@@ -21,6 +21,7 @@
 #include <stdint.h>
 
 #include "gemm_body.h"
+#include "lds_limit.h"
 #include "row_runs.h"
 
 namespace ftk {
@@ -214,6 +215,8 @@ __global__ __launch_bounds__(256, 4) void ft_row_runs(RunArgs g) {
 
 template <int DT, bool BNK, bool OUT16>
 static int launch(const ftk::RunArgs *g, uint32_t lds_bytes, void *stream) {
+    const hipError_t e = ftk::raise_lds_limit<&ftk::ft_row_runs<DT, BNK, OUT16>>();    // (up to 65 680 bytes: run_lds)
+    if (e != hipSuccess) return (int)e;
     hipLaunchKernelGGL((ftk::ft_row_runs<DT, BNK, OUT16>), dim3(g->n_runs), dim3(256), lds_bytes, static_cast<hipStream_t>(stream), *g);
     return (int)hipGetLastError();
 }

@@ -96,3 +96,29 @@ def check(got, ref, refabs, what=""):
 
 def matmul_op(N, K, dtype, m_hi=8192):
     return ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_MATMUL, dtype=dtype, n=N, k=K, m_lo=0, m_hi=m_hi))
+
+
+NAN16 = {ft.FT_F16: 0x7e00, ft.FT_BF16: 0x7fc0}
+
+
+def run_at(plan, A_bits, B_bits, n_out, dtype, form, bias=None, out16=None, off_a=3, off_b=5, off_c=0):
+    """As run_epilogue, with A and B at these element offsets of buffers that hold NaNs everywhere else and C `off_c`
+    elements behind a 256-byte boundary, between canaries; the launch has to take the given form (ft.FT_FORM_*)."""
+    def poisoned(bits, offset):
+        flat = np.ascontiguousarray(bits).reshape(-1)
+        buf = torch.full((flat.size + offset + 64,), NAN16[dtype], dtype=torch.int16, device="cuda")
+        buf[offset:offset + flat.size] = torch.from_numpy(flat.view(np.int16)).cuda()
+        return buf, buf.data_ptr() + 2 * offset
+    keep_a, pa = poisoned(A_bits, off_a)
+    keep_b, pb = poisoned(B_bits, off_b)
+    bias_d = torch.from_numpy(np.ascontiguousarray(bias, dtype=np.float32)).cuda() if bias is not None else None
+    tdt = torch.float32 if out16 is None else torch.float16 if out16 == ft.FT_F16 else torch.bfloat16
+    buf = torch.full((n_out + off_c + 2 * GUARD,), 7.0, dtype=tdt, device="cuda")
+    lo, hi = GUARD + off_c, GUARD + off_c + n_out
+    buf[lo:hi] = float("nan")
+    cptr = buf.data_ptr() + buf.element_size() * lo
+    assert ft.ft_plan_launch_form(plan, pa, pb, cptr).form == form, "another form than the test is about"
+    ft.ft_launch_epilogue(plan, pa, pb, cptr, bias_d.data_ptr() if bias_d is not None else 0, stream())
+    torch.cuda.synchronize()
+    assert bool((buf[:lo] == 7.0).all()) and bool((buf[hi:] == 7.0).all()), "write outside C"
+    return buf[lo:hi].double().cpu().numpy()

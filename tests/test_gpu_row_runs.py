@@ -9,7 +9,7 @@ import paper_2407_21418_amd as ft
 import synth_inputs as si
 from oracle import contraction as oc
 from oracle import epilogue as oe
-from gpu_util import check_epilogue, run_epilogue
+from gpu_util import check_epilogue, run_at, run_epilogue
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +36,19 @@ def test_whole_rows(M, N, K, batch, layout):
         ref = oe.add_bias(ref, bias)
     got = run_epilogue(plan, A, B, batch * M * N, bias, out16)
     check_epilogue(got, ref, refabs, bias, out16, f"{batch}x{M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("M,layout", [(65, ft.FT_B_NK), (128, ft.FT_B_KN), (200, ft.FT_B_NK)])
+def test_the_largest_image(M, layout):
+    """128 columns of fp32 off a 64-byte block in shares of 128 rows: the image of the outputs, 65 680 bytes, is the most
+    LDS a share asks for, and more than a kernel gets without asking for it beforehand."""
+    N, K, batch = 128, 64, 1030
+    g = np.random.default_rng([M, layout])
+    A = si.normal_bits(g, (batch, M, K), 1.0, ft.FT_F16)
+    B = si.normal_bits(g, (batch, K, N) if layout == ft.FT_B_KN else (batch, N, K), 0.2, ft.FT_F16)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_BMM, k=K, m_lo=0, m_hi=512, n_lo=0, n_hi=512, batch_hi=1200, b_layout=layout))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(batch=batch, m=M, n=N))
+    assert ft.ft_plan_launch_form(plan, 0, 0, 16).lds_bytes == 65680
+    got = run_at(plan, A, B, batch * M * N, ft.FT_F16, ft.FT_FORM_ROWS, off_c=4)
+    ref, refabs = (oc.bmm if layout == ft.FT_B_KN else oc.bmm_nk)(A, B, ft.FT_F16, want_abs=True)
+    check_epilogue(got, ref, refabs, None, None, f"{batch}x{M}x{N}x{K}")

@@ -1,9 +1,14 @@
 """Which form a launch takes, as ft_plan_launch_form reports it (the launch itself asks the same function): every form is
 reached by the shapes it is meant for, falls back to the tiles where an operand's alignment does not allow it, is never
 taken by plans that name their tiles, and reports what it computes."""
+import glob
+import os
+
 import pytest
 
 import paper_2407_21418_amd as ft
+
+CSRC = os.path.join(os.path.dirname(ft.__file__), "csrc")
 
 C0 = 1 << 20                              # an address on every alignment asked for
 
@@ -98,3 +103,15 @@ def test_empty_grouped_and_bad_arguments():
     out.struct_size = 4
     assert ft.lib().ft_plan_launch_form(empty.ptr, None, None, None, out) == ft.FT_ERR_INVALID_ARG
     assert ft.lib().ft_plan_launch_form(None, None, None, None, ft.ft_launch_form()) == ft.FT_ERR_INVALID_ARG
+
+
+def test_launchers_raise_the_limit_before_they_ask_for_lds():
+    """Whole rows of 128 fp32 columns off a 64-byte block ask for more than the 64 KB a kernel gets by itself; so do blocks,
+    patches and the tiles.  Every file that launches with dynamic LDS raises the limit."""
+    p = scores(1030, 128, 128)
+    assert form(p, c=C0 + 16).lds_bytes > 65536
+    asking = [f for f in glob.glob(os.path.join(CSRC, "*.hip")) if "extern __shared__" in open(f).read()]
+    assert len(asking) >= 4
+    for f in asking:
+        text = open(f).read()
+        assert "raise_lds_limit<" in text or "hipFuncAttributeMaxDynamicSharedMemorySize" in text, f
