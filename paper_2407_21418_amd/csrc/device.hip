@@ -8,6 +8,7 @@
 #include "ft_internal.h"
 #include "gemm_body.h"
 #include "launch_iface.h"
+#include "ring.h"
 #include "row_runs.h"
 #include "big_gemm.h"
 #include "conv_patch.h"
@@ -402,21 +403,16 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         if (e != hipSuccess) return hip_fail(e);
     }
     int rc;
-    // A reduce axis of fewer k-tiles than the ring has stages never touches the others: the launch asks only for
-    // the stages it uses, so that more workgroups fit a CU.  Measured: Q K^T and P V of 96 heads of 131 rows (one and
-    // three k-tiles) 11.6 -> 10.6 us.
     uint32_t lds_fast = plan->st.lds_bytes;
     if (fast && !plan->two_teams) {
-        const uint32_t k_tiles = a.k_parts > 1 ? a.k_part_tiles : std::max<uint32_t>((a.K + FT_TK - 1) / FT_TK, 1);
-        lds_fast = 0;
+        ftk::RingSlot ring[4];
         for (int i = 0; i < 4; ++i) {
             const int code = (int)a.slot_code[i];
-            const bool splitk = ft_is_splitk_code(code);
-            const uint32_t tiles = splitk ? (k_tiles + 3) / 4 : k_tiles;
-            a.slot_stages[i] = std::max(2u, std::min(a.slot_stages[i], tiles));
-            const uint32_t used = splitk ? 4 * a.slot_stages[i] : std::min(a.slot_stages[i], tiles);
-            lds_fast = std::max(lds_fast, used * ft_stage_bytes_of_code(code));
+            ring[i] = ftk::RingSlot{ft_is_splitk_code(code) != 0, a.slot_stages[i], ft_stage_bytes_of_code(code), 0u};
         }
+        const uint32_t k_tiles = a.k_parts > 1 ? a.k_part_tiles : std::max<uint32_t>((a.K + FT_TK - 1) / FT_TK, 1);
+        lds_fast = ftk::ring_plan(ring, 4, k_tiles, plan->st.n_tiles * a.k_parts, plan->num_cus, plan->st.lds_bytes);
+        for (int i = 0; i < 4; ++i) a.slot_stages[i] = ring[i].depth;
     }
     if (nk) {
         if (plan->two_teams) return FT_ERR_UNSUPPORTED;      // (such an operator derives none)

@@ -921,7 +921,11 @@ struct UKernelSplitK {
         const uint32_t nkw = nk > wave ? (nk - wave + 3) / 4 : 0;     // k-tiles of this wave
         uint32_t S = stages_in < 2 ? 2u : stages_in;
         if (S > (uint32_t)MAX_AHEAD + 2) S = MAX_AHEAD + 2;
-        unsigned char *ring = smem + wave * S * STAGE_BYTES;          // this wave's private ring
+        // The loop is told a depth of one more than a wave's k-tiles when the ring was planned deeper: every tile is then
+        // requested up front, and stages beyond the tiles are never touched, so the rings lie only that many apart (ring.h).
+        const uint32_t most = (nk + 3) / 4;                           // k-tiles of the busiest wave
+        const uint32_t R = S <= most ? S : (most < 2 ? 2u : most);    // stages of a wave's ring
+        unsigned char *ring = smem + wave * R * STAGE_BYTES;          // this wave's private ring
 
         uint32_t goff_a[LA], goff_b[LB];
 #pragma unroll
@@ -993,7 +997,7 @@ struct UKernelSplitK {
         };
 
         const uint32_t sbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem +
-                               wave * S * STAGE_BYTES;
+                               wave * R * STAGE_BYTES;
         const uint32_t fa_row = lane % MB;
         const uint32_t fa_addr0 = sbase + fa_row * (TK * 2) + (((lane / MB) ^ swzA(fa_row)) << 4);
         const uint32_t j16 = lane & 15u;
@@ -1080,7 +1084,7 @@ struct UKernelSplitK {
                 float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
-                    const float4 x = reinterpret_cast<const float4 *>(smem + w * S * STAGE_BYTES)[(wave * (PER / 4) + q / 4) * 64 + lane];
+                    const float4 x = reinterpret_cast<const float4 *>(smem + w * R * STAGE_BYTES)[(wave * (PER / 4) + q / 4) * 64 + lane];
                     sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
                 }
                 fin[q] = sum.x; fin[q + 1] = sum.y; fin[q + 2] = sum.z; fin[q + 3] = sum.w;
@@ -1100,7 +1104,7 @@ struct UKernelSplitK {
             float sum = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w)
-                sum += reinterpret_cast<const float *>(smem + w * S * STAGE_BYTES)[(wave * PER + q) * 64 + lane];
+                sum += reinterpret_cast<const float *>(smem + w * R * STAGE_BYTES)[(wave * PER + q) * 64 + lane];
             fin[q] = sum;
         }
         }
