@@ -706,20 +706,41 @@ ft_patch_grid ft_patch_grid_of(const ft_plan *pl) {
     return g;
 }
 
+namespace {
+// Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in address
+// order (row_runs.hip), or the program's tiles.  Rows on 64-byte blocks stay with the tiles, which write them at the same
+// rate and read B less often (160 columns: 20.7 against 24.7 us).  Otherwise the rows are faster, but for three kinds of
+// launches (2056 shapes with both forms: 8 to 320 columns, 1 to 512 rows, 24 to 768 matrices; us, rows against tiles):
+//   - less than a workgroup per CU, which tiles spread over more of them (12 x 300 x 300: 5.4 / 4.2);
+//   - more than 128 columns, where the rows make fewer than two and a half workgroups per CU and the tiles few more, and
+//     those not large: a workgroup's path through its columns is the whole time, and tiles share it out (96 x 131 x 131:
+//     5.2 / 4.8, 48 x 190 x 190: 5.4 / 4.6, 384 x 1 x 131: 4.9 / 4.0; not with larger tiles, 192 x 128 x 190: 8.5 / 9.7,
+//     48 x 512 x 258: 9.7 / 11.3);
+//   - more than 256 columns, whose 32-row shares read all of B for about as many bytes of C: long launches of tall matrices in
+//     fp32, where the program has fewer tiles than 0.7 of the shares (768 x 512 x 300: 136 / 112), and with B as [K][N], which
+//     costs a share more, about as many tiles as shares where those are less than four per CU (96 x 270 x 270: 14.4 / 13.0; not
+//     with many tiles, 48 x 300 x 300: 9.2 / 10.1) or, in fp32, fewer tiles than shares (768 x 319 x 319: 101 / 90; with B as
+//     [N][K] 84 / 87).
+bool rows_beat_tiles(const ft_plan *pl, uint64_t n, uint32_t es, bool nk) {
+    const uint64_t cus = pl->num_cus, tiles = pl->st.n_tiles, N = pl->st.n, M = pl->st.m;
+    if (n < cus || n >= (1u << 31)) return false;
+    if (N > 128 && 2 * n < 5 * cus && tiles <= (N > 256 ? 2 : 3) * cus && pl->st.useful_elems < (N > 256 ? 14000 : 6000) * tiles) return false;
+    if (N > 256 && es == 4 && M >= 400 && n >= 8 * cus && 10 * tiles < 7 * n) return false;
+    if (N > 256 && !nk && M > 256 && 10 * tiles >= 7 * n && (n < 4 * cus ? 4 * tiles < 5 * n : es == 4 && tiles < n)) return false;
+    return true;
+}
+}  // namespace
+
 ft_form_choice ft_choose_form(const ft_plan *pl, const void *A, const void *B, const void *C) {
     ft_form_choice f = {FT_FORM_TILES, 0, 0};
     const uintptr_t a = reinterpret_cast<uintptr_t>(A), b = reinterpret_cast<uintptr_t>(B), c = reinterpret_cast<uintptr_t>(C);
     if (a % 2 || b % 2) return f;                                     // the general bodies
     const uint32_t es = pl->op.out_dtype == FT_OUT_SAME ? 2 : 4;
-    // Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in
-    // address order (row_runs.hip has the measurements), as long as they make a workgroup per CU.  Rows on 64-byte
-    // blocks stay with the tile bodies, which write them at the same rate and read B less often (160 columns: 20.7
-    // against 24.7 us); so do launches of few rows, which tiles spread over more CUs (12 x 300 x 300: 4.2 against 5.4 us).
     if (pl->row_runs && ((uint64_t)pl->st.n * es % 64 || c % 64)) {
-        const uint32_t rb = ftk::run_rb_log2(pl->st.m, pl->st.n, pl->st.batch, pl->num_cus);
+        const bool nk = pl->op.b_layout == FT_B_NK;
+        const uint32_t rb = ftk::run_rb_log2(pl->st.m, pl->st.n, pl->st.batch, es, nk, pl->num_cus);
         const uint32_t shares = (pl->st.m + (32u << rb) - 1) / (32u << rb);
-        const uint64_t n = (uint64_t)pl->st.batch * shares;
-        if (n >= pl->num_cus && n < (1u << 31)) { f.form = FT_FORM_ROWS; f.run_rb_log2 = rb; f.run_shares = shares; }
+        if (rows_beat_tiles(pl, (uint64_t)pl->st.batch * shares, es, nk)) { f.form = FT_FORM_ROWS; f.run_rb_log2 = rb; f.run_shares = shares; }
         return f;
     }
     if (c % 16) return f;                                             // blocks and patches store 16 bytes per lane

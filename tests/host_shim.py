@@ -29,7 +29,9 @@ void shim_block(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32
     out[0] = t.m0; out[1] = t.n0; out[2] = t.half;
 }
 uint32_t shim_run_lds(uint32_t n, uint32_t rb_log2, uint32_t es, int bnk) { return ftk::run_lds(n, rb_log2, es, bnk != 0); }
-uint32_t shim_run_rb_log2(uint32_t m, uint32_t n, uint64_t batch, uint32_t cus) { return ftk::run_rb_log2(m, n, batch, cus); }
+uint32_t shim_run_rb_log2(uint32_t m, uint32_t n, uint64_t batch, uint32_t es, int bnk, uint32_t cus) {
+    return ftk::run_rb_log2(m, n, batch, es, bnk != 0, cus);
+}
 uint32_t shim_run_pitch(uint32_t n) { return ftk::run_kn_pitch(n); }
 uint32_t shim_patch_bytes(uint32_t th, uint32_t tw) { return ftk::conv_patch_bytes(ftk::conv_patch_rows(th, tw)); }
 }
@@ -50,7 +52,7 @@ def load():
     u32, u64, p = C.c_uint32, C.c_uint64, C.POINTER(C.c_uint32)
     lib.shim_ring.argtypes, lib.shim_ring.restype = [C.c_int, p, p, p, u32, u64, u32, u32, p], u32
     lib.shim_block.argtypes, lib.shim_block.restype = [u32] * 7 + [p], None
-    for name, args in (("run_lds", [u32, u32, u32, C.c_int]), ("run_rb_log2", [u32, u32, u64, u32]), ("run_pitch", [u32]), ("patch_bytes", [u32, u32])):
+    for name, args in (("run_lds", [u32, u32, u32, C.c_int]), ("run_rb_log2", [u32, u32, u64, u32, C.c_int, u32]), ("run_pitch", [u32]), ("patch_bytes", [u32, u32])):
         fn = getattr(lib, "shim_" + name)
         fn.argtypes, fn.restype = args, u32
     return lib

@@ -52,3 +52,29 @@ def test_the_largest_image(M, layout):
     got = run_at(plan, A, B, batch * M * N, ft.FT_F16, ft.FT_FORM_ROWS, off_c=4)
     ref, refabs = (oc.bmm if layout == ft.FT_B_KN else oc.bmm_nk)(A, B, ft.FT_F16, want_abs=True)
     check_epilogue(got, ref, refabs, None, None, f"{batch}x{M}x{N}x{K}")
+
+
+# (M, N, K, batch): every share height (32, 64 and 128 rows), one to ten column blocks, short reduce axes
+ANYWHERE = [(1, 9, 64, 600), (33, 33, 64, 768), (64, 65, 8, 700), (65, 127, 56, 800), (129, 100, 64, 520), (100, 131, 64, 768), (33, 191, 64, 700),
+            (70, 257, 24, 300), (40, 319, 64, 700), (31, 8, 16, 512)]
+
+
+@pytest.mark.parametrize("layout", [ft.FT_B_KN, ft.FT_B_NK], ids=["kn", "nk"])
+@pytest.mark.parametrize("M,N,K,batch", ANYWHERE)
+def test_whole_rows_anywhere_in_memory(M, N, K, batch, layout):
+    """Operands at odd element offsets among NaNs, C off every alignment but its element's; the launch is in whole rows."""
+    dtype = (M + N + layout) % 2
+    out16 = None if (N + K + layout) % 3 else dtype
+    g = np.random.default_rng([M, N, K, layout, 1])
+    A = si.normal_bits(g, (batch, M, K), 1.0, dtype)
+    B = si.normal_bits(g, (batch, K, N) if layout == ft.FT_B_KN else (batch, N, K), 0.2, dtype)
+    bias = g.standard_normal(N).astype(np.float32) if M % 2 else None
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_BMM, dtype=dtype, k=K, m_lo=0, m_hi=512, n_lo=0, n_hi=512, batch_hi=1200, b_layout=layout,
+                                         out_dtype=ft.FT_OUT_F32 if out16 is None else ft.FT_OUT_SAME,
+                                         epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(batch=batch, m=M, n=N))
+    ref, refabs = (oc.bmm if layout == ft.FT_B_KN else oc.bmm_nk)(A, B, dtype, want_abs=True)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    got = run_at(plan, A, B, batch * M * N, dtype, ft.FT_FORM_ROWS, bias, out16, off_c=1 + M % 7)
+    check_epilogue(got, ref, refabs, bias, out16, f"{batch}x{M}x{N}x{K}")

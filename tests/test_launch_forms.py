@@ -6,6 +6,7 @@ import os
 
 import pytest
 
+import host_shim
 import paper_2407_21418_amd as ft
 
 CSRC = os.path.join(os.path.dirname(ft.__file__), "csrc")
@@ -115,3 +116,39 @@ def test_launchers_raise_the_limit_before_they_ask_for_lds():
     for f in asking:
         text = open(f).read()
         assert "raise_lds_limit<" in text or "hipFuncAttributeMaxDynamicSharedMemorySize" in text, f
+
+
+def test_whole_rows_are_taken_where_they_measured_faster():
+    rows, tiles = ft.FT_FORM_ROWS, ft.FT_FORM_TILES
+    for b, m, n, layout, out, want in [
+            (768, 131, 131, ft.FT_B_NK, ft.FT_OUT_F32, rows), (768, 300, 300, ft.FT_B_KN, ft.FT_OUT_F32, rows), (96, 100, 100, ft.FT_B_NK, ft.FT_OUT_F32, rows),
+            (12, 300, 300, ft.FT_B_NK, ft.FT_OUT_F32, tiles),          # fewer workgroups than CUs
+            (96, 131, 131, ft.FT_B_NK, ft.FT_OUT_F32, tiles), (48, 190, 190, ft.FT_B_NK, ft.FT_OUT_F32, tiles), (384, 1, 131, ft.FT_B_NK, ft.FT_OUT_F32, tiles),
+            (192, 128, 190, ft.FT_B_NK, ft.FT_OUT_F32, rows), (768, 1, 131, ft.FT_B_NK, ft.FT_OUT_F32, rows),
+            (768, 512, 300, ft.FT_B_NK, ft.FT_OUT_F32, tiles), (768, 512, 300, ft.FT_B_NK, ft.FT_OUT_SAME, rows),
+            (768, 319, 319, ft.FT_B_KN, ft.FT_OUT_F32, tiles), (768, 319, 319, ft.FT_B_NK, ft.FT_OUT_F32, rows)]:
+        p = scores(b, m, n, b_layout=layout, out_dtype=out)
+        assert form(p).form == want, (b, m, n, layout, out, ft.ft_plan_stats_get(p[2]).n_tiles)
+
+
+def test_height_and_lds_of_a_share():
+    lib = host_shim.load()
+    for n in list(range(8, 193)) + list(range(257, 321)):
+        for es in (2, 4):
+            for bnk in (0, 1):
+                for rb in range(3):
+                    lds = lib.shim_run_lds(n, rb, es, bnk)
+                    blocks = (n + 31) // 32
+                    a, b = 32 * 128 << rb, blocks * 32 * 128 if bnk else 64 * 16 * lib.shim_run_pitch(n)
+                    image = 127 + (32 << rb) * n * es          # furthest byte of the run's image, from any phase of a 128-byte line,
+                    assert lds >= a + b and lds >= (image + 15) // 16 * 16 + 16 and lds % 16 == 0    # and the chunk behind it that is read along
+                    assert lib.shim_run_pitch(n) * 8 >= blocks * 32
+                for m in (1, 31, 33, 65, 129, 300, 512):
+                    for batch in (1, 100, 256, 768, 5000):
+                        rb = lib.shim_run_rb_log2(m, n, batch, es, bnk, 256)
+                        assert rb <= (2 if n <= 128 else 1 if n <= 256 else 0)      # four accumulator blocks per wave
+                        if rb:
+                            assert batch * -(-m // (32 << rb)) >= 3 * 256
+    # (rows, columns, matrices) -> height: three shares per CU that are all held at once; not if a second round has few
+    assert lib.shim_run_rb_log2(33, 33, 768, 4, 1, 256) == 1 and lib.shim_run_rb_log2(33, 33, 384, 4, 1, 256) == 0
+    assert lib.shim_run_rb_log2(190, 190, 288, 4, 1, 256) == 0 and lib.shim_run_rb_log2(190, 190, 288, 2, 1, 256) == 1
