@@ -627,8 +627,15 @@ uint64_t conv_tile(uint32_t P, uint32_t Q, uint32_t pixels, uint32_t lds, uint32
 // 3 x 3 filters over 64 channels, stride 1 (conv_patch.hip).  Its taps are unrolled and its patch rows are one pixel's 64
 // channels; with a stride the patch holds stride^2 pixels per output (8 x 112 x 112, stride 2: 11.3 us against the gather's
 // 11.2).  Every workgroup walks the same number of tiles, so a tile of 64 * bm pixels costs rounds * (0.6 + bm): measured on
-// 8 x 224 x 224 1.9, 2.9, 4.2 and 5.7 us per round for bm = 1 .. 4.  In time against the gather (us, fp32 results): 28^2
-// 5.2 / 6.6, 45^2 8.2 / 8.1, 56^2 9.9 / 10.8, 91^2 16 / 23, 150^2 37 / 41, 224^2 74 / 89: no size is left to the gather.
+// 8 x 224 x 224 1.9, 2.9, 4.2 and 5.7 us per round for bm = 1 .. 4.
+//
+// Where a workgroup has one tile the patches are the faster form (8 images, 128 channels: 28^2 5.1 / 6.2 us, 56^2 9.8 / 10.9; the
+// exception seen is one image with thousands of channels, 28^2 with 4096: 12.0 / 10.9).  With more, a short last round costs a whole one, which the gather's smaller tiles avoid where all of them
+// are resident at once (80^2 17.0 / 15.7, one round later 92^2 19.0 / 24.2); and an image smaller than a tile fills one
+// all the same (1000 images of 5 x 5, 384 channels: 44 / 23).  Both forms have a reduce axis of nine k-tiles, so their times
+// are estimated in us from the shapes alone: constants fitted to 1206 layers (1 to 1000 images, 2 to 400 pixels across, 8 to
+// 512 channels, both result types), where the choice below is slower than the other form by more than 3 % on 34, the
+// patches alone on 122 and up to six times.
 void conv_schedule(ft_plan *pl) {
     const ft_op_desc &d = pl->op;
     const uint64_t P = pl->out_p, Q = pl->out_q, cols = ceil_div(d.c_out, 64);
@@ -636,13 +643,31 @@ void conv_schedule(ft_plan *pl) {
     if (P == 0 || Q == 0 || P > 32000 || Q > 32000 || P * Q * d.c_out >= (1u << 29)) return;     // 16-bit coordinates; results of an image below 2^31 bytes
     const uint64_t images = pl->st.m / (P * Q), walkers = pl->num_cus / cols;
     double best = 0;
+    uint64_t rounds = 0;
+    uint32_t best_th = 0, best_tw = 0, best_bm = 0;
     for (uint32_t bm = 1; bm <= 4; ++bm) {
         uint32_t th = 0, tw = 0;
         const uint64_t tiles = images * conv_tile((uint32_t)P, (uint32_t)Q, 64 * bm, ftk::kConvPatchRoom, &th, &tw);
         if (tiles == 0 || tiles >= (1u << 31)) continue;
         const double cost = (double)ceil_div(tiles, walkers) * (0.6 + bm);
-        if (best == 0 || cost < best) { best = cost; pl->conv_th = th; pl->conv_tw = tw; pl->conv_bm = bm; }
+        if (best == 0 || cost < best) { best = cost; rounds = ceil_div(tiles, walkers); best_th = th; best_tw = tw; best_bm = bm; }
     }
+    if (best == 0) return;
+    const uint64_t n = pl->st.n_tiles, cus = pl->num_cus;
+    if (rounds > 1 && (n <= 2 * cus || best_bm == 1)) {               // (more tiles than are resident: the gather loses its rounds too)
+        double side = 0;
+        bool slow = false;                                            // one tile per CU at a time, or tiles that only the general bodies have
+        for (int i = 0; i < 2; ++i) {
+            if (i == 1 && pl->st.n_ukernels < 2) break;
+            side = std::max(side, (double)(pl->slot_tm[i] + pl->slot_tn[i]));
+            slow = slow || pl->slot_tm[i] * pl->slot_tn[i] > 128 * 128 || ft_is_partial_code(ft_general_code((int)pl->slot_code[i]));
+        }
+        const double gather = std::max(5.4, 2.4 + 0.031 * side) * (n <= cus ? 1.0 : 1.45 * (double)ceil_div(n, 2 * cus)) * (slow ? 2 : 1);
+        const double patches = best_bm == 1 ? 3.0 + 1.55 * (double)rounds
+                                            : (3.5 + (double)rounds * (0.3 + 1.6 * best_bm)) * (d.out_dtype == FT_OUT_SAME ? 0.85 : 1.0);
+        if (patches > 1.03 * gather) return;
+    }
+    pl->conv_th = best_th; pl->conv_tw = best_tw; pl->conv_bm = best_bm;
 }
 
 int level_of(const Program &p) { return p.in_bound ? 0 : 1; }

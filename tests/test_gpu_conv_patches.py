@@ -9,7 +9,7 @@ import paper_2407_21418_amd as ft
 import synth_inputs as si
 from oracle import contraction as oc
 from oracle import epilogue as oe
-from gpu_util import GUARD, check_epilogue, dev_bits, stream
+from gpu_util import GUARD, check_epilogue, dev_bits, run_at, stream
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,35 @@ def test_patches(n, h, w, co, pad):
         ref = oe.add_bias(ref, bias)
     got = body[torch.from_numpy(pix).cuda()].float().cpu().numpy().astype(np.float64)
     check_epilogue(got, ref, refabs, bias, out16, f"{n}x{h}x{w} -> {co}, padding {pad}")
+
+
+# (images, height, width, output channels, padding): one tile and several per workgroup, each tile height (1 to 4 blocks of 16
+# pixels per wave), channels that end inside a block
+ANYWHERE = [(1, 5, 3, 8, 1), (5, 17, 33, 128, 0), (2, 40, 40, 72, 1), (8, 50, 50, 128, 1), (8, 92, 92, 128, 1), (1, 64, 300, 200, 3), (3, 131, 57, 16, 2)]
+
+
+@pytest.mark.parametrize("out", [ft.FT_OUT_F32, ft.FT_OUT_SAME], ids=["f32", "same"])
+@pytest.mark.parametrize("n,h,w,co,pad", ANYWHERE)
+def test_patches_anywhere_in_memory(n, h, w, co, pad, out):
+    """Image and filter at odd element offsets among NaNs (the gather's bodies want 16 bytes), the launch is in patches; with an
+    output off 16 bytes it is in tiles, with the same results."""
+    dtype = (h + n) % 2
+    out16 = dtype if out == ft.FT_OUT_SAME else None
+    g = np.random.default_rng([n, h, w, co, pad])
+    bias = g.standard_normal(co).astype(np.float32) if h % 2 else None
+    X = si.normal_bits(g, (n, h, w, 64), 1.0, dtype)
+    Wt = si.normal_bits(g, (3, 3, 64, co), 0.04, dtype)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_CONV2D, dtype=dtype, c_in=64, c_out=co, r=3, s=3, stride=1, pad=pad, m_lo=1, m_hi=1 << 22,
+                                         out_dtype=out, epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(img_n=n, img_h=h, img_w=w))
+    M = n * (h + 2 * pad - 2) * (w + 2 * pad - 2)
+    pix = np.arange(M) if M * co < 1 << 19 else np.array(sorted({0, M - 1} | {int(x) for x in g.integers(0, M, 400)}))
+    ref, refabs = oc.conv2d_nhwc(X, Wt, dtype, pad=pad, pixels=pix, want_abs=True)
+    ref, refabs = ref.reshape(len(pix), co), refabs.reshape(len(pix), co)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    per16 = 4 if out16 is None else 8                                  # elements of 16 bytes
+    for off_c, form in ((per16, ft.FT_FORM_PATCHES), (1, ft.FT_FORM_TILES)):
+        got = run_at(plan, X, Wt, M * co, dtype, form, bias, out16, off_c=off_c).reshape(M, co)
+        assert np.isfinite(got).all(), "uncovered outputs"
+        check_epilogue(got[pix], ref, refabs, bias, out16, f"{n}x{h}x{w} -> {co}, padding {pad}, form {form}")

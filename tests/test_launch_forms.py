@@ -152,3 +152,17 @@ def test_height_and_lds_of_a_share():
     # (rows, columns, matrices) -> height: three shares per CU that are all held at once; not if a second round has few
     assert lib.shim_run_rb_log2(33, 33, 768, 4, 1, 256) == 1 and lib.shim_run_rb_log2(33, 33, 384, 4, 1, 256) == 0
     assert lib.shim_run_rb_log2(190, 190, 288, 4, 1, 256) == 0 and lib.shim_run_rb_log2(190, 190, 288, 2, 1, 256) == 1
+
+
+def test_patches_are_taken_where_they_measured_faster():
+    patches, tiles = ft.FT_FORM_PATCHES, ft.FT_FORM_TILES
+    for n, size, co, out, want in [
+            (8, 28, 128, ft.FT_OUT_F32, patches), (8, 56, 128, ft.FT_OUT_F32, patches), (8, 224, 128, ft.FT_OUT_F32, patches), (1, 7, 8, ft.FT_OUT_F32, patches),
+            (8, 80, 128, ft.FT_OUT_F32, tiles), (8, 80, 128, ft.FT_OUT_SAME, patches), (8, 92, 128, ft.FT_OUT_F32, patches),
+            (8, 56, 256, ft.FT_OUT_F32, tiles), (1, 28, 8200, ft.FT_OUT_F32, patches),
+            (256, 3, 256, ft.FT_OUT_F32, tiles), (1000, 5, 384, ft.FT_OUT_SAME, tiles), (1000, 2, 512, ft.FT_OUT_F32, tiles), (64, 14, 64, ft.FT_OUT_F32, patches),
+            (8, 112, 16, ft.FT_OUT_F32, patches)]:
+        p = conv(n, size, size, co, out_dtype=out)
+        assert form(p).form == want, (n, size, co, out)
+    assert form(conv(8, 56, 56, 128, ci=128)).form == tiles and form(conv(8, 56, 56, 128, stride=2)).form == tiles
+    assert form(conv(8, 56, 56, 132)).form == tiles
