@@ -573,7 +573,10 @@ bool better(const Program &a, const Program &b) {      // Top-1 order: SIA, then
 // that the program's smaller tiles are faster (K = 4096, blocks against tiles: 403 x 11008 54 against 61 us at 67 % busy,
 // 1200 x 4096 53 against 54 at 62 %; 1100 x 4096 53 against 49 at 56 %, 700 x 11008 86 against 84 at 50 %), and from twelve
 // k-tiles on (8192 x 3072 x 768: 43 against 52 us), so that the first copies and the stores of a block do not dominate;
-// halves alone want 32 (2048 x 3072 x 768: 17.6 against 15.7 us, x 2048: 29 against 32).
+// halves alone want 32 (2048 x 3072 x 768: 17.6 against 15.7 us, x 2048: 29 against 32).  fp32 results take twice as long to
+// store, which nothing hides in a CU's one block; up to 24 k-tiles they are left to the program's tiles unless the device is
+// busy for 85 % of the schedule (621 shapes timed in both forms, blocks against tiles: 5000 x 4096 x 768 52.6 / 44.4 us, 6000 x
+// 8192 x 768 91 / 97), and for more than one round if those tiles are as large (8192 x 8192 x 1024 179 / 158).
 void big_schedule(ft_plan *pl) {
     const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
     if (K % 64 || K < 12 * 64 || N % 8 || P == 0) return;
@@ -598,6 +601,8 @@ void big_schedule(ft_plan *pl) {
     const uint64_t full = blocks - halved, half = strip + 2 * halved;
     if ((full * kBlock + half * kHalf) * 10 < 6 * best * P) return;
     if (full == 0 && K < 2048) return;
+    if (pl->op.out_dtype == FT_OUT_F32 && K < 24 * 64 &&
+        ((full * kBlock + half * kHalf) * 20 < 17 * best * P || (best > kBlock + kHalf && pl->slot_tm[0] * pl->slot_tn[0] >= 256 * 256))) return;
     if (M * N * 20 < 9 * (full * 2 + half) * 256 * 128) return;
     pl->big = true;
     pl->big_rows = (uint32_t)rows; pl->big_cols = (uint32_t)cols;

@@ -9,7 +9,7 @@ import paper_2407_21418_amd as ft
 import synth_inputs as si
 from oracle import contraction as oc
 from oracle import epilogue as oe
-from gpu_util import GUARD, check_epilogue, dev_bits, stream
+from gpu_util import GUARD, check_epilogue, dev_bits, run_at, stream
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,34 @@ def test_blocks(M, N, K):
         ref = oe.add_bias(ref, bias)
     got = body[torch.from_numpy(rows).cuda()].float().cpu().numpy().astype(np.float64)
     check_epilogue(got, ref, refabs, bias, out16, f"{M}x{N}x{K}")
+
+
+# (M, N, K): rows and columns that end inside a block, the strip below the grid, halves alone, one tile column; the shortest reduce
+# axis and every remainder of the two rings (five slots, three stages)
+ANYWHERE = [(3073, 4104, 832), (3200, 4088, 896), (2049, 8192, 1024), (8191, 2056, 768), (1400, 11008, 960), (600, 11008, 2048), (130, 70000, 2112)]
+
+
+@pytest.mark.parametrize("out", [ft.FT_OUT_F32, ft.FT_OUT_SAME], ids=["f32", "same"])
+@pytest.mark.parametrize("M,N,K", ANYWHERE)
+def test_blocks_anywhere_in_memory(M, N, K, out):
+    """A and B at odd element offsets among NaNs, the launch is in blocks; with C off 16 bytes it is in tiles, within the same bounds.
+    (fp32 results with a short reduce axis are launched in tiles: those take a longer one here.)"""
+    K = K + 768 if out == ft.FT_OUT_F32 and K < 1536 else K
+    dtype = (M + N // 8) % 2
+    out16 = dtype if out == ft.FT_OUT_SAME else None
+    g = np.random.default_rng([M, N, K, 1])
+    bias = g.standard_normal(N).astype(np.float32) if M % 2 else None
+    A = si.normal_bits(g, (M, K), 1.0, dtype)
+    B = si.normal_bits(g, (K, N), 0.02, dtype)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_MATMUL, dtype=dtype, n=N, k=K, m_lo=1, m_hi=8192, out_dtype=out,
+                                         epilogue=ft.FT_EPI_NONE if bias is None else ft.FT_EPI_BIAS))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(m=M))
+    edges = {r for e in range(0, M + 1, 128) for r in (e - 1, e) if 0 <= r < M}
+    rows = np.array(sorted(set(sorted(edges)[-24:]) | {0, 127, 128, M - 1} & set(range(M)) | {int(x) for x in g.integers(0, M, 12)}))
+    ref, refabs = oc.matmul(A, B, dtype, rows=rows, want_abs=True)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    for off_c, form in ((4 if out16 is None else 8, ft.FT_FORM_BLOCKS), (2, ft.FT_FORM_TILES)):
+        got = run_at(plan, A, B, M * N, dtype, form, bias, out16, off_c=off_c).reshape(M, N)
+        assert np.isfinite(got).all(), "uncovered outputs"
+        check_epilogue(got[rows], ref, refabs, bias, out16, f"{M}x{N}x{K} form {form}")

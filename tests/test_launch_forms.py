@@ -74,7 +74,7 @@ def test_alignment_of_c():
 
 def test_what_a_form_computes():
     """Padding is counted on what runs, not on the program that does not."""
-    p = matmul(3073, 4104, 832)
+    p = matmul(3073, 4104, 832, out_dtype=ft.FT_OUT_SAME)
     f, st = form(p), ft.ft_plan_stats_get(p[2])
     assert f.form == ft.FT_FORM_BLOCKS and st.useful_elems == 3073 * 4104
     # 12 x 17 blocks of 256 x 256 and the strip of 17 halves for the row below them, whatever the blocks of the last round become
@@ -166,3 +166,46 @@ def test_patches_are_taken_where_they_measured_faster():
         assert form(p).form == want, (n, size, co, out)
     assert form(conv(8, 56, 56, 128, ci=128)).form == tiles and form(conv(8, 56, 56, 128, stride=2)).form == tiles
     assert form(conv(8, 56, 56, 132)).form == tiles
+
+
+def test_blocks_are_taken_where_they_measured_faster():
+    blocks, tiles = ft.FT_FORM_BLOCKS, ft.FT_FORM_TILES
+    for m, n, k, out, want in [
+            (8192, 11008, 4096, ft.FT_OUT_SAME, blocks), (4096, 4096, 4096, ft.FT_OUT_F32, blocks), (403, 11008, 4096, ft.FT_OUT_F32, blocks),
+            (403, 4096, 4096, ft.FT_OUT_F32, tiles), (2048, 3072, 768, ft.FT_OUT_F32, tiles), (2048, 3072, 2048, ft.FT_OUT_F32, blocks),
+            (5000, 4096, 768, ft.FT_OUT_F32, tiles), (5000, 4096, 768, ft.FT_OUT_SAME, blocks), (6000, 8192, 768, ft.FT_OUT_F32, blocks),
+            (8192, 8192, 1024, ft.FT_OUT_F32, tiles), (8192, 8192, 1024, ft.FT_OUT_SAME, blocks), (8192, 8192, 1536, ft.FT_OUT_F32, blocks),
+            (4096, 4096, 768, ft.FT_OUT_F32, blocks), (4096, 4096, 704, ft.FT_OUT_SAME, tiles), (4096, 4096, 4104, ft.FT_OUT_SAME, tiles)]:
+        p = matmul(m, n, k, out_dtype=out)
+        assert form(p).form == want, (m, n, k, out)
+    assert form(matmul(4096, 4096, 4096, b_layout=ft.FT_B_NK)).form == tiles and form(matmul(4096, 4092, 4096)).form == tiles
+
+
+@pytest.mark.parametrize("cus,xcds", [(256, 8), (80, 8), (256, 1), (7, 3)])
+def test_blocks_cover_c_once(cus, xcds):
+    """Every element of C lies in exactly one block, half or strip of the launch the plan describes, for whatever device it is
+    planned."""
+    import numpy as np
+    hw = ft.ft_hw_default_gfx950()
+    hw.num_cus, hw.num_xcds = cus, xcds
+    taken = 0
+    for m, n, k in [(4096, 4096, 1024), (3073, 4104, 832), (3200, 4088, 896), (2049, 8192, 1024), (600, 11008, 2048), (130, 8200, 2048), (8191, 2056, 1536),
+                    (4000, 3000, 768), (1, 8, 768), (257, 264, 2048)]:
+        op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_MATMUL, n=n, k=k, m_lo=1, m_hi=8192, out_dtype=ft.FT_OUT_SAME))
+        plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op, hw), ft.ft_shape(m=m), ft.FT_PLAN_HOST_ONLY)
+        f = ft.ft_plan_launch_form(plan)
+        if f.form != ft.FT_FORM_BLOCKS:
+            continue
+        taken += 1
+        rows, cols = m // 256 + (m % 256 > 128), -(-n // 256)
+        half = 2 * f.workgroups - f.computed_elems // (128 * 256)           # full * 2 + half = computed, full + half = workgroups
+        full = f.workgroups - half
+        seen = np.zeros((-(-m // 128), cols), int)
+        for b in range(f.workgroups):
+            m0, n0, is_half = host_shim.block(b, rows, cols, 4, full, half, xcds)
+            assert m0 % 128 == 0 and n0 % 256 == 0 and is_half == (b >= full)
+            seen[m0 // 128, n0 // 256] += 1
+            if not is_half and m0 // 128 + 1 < seen.shape[0]:
+                seen[m0 // 128 + 1, n0 // 256] += 1
+        assert (seen == 1).all(), (m, n, k)
+    assert taken >= 3
