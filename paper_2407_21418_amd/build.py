@@ -32,7 +32,7 @@ def _run(cmd, log):
 
 
 def _resource_usage(log):
-    """The compiler's kernel-resource-usage remarks of one object, as {name: value}."""
+    """The compiler's kernel-resource-usage remarks of one object, as {name: largest value of its kernels}."""
     out = {}
     with open(log) as f:
         for line in f:
@@ -43,8 +43,44 @@ def _resource_usage(log):
                 k, v = body.rsplit(":", 1)
                 k, v = k.strip(), v.strip()
                 if k in ("VGPRs", "AGPRs", "ScratchSize [bytes/lane]", "VGPRs Spill", "SGPRs Spill", "Occupancy [waves/SIMD]"):
-                    out[k] = int(v)
+                    out[k] = max(int(v), out.get(k, 0))
     return out
+
+
+def _scratch_allowed(name):
+    """Bytes of scratch per lane that the kernels of object `name` may use; None for objects without kernels of the main path."""
+    if name in ("row_runs_hip.o", "big_gemm_hip.o", "conv_patch_hip.o"):
+        return 0      # (their LDS reads are inline asm: a fragment spilled while it is in flight would be stored stale)
+    if "dispatch_" not in name:
+        return None
+    # the general (unaligned-operand) dispatchers may spill a few registers in their largest bodies
+    if "_gen_" in name or "_grp_" in name:
+        return 32
+    # (the grouped LDS-DMA dispatchers of the 256-register class spill three registers around the
+    # fix-up of a ragged last k-tile, outside the k loop's steady state: measured, no change)
+    if "_grpf_c1" in name or "_grpnk_c1" in name:
+        return 16
+    # (the 512-register LDS-DMA dispatchers of bf16 spill one or two registers in the store code of the
+    # 256 x 256 body -- the rounding to bf16 needs more temporaries than a conversion to fp16 -- outside
+    # every k loop: one store and two loads per workgroup)
+    if "_dt1_" in name and name.endswith("_c2.o"):
+        return 8
+    return 0
+
+
+def check_scratch(obj):
+    """Refuses an object whose kernels touch scratch memory (spilled registers, kernel arguments copied to the stack by a
+    dynamically indexed array): several times slower.  Returns what the compiler reported, {} for other objects."""
+    name = os.path.basename(obj)
+    allowed = _scratch_allowed(name)
+    if allowed is None or not os.path.exists(obj + ".log"):
+        return {}
+    use = _resource_usage(obj + ".log")
+    if "ScratchSize [bytes/lane]" not in use:
+        raise RuntimeError(f"{name}: no resource remarks in its log")
+    if use["ScratchSize [bytes/lane]"] > allowed:
+        raise RuntimeError(f"{name} uses scratch memory: {use}")
+    return use
 
 
 def _stale(obj, srcs):
@@ -123,7 +159,7 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
     steps = gen + steps
     for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip", "conv_patch.hip"):
         obj = os.path.join(OUT, src.replace(".", "_") + ".o")
-        steps.append((obj, [HIPCC] + COMMON + ["-c", os.path.join(CSRC, src), "-o", obj]))
+        steps.append((obj, [HIPCC] + COMMON + ["-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj]))
     jobs = jobs or min(8, len(steps))
     if trace:
         # only the f16 LDS-DMA dispatchers and the launch code carry the marks; everything else is
@@ -141,30 +177,10 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
             dt = fut.result()
             if verbose:
                 print(f"  built {os.path.basename(futs[fut])} in {dt:.1f}s", flush=True)
-    # a dispatcher that touches scratch memory (spilled registers, kernel arguments copied to the
-    # stack by a dynamically indexed array) is several times slower: refuse to link it.  The general
-    # (unaligned-operand) dispatchers may spill a few registers in their largest bodies.
     for obj, _ in steps:
-        if "dispatch_" not in obj or not os.path.exists(obj + ".log"):
-            continue
-        use = _resource_usage(obj + ".log")
-        if verbose or remarks:
+        use = _resource_usage(obj + ".log") if trace and os.path.exists(obj + ".log") else check_scratch(obj)   # (development variants are not held to it)
+        if use and (verbose or remarks):
             print(f"  {os.path.basename(obj)}: {use}", flush=True)
-        name = os.path.basename(obj)
-        allowed = 32 if ("_gen_" in name or "_grp_" in name) else 0
-        # (the grouped LDS-DMA dispatchers of the 256-register class spill three registers around the
-        # fix-up of a ragged last k-tile, outside the k loop's steady state: measured, no change)
-        if ("_grpf_c1" in name or "_grpnk_c1" in name):
-            allowed = 16
-        # (the 512-register LDS-DMA dispatchers of bf16 spill one or two registers in the store code of the
-        # 256 x 256 body -- the rounding to bf16 needs more temporaries than a conversion to fp16 -- outside
-        # every k loop: one store and two loads per workgroup)
-        if "_dt1_" in name and name.endswith("_c2.o") and allowed == 0:
-            allowed = 8
-        if trace:
-            allowed = 1 << 20                 # development variants are not held to it
-        if use.get("ScratchSize [bytes/lane]", 0) > allowed:
-            raise RuntimeError(f"{os.path.basename(obj)} uses scratch memory: {use}")
     link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + [o for o, _ in steps]
     _run(link, os.path.join(OUT, "link.log"))
     if verbose:
