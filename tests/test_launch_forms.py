@@ -209,3 +209,21 @@ def test_blocks_cover_c_once(cus, xcds):
                 seen[m0 // 128 + 1, n0 // 256] += 1
         assert (seen == 1).all(), (m, n, k)
     assert taken >= 3
+
+
+def test_patch_tiles_fit_and_cover():
+    """Whatever the image, a patch launch fits a CU's LDS, has at most a workgroup per CU and computes every output."""
+    import random
+    rng = random.Random(5)
+    taken = 0
+    for _ in range(300):
+        size = lambda hi: int(round(2 ** rng.uniform(0, hi)))
+        n, h, w, co, pad = size(6), size(8), size(10), 8 * size(6), rng.randint(0, 4)
+        if n * (h + 2 * pad) * (w + 2 * pad) * co >= 1 << 29 or h + 2 * pad < 3 or w + 2 * pad < 3:
+            continue
+        p = conv(n, h, w, co, pad=pad)
+        f, st = form(p), ft.ft_plan_stats_get(p[2])
+        if f.form == ft.FT_FORM_PATCHES:
+            taken += 1
+            assert 9 * 8192 + 1024 <= f.lds_bytes <= 163840 and f.workgroups <= 256 and f.computed_elems >= st.useful_elems, (n, h, w, co, pad)
+    assert taken > 100
