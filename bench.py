@@ -300,8 +300,8 @@ def main():
                          "ms_per_step": round(sum(r["ms_base"] for r in rows), 5)} if "base" in variants else None,
         "fp16_output": {"value": round(geomean([r["tflops_out16"] for r in rows]), 3),
                         "ms_per_step": round(sum(r["ms_out16"] for r in rows), 5),
-                        "note": "same sweep, cold, C rounded to fp16 in the epilogue (not the headline: the "
-                                "north star fixes fp32 output)"} if "out16" in variants else None,
+                        "note": "same sweep, cold, C rounded to fp16 in the epilogue (not the headline: its "
+                                "results are fp32)"} if "out16" in variants else None,
         "bucketed_baseline": {"value": round(geomean([r["tflops_bucket"] for r in rows]), 3),
                               "ms_per_step": round(sum(r["ms_bucket"] for r in rows), 5),
                               "padding_waste_pct": round(100.0 * (1.0 - sum(r["M"] * r["N"] for r in rows) /

@@ -5,9 +5,9 @@
 // workgroup keeps the filter taps of 64 output channels in LDS (72 KB) and walks over tiles of up to 256 output pixels: a
 // tile's patch of the image is fetched once, halo and zero padding included, and every tap reads its rows of A from the
 // patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 to 74 us with fp32 results, 88 to 60 with 16-bit ones; 8 x 56 x 56: 10.8
-// to 9.9; 8 x 28 x 28: 6.6 to 5.2.  A tile of 256 pixels takes 2.6 us of MFMAs and reads at 90 % of the matrix cores' rate
-// and 1.5 us of copies, waits and barrier; the smallest launches are bound by their latencies: taps and patch 1.5 us, nine
-// taps 1.3.
+// to 9.9; 8 x 28 x 28: 6.6 to 5.2.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
+// 2.2 GHz, and 1.5 us of copies, waits and barrier (counters: matrix cores busy for 54 % of the cycles on 224 x 224); the
+// smallest launches are bound by their latencies: taps and patch 1.5 us, nine taps 1.3 (27 % on 56 x 56).
 //   - One workgroup of eight waves per CU, the patch of the next tile arriving while this one is computed: no wait and no
 //     barrier inside a tile.  (A form that streamed the taps through a ring, two workgroups per CU, spent 0.57 us per tap
 //     on 0.21 us of MFMAs: its barrier per tap and the taps' latency.  Starting a single tile before all taps have landed
@@ -15,10 +15,11 @@
 //   - The results of a tile leave while the next one is computed, a store or two per tap: a CU's vector memory path is in
 //     order, and a burst of stores would hold up the waves and the next patch behind it.
 //   - A pixel's 64 channels are one 128-byte row of LDS, its 16-byte chunks at chunk ^ (x & 7), x the column in the patch: 16
-//     neighbouring pixels are read without a bank conflict whatever column a tap makes them start at, and a tap's rows
-//     differ from those of the tap above by a constant.
+//     neighbouring pixels are read without a bank conflict whatever column a tap makes them start at (counted: none on
+//     224 x 224, tiles 16 wide; 23 % of the LDS cycles on 56 x 56, where 16 pixels of a tile 28 wide lie in two of its rows), and
+//     a tap's rows differ from those of the tap above by a constant.
 //   - Operands are handed to the MFMAs the other way round, so that a lane holds four neighbouring channels of one pixel.
-// The host picks the tile (see conv_schedule).
+// The host picks the tile, and the layers that are left to the gather (see conv_schedule).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

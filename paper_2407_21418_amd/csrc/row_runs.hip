@@ -14,7 +14,8 @@
 // Measured with timestamps (768 matrices of 300 x 300): a workgroup of 32 rows spends 3.0 us on its loads, which
 // queue behind the stores of the CU's other workgroups, 1.4 us on MFMAs and image, 1.9 us on stores.  What
 // overlaps them is several workgroups per CU; from about 350 columns on the tile bodies, which hold more of them,
-// are faster (300 columns: 84 against 101 us, 380: 115 against 102, 131: 18.1 against 22.1, 100: 10.7 against 17.8).
+// are faster (300 columns: 84 against 101 us, 380: 115 against 102, 131: 18.1 against 22.1, 100: 10.7 against 17.8).  Which
+// launches of up to 320 columns are left to the tiles: rows_beat_tiles in host.cpp.
 // Keeping B in registers over several steps of rows, or computing and storing waves of their own, left
 // fewer workgroups, or fewer of them ready, and measured 5-30 % slower.
 #include <hip/hip_runtime.h>

@@ -5,7 +5,7 @@ import torch
 
 import paper_2407_21418_amd as ft
 
-REL_TOL = 2e-3          # max relative error for fp32-accumulated fp16/bf16 (the benchmark spec)
+REL_TOL = 2e-3          # max relative error for fp32-accumulated fp16/bf16
 GUARD = 256             # canary floats on each side of C
 
 
