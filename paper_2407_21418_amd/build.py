@@ -159,7 +159,11 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
     steps = gen + steps
     for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip", "conv_patch.hip"):
         obj = os.path.join(OUT, src.replace(".", "_") + ".o")
-        steps.append((obj, [HIPCC] + COMMON + ["-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj]))
+        # The planner's enumeration is short loops: unaligned, its time moves by up to 15 % with whatever stands before
+        # them in the library (1.29 to 1.49 ms for one unchanged attention operator on an EPYC host). Aligned to a cache
+        # line it stays at 1.29 ms in each layout tried; functions alone aligned, 1.53 ms.
+        align = ["-falign-functions=64", "-falign-loops=64"] if src == "host.cpp" else []
+        steps.append((obj, [HIPCC] + COMMON + align + ["-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj]))
     jobs = jobs or min(8, len(steps))
     if trace:
         # only the f16 LDS-DMA dispatchers and the launch code carry the marks; everything else is
