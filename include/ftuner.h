@@ -6,14 +6,15 @@
  * uKernel tiles (Sec. 3; Fig. 4(c)): each workgroup computes one tile of the output with
  * fp16/bf16 MFMA and fp32 accumulation, and the tiles of one or two uKernel shapes cover
  * the output exactly once with no padding on the main axis beyond the 16-row MFMA granule.
- * Three kinds of work are launched in another form than their plan's tiles (FT_FORM_* below).
+ * Four kinds of work are launched in another form than their plan's tiles (FT_FORM_* below).
  *
  * The four stages follow the paper's problem statement:
  *   (a) ft_op_register      operator template + every possible shape        (Sec. 3, Sec. 4)
  *   (b) ft_ukernels_derive  uKernel set from the hardware model             (Sec. 4, Alg. 1)
  *   (c) ft_plan             uKernel-based program for one runtime shape     (Sec. 5, Alg. 2, Eq. 1)
  *   (d) ft_launch           one launch over the tile-descriptor table       (Sec. 3: uKernel = thread block)
- *                           (ft_plan_launch_form: or over row runs, large blocks, image patches)
+ *                           (ft_plan_launch_form: or over row runs, large blocks, image patches,
+ *                           one grid of equal tiles)
  *
  * Conventions
  *   - Plain C, no exceptions cross the boundary; every call returns ft_status (0 = FT_OK).
@@ -360,9 +361,10 @@ void ft_plan_destroy(ft_plan *plan);
  *   FT_FORM_ROWS     whole rows of C (batched products of one k-tile whose rows of C do not lie on 64-byte blocks)
  *   FT_FORM_BLOCKS   blocks of 256 x 256 and halves of 128 x 256 (large Matmuls; C 16-byte aligned)
  *   FT_FORM_PATCHES  image patches (3 x 3 Conv2d of 64 input channels; C 16-byte aligned)
+ *   FT_FORM_GRID     one grid of equal tiles (Matmuls of the middle range with 16-bit results; A, B, C 16-byte aligned)
  * Forced programs, pad baselines, grouped plans and FT_PLAN_TABLE_ORDER always launch tiles.  Every form keeps
  * fp32 sums; the order of a sum's terms, and with it the last bits of a result, depends on the form. */
-enum { FT_FORM_TILES = 0, FT_FORM_ROWS = 1, FT_FORM_BLOCKS = 2, FT_FORM_PATCHES = 3 };
+enum { FT_FORM_TILES = 0, FT_FORM_ROWS = 1, FT_FORM_BLOCKS = 2, FT_FORM_PATCHES = 3, FT_FORM_GRID = 4 };
 typedef struct ft_launch_form {
     uint32_t struct_size;
     uint32_t form;                 /* FT_FORM_*                                              */

@@ -21,7 +21,7 @@ FT_EPI_NONE, FT_EPI_BIAS = 0, 1
 FT_B_KN, FT_B_NK = 0, 1
 FT_PLAN_PATCHWORK, FT_PLAN_PAD_BASELINE, FT_PLAN_FORCED, FT_PLAN_HOST_ONLY, FT_PLAN_TABLE_ORDER = 0, 1, 2, 16, 32
 FT_SIA_LINEAR, FT_SIA_PRODUCT = 0, 1
-FT_FORM_TILES, FT_FORM_ROWS, FT_FORM_BLOCKS, FT_FORM_PATCHES = 0, 1, 2, 3
+FT_FORM_TILES, FT_FORM_ROWS, FT_FORM_BLOCKS, FT_FORM_PATCHES, FT_FORM_GRID = 0, 1, 2, 3, 4
 
 u32, u64, u16 = C.c_uint32, C.c_uint64, C.c_uint16
 

@@ -49,7 +49,7 @@ def _resource_usage(log):
 
 def _scratch_allowed(name):
     """Bytes of scratch per lane that the kernels of object `name` may use; None for objects without kernels of the main path."""
-    if name in ("row_runs_hip.o", "big_gemm_hip.o", "conv_patch_hip.o"):
+    if name in ("row_runs_hip.o", "big_gemm_hip.o", "conv_patch_hip.o", "grid_gemm_hip.o"):
         return 0      # (their LDS reads are inline asm: a fragment spilled while it is in flight would be stored stale)
     if "dispatch_" not in name:
         return None
@@ -157,7 +157,7 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
                 gen.append((obj, cmd))
     gen.sort(key=lambda oc: "_c2" not in oc[0])   # the 512-register kernels take longest: start them first
     steps = gen + steps
-    for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip", "conv_patch.hip"):
+    for src in ("host.cpp", "device.hip", "row_runs.hip", "big_gemm.hip", "conv_patch.hip", "grid_gemm.hip"):
         obj = os.path.join(OUT, src.replace(".", "_") + ".o")
         # The planner's enumeration is short loops: unaligned, its time moves by up to 15 % with whatever stands before
         # them in the library (1.29 to 1.49 ms for one unchanged attention operator on an EPYC host). Aligned to a cache

@@ -11,6 +11,7 @@
 #include "ring.h"
 #include "row_runs.h"
 #include "big_gemm.h"
+#include "grid_gemm.h"
 #include "conv_patch.h"
 
 // Workspace of ft_launch_noalloc: the fp32 partial tiles and arrival counters of a reduce-axis split,
@@ -363,6 +364,18 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.n_full = plan->big_full; r.n_half = plan->big_half;
         r.num_xcds = plan->num_xcds;
         const int rc = ft_launch_big(&r, (int)plan->op.dtype, hip_stream);
+        if (rc != 0) return hip_fail((hipError_t)rc);
+        return FT_OK;
+    }
+    if (form.form == FT_FORM_GRID) {
+        ftk::GridArgs r;
+        std::memset(&r, 0, sizeof(r));
+        r.A = a.A; r.B = a.B; r.C = static_cast<uint16_t *>(C); r.bias = bias;
+        r.M = a.M; r.N = a.N; r.K = a.K;
+        r.rows = plan->grid_rows; r.cols = plan->grid_cols; r.tiles = plan->grid_rows * plan->grid_cols;
+        r.group = plan->grid_group;
+        r.num_xcds = plan->num_xcds;
+        const int rc = ft_launch_grid(&r, plan->grid_body, (int)plan->op.dtype, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }

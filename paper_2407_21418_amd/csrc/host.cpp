@@ -9,6 +9,8 @@
 #include "family.h"
 #include "conv_patch.h"
 #include "ft_internal.h"
+#include "big_gemm.h"
+#include "grid_gemm.h"
 #include "row_runs.h"
 #include "tile_order.h"
 
@@ -609,6 +611,58 @@ void big_schedule(ft_plan *pl) {
     pl->big_full = (uint32_t)full; pl->big_half = (uint32_t)half;
 }
 
+// Matmuls with 16-bit results may be executed in one grid of equal tiles (grid_gemm.hip), whatever tiles the program has.  Which
+// tile: time in us = first + more * (w - 1) + k-tiles * (step + step_more * (w - 1)), w = tiles per CU on the busiest CU,
+// fitted to 253 shapes (1 to 4096 rows, 768 to 11008 columns, K of 768 to 4096) with every body timed; the least estimate is 0.2 %
+// from the fastest body in the mean, 8 % at worst.
+// Against the program's tiles and the blocks of 256 x 256, on the same shapes:
+//   - one tile per CU at most: faster than the tiles by a fifth in the mean, and than the blocks (1232 x 4096 x 4096 42 / 49 us,
+//     403 x 11008 x 4096 46 / 52, 1232 x 5120 x 2048 28.6 / 29.1), but for launches of few small tiles: up to 16 rows with a short
+//     reduce axis (768 x 768: 3.2 / 3.1), and a long reduce axis shared by fewer than 160 workgroups, which the program splits
+//     finer (48 x 768 x 3072 7.4 / 6.7, 200 x 768 x 3072 8.8 / 9.0, 16 x 4096 x 4096 11.7 / 10.9, 33 x 4096 x 4096 11.1 / 12.3);
+//   - two or three: where the blocks are not taken and the program has more than two workgroups per CU (800 x 11008 x 4096
+//     88 / 112, 2600 x 3072 x 768 17.5 / 20.4; with fewer 1600 x 5120 x 2048 43 / 39); more than three were not looked at.
+// fp32 results stay with the program's tiles, whose sums FT_PLAN_TABLE_ORDER gives again bit for bit.
+struct GridCost {
+    double first, more, step, step_more;
+};
+constexpr GridCost kGridCost[ftk::kNumGridBodies] = {
+    {1.76, 1.14, 0.129, 0.135}, {1.91, 1.63, 0.137, 0.097}, {2.20, 1.93, 0.151, 0.119}, {2.53, 2.26, 0.174, 0.145},
+    {2.23, 0.81, 0.192, 0.164}, {2.47, 1.11, 0.228, 0.205}, {2.76, 2.52, 0.263, 0.276}, {3.28, 2.68, 0.317, 0.386},
+    {4.00, 3.43, 0.344, 0.461}, {5.08, 5.22, 0.459, 0.628}, {5.29, 4.61, 0.583, 0.839}};
+void grid_schedule(ft_plan *pl) {
+    const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
+    if (pl->op.out_dtype != FT_OUT_SAME || K % 64 || K < 12 * 64 || N % 8 || N < 512 || M == 0 || P == 0) return;
+    if (M * K >= (1ull << 30) || K * N >= (1ull << 30)) return;       // the copies address an operand with 32 bits
+    double best = 0;
+    uint64_t per_cu = 0;
+    for (uint32_t i = 0; i < ftk::kNumGridBodies; ++i) {
+        const ftk::GridBodyInfo &b = ftk::kGridBodies[i];
+        const uint64_t rows = ceil_div(M, b.tm), cols = ceil_div(N, b.tn), w = ceil_div(rows * cols, P);
+        if (w > 3 || K % (64 * b.gk)) continue;
+        const GridCost &c = kGridCost[i];
+        const double cost = c.first + c.more * (double)(w - 1) + (double)(K / 64) * (c.step + c.step_more * (double)(w - 1));
+        if (best == 0 || cost < best) {
+            best = cost; per_cu = w;
+            pl->grid_body = i; pl->grid_rows = (uint32_t)rows; pl->grid_cols = (uint32_t)cols;
+        }
+    }
+    if (per_cu == 0) return;
+    const ftk::GridBodyInfo &b = ftk::kGridBodies[pl->grid_body];
+    const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols;
+    if (per_cu > 1 && (pl->big || pl->st.n_tiles * pl->st.k_parts <= 2 * P)) return;
+    if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
+    // rows of tiles walked together: those with which an XCD's run of tiles touches the fewest rows of A and columns of B
+    const uint64_t run = ceil_div(tiles, pl->num_xcds ? pl->num_xcds : 1);
+    uint64_t least = ~0ull;
+    for (uint32_t g = 1; g <= pl->grid_rows; ++g) {
+        const uint64_t columns = ceil_div(run, g), passes = ceil_div(columns, pl->grid_cols);
+        const uint64_t touched = g * passes * b.tm + std::min<uint64_t>(columns, pl->grid_cols) * b.tn;
+        if (touched < least) { least = touched; pl->grid_group = g; }
+    }
+    pl->grid = true;
+}
+
 // The tile of at most `pixels` output pixels whose patch fits `lds` bytes and that needs the fewest tiles per image (then
 // the smallest patch); 0 if there is none.
 uint64_t conv_tile(uint32_t P, uint32_t Q, uint32_t pixels, uint32_t lds, uint32_t *th, uint32_t *tw) {
@@ -775,6 +829,7 @@ ft_form_choice ft_choose_form(const ft_plan *pl, const void *A, const void *B, c
     }
     if (c % 16) return f;                                             // blocks and patches store 16 bytes per lane
     if (pl->conv_th) f.form = FT_FORM_PATCHES;
+    else if (pl->grid && a % 16 == 0 && b % 16 == 0) f.form = FT_FORM_GRID;
     else if (pl->big) f.form = FT_FORM_BLOCKS;
     return f;
 }
@@ -1074,6 +1129,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     pl->row_runs = false; pl->num_cus = set->hw.num_cus;
     pl->conv_th = pl->conv_tw = pl->conv_bm = 0;
     pl->big = false; pl->big_rows = pl->big_cols = pl->big_full = pl->big_half = 0;
+    pl->grid = false; pl->grid_body = pl->grid_rows = pl->grid_cols = 0; pl->grid_group = 1;
     pl->ws_tile_stride = 0;
     pl->device = -1;
     pl->num_xcds = set->hw.num_xcds ? set->hw.num_xcds : 1;
@@ -1378,7 +1434,10 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
         if (!ok) pl->table_order = true;
     }
     if (flags & FT_PLAN_TABLE_ORDER) pl->table_order = true;
-    if (op->d.kind == FT_OP_MATMUL && op->d.b_layout == FT_B_KN && mode == FT_PLAN_PATCHWORK && !pl->table_order) big_schedule(pl);
+    if (op->d.kind == FT_OP_MATMUL && op->d.b_layout == FT_B_KN && mode == FT_PLAN_PATCHWORK && !pl->table_order) {
+        big_schedule(pl);
+        grid_schedule(pl);
+    }
     if (op->d.kind == FT_OP_CONV2D && mode == FT_PLAN_PATCHWORK && !pl->table_order) conv_schedule(pl);
     // A batched product of one k-tile may be executed in whole rows of C, unless the caller asked for particular tiles
     pl->row_runs = op->d.kind == FT_OP_BMM && mode == FT_PLAN_PATCHWORK && !pl->table_order && ftk::run_shape_ok((uint32_t)r.N, (uint32_t)r.K);
@@ -1635,6 +1694,11 @@ ft_status ft_plan_launch_form(const ft_plan *plan, const void *A, const void *B,
         out->workgroups = (uint64_t)plan->big_full + plan->big_half;
         out->lds_bytes = 163840;
         out->computed_elems = ((uint64_t)plan->big_full * 2 + plan->big_half) * (128 * 256);
+    } else if (f.form == FT_FORM_GRID) {
+        const ftk::GridBodyInfo &b = ftk::kGridBodies[plan->grid_body];
+        out->workgroups = (uint64_t)plan->grid_rows * plan->grid_cols;
+        out->lds_bytes = b.lds;
+        out->computed_elems = out->workgroups * b.tm * b.tn;
     } else if (f.form == FT_FORM_PATCHES) {
         const ft_patch_grid g = ft_patch_grid_of(plan);
         out->workgroups = (uint64_t)g.walkers * g.cols;

@@ -13,6 +13,7 @@ SOURCE = r"""
 #include "big_gemm.h"
 #include "conv_patch.h"
 #include "family.h"
+#include "grid_gemm.h"
 #include "ring.h"
 #include "row_runs.h"
 extern "C" {
@@ -27,6 +28,15 @@ uint32_t shim_ring(int n, const uint32_t *splitk, const uint32_t *planned, const
 void shim_block(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t n_full, uint32_t n_half, uint32_t nx, uint32_t *out) {
     const ftk::BigBlock t = ftk::big_block(b, rows, cols, group, n_full, n_half, nx);
     out[0] = t.m0; out[1] = t.n0; out[2] = t.half;
+}
+void shim_grid_tile(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx, uint32_t *out) {
+    const ftk::GridTile t = ftk::grid_tile(b, rows, cols, group, nx);
+    out[0] = t.row; out[1] = t.col;
+}
+uint32_t shim_grid_bodies() { return ftk::kNumGridBodies; }
+void shim_grid_body(uint32_t i, uint32_t *out) {
+    const ftk::GridBodyInfo &b = ftk::kGridBodies[i];
+    out[0] = b.tm; out[1] = b.tn; out[2] = b.gk; out[3] = b.waves; out[4] = b.lds;
 }
 uint32_t shim_run_lds(uint32_t n, uint32_t rb_log2, uint32_t es, int bnk) { return ftk::run_lds(n, rb_log2, es, bnk != 0); }
 uint32_t shim_run_rb_log2(uint32_t m, uint32_t n, uint64_t batch, uint32_t es, int bnk, uint32_t cus) {
@@ -52,6 +62,9 @@ def load():
     u32, u64, p = C.c_uint32, C.c_uint64, C.POINTER(C.c_uint32)
     lib.shim_ring.argtypes, lib.shim_ring.restype = [C.c_int, p, p, p, u32, u64, u32, u32, p], u32
     lib.shim_block.argtypes, lib.shim_block.restype = [u32] * 7 + [p], None
+    lib.shim_grid_tile.argtypes, lib.shim_grid_tile.restype = [u32] * 5 + [p], None
+    lib.shim_grid_bodies.argtypes, lib.shim_grid_bodies.restype = [], u32
+    lib.shim_grid_body.argtypes, lib.shim_grid_body.restype = [u32, p], None
     for name, args in (("run_lds", [u32, u32, u32, C.c_int]), ("run_rb_log2", [u32, u32, u64, u32, C.c_int, u32]), ("run_pitch", [u32]), ("patch_bytes", [u32, u32])):
         fn = getattr(lib, "shim_" + name)
         fn.argtypes, fn.restype = args, u32
@@ -71,3 +84,19 @@ def block(b, rows, cols, group, n_full, n_half, nx):
     out = (C.c_uint32 * 3)()
     load().shim_block(b, rows, cols, group, n_full, n_half, nx, out)
     return tuple(out)
+
+
+def grid_tile(b, rows, cols, group, nx):
+    out = (C.c_uint32 * 2)()
+    load().shim_grid_tile(b, rows, cols, group, nx, out)
+    return tuple(out)
+
+
+def grid_bodies():
+    """(tm, tn, groups along the reduce axis, waves, LDS bytes) of every body."""
+    out = (C.c_uint32 * 5)()
+    bodies = []
+    for i in range(load().shim_grid_bodies()):
+        load().shim_grid_body(i, out)
+        bodies.append(tuple(out))
+    return bodies

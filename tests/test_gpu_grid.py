@@ -1,0 +1,122 @@
+"""Matmuls executed in one grid of equal tiles: every body at rows and columns that end inside a tile, the shortest reduce axis
+taken, even and odd numbers of k-tiles around the rings' depth, both types, with and without bias; against the CPU oracle.
+The index functions that kernel and host share are walked on the CPU."""
+import random
+
+import numpy as np
+import pytest
+import torch
+
+import host_shim
+import paper_2407_21418_amd as ft
+import synth_inputs as si
+from oracle import contraction as oc
+from oracle import epilogue as oe
+
+# (M, N, K, tm, tn, k-tiles of 64 in turn): two shapes or more for each body, one tile row short of full among them
+CASES = [(17, 1568, 2048, 32, 32, 4), (93, 2408, 3072, 32, 32, 4), (52, 2568, 768, 32, 32, 4),
+         (227, 1032, 2560, 16, 64, 4), (80, 3224, 768, 16, 64, 4),
+         (34, 1984, 896, 32, 64, 2), (263, 1160, 2176, 32, 64, 2), (135, 1984, 768, 32, 64, 2),
+         (799, 760, 2560, 48, 64, 2), (241, 2088, 2560, 48, 64, 2),
+         (297, 1016, 832, 64, 64, 1), (1250, 656, 896, 64, 64, 1), (160, 3304, 768, 64, 64, 1),
+         (1803, 624, 1088, 96, 64, 1), (329, 3784, 832, 96, 64, 1),
+         (2003, 1016, 832, 128, 64, 1), (1519, 1240, 768, 128, 64, 1), (996, 1944, 2048, 128, 64, 1),
+         (1904, 1328, 768, 96, 128, 1), (881, 3112, 896, 96, 128, 1), (2557, 1016, 832, 96, 128, 1),
+         (2567, 1432, 832, 128, 128, 1), (907, 3672, 768, 128, 128, 1),
+         (1182, 3304, 768, 128, 192, 1), (1117, 3936, 1088, 128, 192, 1), (2428, 3792, 2176, 128, 192, 1),
+         (2184, 3496, 832, 128, 256, 1), (2211, 2872, 768, 128, 256, 1)]
+
+
+def plan_of(M, N, K, dtype=ft.FT_F16, bias=False, flags=0, out=ft.FT_OUT_SAME):
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_MATMUL, dtype=dtype, n=N, k=K, m_lo=1, m_hi=8192, out_dtype=out,
+                                         epilogue=ft.FT_EPI_BIAS if bias else ft.FT_EPI_NONE))
+    uks = ft.ft_ukernels_derive(op)
+    return op, uks, ft.ft_plan_create(op, uks, ft.ft_shape(m=M), flags)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [ft.FT_F16, ft.FT_BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("M,N,K,tm,tn,gk", CASES)
+def test_every_body(M, N, K, tm, tn, gk, dtype):
+    from gpu_util import check_epilogue, run_at
+    g = np.random.default_rng([M, N, K, dtype])
+    bias = g.standard_normal(N).astype(np.float32) if (M + dtype) % 2 else None
+    _, _, plan = plan_of(M, N, K, dtype, bias is not None)
+    f = ft.ft_plan_launch_form(plan)
+    body = [b for b in host_shim.grid_bodies() if b[:3] == (tm, tn, gk)]
+    assert f.form == ft.FT_FORM_GRID and body and (f.workgroups, f.lds_bytes) == (-(-M // tm) * -(-N // tn), body[0][4]), "another body than the test is about"
+    A = si.normal_bits(g, (M, K), 1.0, dtype)
+    B = si.normal_bits(g, (K, N), 0.02, dtype)
+    rows = np.array(sorted({0, M - 1} | {r for e in range(0, M, tm) for r in (e - 1, e, e + 15, e + 16) if 0 <= r < M and (e < 3 * tm or e > M - 2 * tm)}))
+    ref, refabs = oc.matmul(A, B, dtype, rows=rows, want_abs=True)
+    if bias is not None:
+        ref = oe.add_bias(ref, bias)
+    # (A and B on 16 bytes among NaNs: nothing beyond an operand may reach a result)
+    got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, dtype, off_a=8, off_b=24, off_c=8).reshape(M, N)
+    assert np.isfinite(got).all(), "uncovered outputs"
+    check_epilogue(got[rows], ref, refabs, bias, dtype, f"{M}x{N}x{K}")
+    again = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, dtype, off_a=8, off_b=24, off_c=8).reshape(M, N)
+    assert np.array_equal(got, again)
+    # off 16 bytes the same plan launches its tiles, within the same bounds
+    other = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_TILES, bias, dtype, off_a=3, off_b=8, off_c=8).reshape(M, N)
+    check_epilogue(other[rows], ref, refabs, bias, dtype, f"{M}x{N}x{K} tiles")
+
+
+@pytest.mark.gpu
+def test_grid_launches_in_a_graph():
+    """Captured launches on rotating operands, replayed with eager launches in between, give the eager bits."""
+    from gpu_util import dev_bits, stream
+    M, N, K = 329, 3784, 832
+    g = np.random.default_rng(9)
+    _, _, plan = plan_of(M, N, K)
+    A = [dev_bits(si.normal_bits(g, (M, K), 1.0, ft.FT_F16)) for _ in range(2)]
+    B = [dev_bits(si.normal_bits(g, (K, N), 0.02, ft.FT_F16)) for _ in range(2)]
+    want = []
+    for a, b in zip(A, B):
+        c = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        ft.ft_launch(plan, a.data_ptr(), b.data_ptr(), c.data_ptr(), stream())
+        want.append(c)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        C = [torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+        ft.ft_launch_timed(plan, [t.data_ptr() for t in A], [t.data_ptr() for t in B], [t.data_ptr() for t in C], side.cuda_stream, 5, graph=True)
+        torch.cuda.synchronize()
+        for c, w in zip(C, want):
+            assert bool((c.view(torch.int16) == w.view(torch.int16)).all())
+        ft.ft_launch(plan, A[0].data_ptr(), B[0].data_ptr(), C[0].data_ptr(), stream())
+        torch.cuda.synchronize()
+        assert bool((C[0].view(torch.int16) == want[0].view(torch.int16)).all())
+
+
+@pytest.mark.parametrize("nx", [8, 1, 3])
+def test_every_tile_has_one_workgroup(nx):
+    rng = random.Random(nx)
+    for _ in range(200):
+        rows, cols = rng.randint(1, 40), rng.randint(1, 60)
+        group = rng.randint(1, rows)
+        tiles = [host_shim.grid_tile(b, rows, cols, group, nx) for b in range(rows * cols)]
+        assert sorted(tiles) == [(r, c) for r in range(rows) for c in range(cols)], (rows, cols, group, nx)
+
+
+def test_bodies_fit_a_cu():
+    for tm, tn, gk, waves, lds in host_shim.grid_bodies():
+        assert lds <= 163840 and waves in (4, 8) and gk * tm * tn * 4 * (gk > 1) <= lds
+
+
+def test_where_the_grid_is_taken():
+    def form(M, N, K, a=1 << 20, b=1 << 20, c=1 << 20, **kw):
+        plan = plan_of(M, N, K, flags=ft.FT_PLAN_HOST_ONLY | kw.pop("flags", 0), **kw)[2]
+        return ft.ft_plan_launch_form(plan, a, b, c).form
+    grid, tiles, blocks = ft.FT_FORM_GRID, ft.FT_FORM_TILES, ft.FT_FORM_BLOCKS
+    assert form(688, 2304, 768) == form(688, 768, 3072) == form(403, 4096, 4096) == form(77, 3072, 768) == grid
+    assert form(8, 768, 768) == form(48, 768, 3072) == form(16, 4096, 4096) == form(1600, 5120, 2048) == tiles
+    assert form(1232, 4096, 4096) == form(403, 11008, 4096) == grid and form(2600, 4096, 4096) == form(2600, 5120, 2048) == blocks
+    # what the copies and stores do not take: short, ragged or unaligned operands; fp32 results; plans that name their tiles
+    assert form(688, 2304, 704) == form(688, 2304, 776) == form(688, 2300, 768) == form(688, 504, 768) == tiles
+    for kw in (dict(a=8), dict(b=8), dict(c=8)):
+        kw = {k: (1 << 20) + v for k, v in kw.items()}
+        assert form(688, 2304, 768, **kw) == tiles
+    assert form(403, 11008, 4096, a=(1 << 20) + 2) == blocks
+    assert form(688, 2304, 768, out=ft.FT_OUT_F32) == form(688, 2304, 768, flags=ft.FT_PLAN_TABLE_ORDER) == form(688, 2304, 768, flags=ft.FT_PLAN_PAD_BASELINE) == tiles
