@@ -361,7 +361,7 @@ void ft_plan_destroy(ft_plan *plan);
  *   FT_FORM_ROWS     whole rows of C (batched products of one k-tile whose rows of C do not lie on 64-byte blocks)
  *   FT_FORM_BLOCKS   blocks of 256 x 256 and halves of 128 x 256 (large Matmuls; C 16-byte aligned)
  *   FT_FORM_PATCHES  image patches (3 x 3 Conv2d of 64 input channels; C 16-byte aligned)
- *   FT_FORM_GRID     one grid of equal tiles (Matmuls of the middle range with 16-bit results; A, B, C 16-byte aligned)
+ *   FT_FORM_GRID     one grid of equal tiles (Matmuls of the middle range; A, B, C 16-byte aligned)
  * Forced programs, pad baselines, grouped plans and FT_PLAN_TABLE_ORDER always launch tiles.  Every form keeps
  * fp32 sums; the order of a sum's terms, and with it the last bits of a result, depends on the form. */
 enum { FT_FORM_TILES = 0, FT_FORM_ROWS = 1, FT_FORM_BLOCKS = 2, FT_FORM_PATCHES = 3, FT_FORM_GRID = 4 };

@@ -17,14 +17,15 @@ namespace ftk {
     X(5, 48, 32, 2, 2, 1, 4)                                                                       \
     X(6, 64, 32, 2, 2, 1, 4)                                                                       \
     X(7, 48, 64, 2, 2, 1, 3)                                                                       \
-    X(8, 64, 64, 2, 2, 1, 3)                                                                       \
+    X(8, 64, 32, 2, 4, 1, 4)                                                                       \
     X(9, 64, 48, 2, 4, 1, 3)                                                                       \
-    X(10, 64, 64, 2, 4, 1, 3)
+    X(10, 64, 64, 2, 4, 1, 3)                                                                      \
+    X(11, 32, 32, 2, 4, 1, 4)
 
 struct GridArgs {
     const uint16_t *A;
     const uint16_t *B;
-    uint16_t *C;                         // the inputs' 16-bit type
+    void *C;                             // fp32 or the inputs' 16-bit type
     const float *bias;                   // one per column, or NULL
     uint32_t M, N, K;
     uint32_t rows, cols, tiles;          // tiles = rows * cols workgroups
@@ -62,4 +63,4 @@ constexpr uint32_t kNumGridBodies = sizeof(kGridBodies) / sizeof(kGridBodies[0])
 
 }  // namespace ftk
 
-extern "C" int ft_launch_grid(const ftk::GridArgs *args, uint32_t body, int dt, void *stream);
+extern "C" int ft_launch_grid(const ftk::GridArgs *args, uint32_t body, int dt, int out16, void *stream);

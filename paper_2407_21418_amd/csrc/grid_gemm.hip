@@ -1,4 +1,4 @@
-// Matmuls of the middle range, 16-bit results: one grid of equal tiles, at most two per CU.
+// Matmuls of the middle range: one grid of equal tiles, at most three per CU.
 //
 // What bounds these launches (a few hundred tiles, 12 to 64 k-tiles of 64) is neither memory nor the matrix cores but the
 // instructions a wave issues: a SIMD with one or two waves issues one instruction of a wave every four cycles, and a k-tile of
@@ -14,7 +14,8 @@
 //   - MFMAs are 16x16x32, operands handed over the other way round (a lane's four registers are four neighbouring columns).
 // Beyond that a CU pulls its operand panels through one path at about 46 bytes a cycle, the tile's bytes set the time.
 // f16, us, the program's tiles against this: 688 x 2304 x 768 8.5 / 6.4, x 768 x 768 6.9 / 4.7, x 3072 x 768 8.7 / 7.5,
-// x 768 x 3072 12.9 / 11.3, 1600 x 768 x 3072 17.0 / 14.7.
+// x 768 x 3072 12.9 / 11.3, 1600 x 768 x 3072 17.0 / 14.2; with fp32 results 688 x 768 x 768
+// 7.4 / 5.5, 429 x 3072 x 768 8.4 / 6.7, 131 x 3072 x 768 6.5 / 4.9 (16 bytes per lane straight from the accumulators).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -55,7 +56,7 @@ template <int TN> __device__ __forceinline__ uint32_t grid_swzB(uint32_t row) {
     else return swzB<TN>(row);
 }
 
-template <int DT, int WM, int WN, int GM, int GN, int GK, int S>
+template <int DT, bool OUT16, int WM, int WN, int GM, int GN, int GK, int S>
 struct GridBody {
     static constexpr int TM = GM * WM, TN = GN * WN, NWG = GM * GN, BM = WM / 16, BN = WN / 16, NB = BM * BN;
     static constexpr int A_BYTES = TM * 128, B_BYTES = TN * 128, STAGE = A_BYTES + B_BYTES, RING = S * STAGE;
@@ -129,6 +130,13 @@ struct GridBody {
     __device__ static __forceinline__ uint32_t pack(float x, float y) {                           // both rounded to nearest even
         if constexpr (DT == DT_F16) return (uint32_t)out_cvt<OUT_F16>(x) | ((uint32_t)out_cvt<OUT_F16>(y) << 16);
         else return __builtin_bit_cast(uint32_t, __builtin_convertvector(grid_f32x2{x, y}, grid_bf16x2));
+    }
+    // four neighbouring columns from c on
+    __device__ static __forceinline__ void store4(const GridArgs &g, uint32_t r, uint32_t c, f32x4 v) {
+        if (r >= g.M || c >= g.N) return;
+        const uint64_t at = (uint64_t)r * g.N + c;
+        if constexpr (OUT16) *reinterpret_cast<grid_u32x2 *>(static_cast<uint16_t *>(g.C) + at) = grid_u32x2{pack(v[0], v[1]), pack(v[2], v[3])};
+        else *reinterpret_cast<f32x4 *>(static_cast<float *>(g.C) + at) = v;
     }
     __device__ static __forceinline__ f32x4 bias_of(const GridArgs &g, uint32_t c) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -242,46 +250,45 @@ struct GridBody {
                 for (int q = 1; q < GK; ++q) s += x[((q * NWG + wave) * NB + b) * 64u + lane];
                 s += bias[p];
                 const uint32_t r = m0 + wm * WM + (b / BN) * 16u + (lane & 15u), cc = col0 + (b % BN) * 16u + q4 * 4u;
-                if (r < g.M && cc < g.N) *reinterpret_cast<grid_u32x2 *>(g.C + (uint64_t)r * g.N + cc) = grid_u32x2{pack(s[0], s[1]), pack(s[2], s[3])};
+                store4(g, r, cc, s);
             }
         } else {
-            // two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them
+            // 16-bit results, two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them
             const uint32_t row0 = m0 + wm * WM + (lane & 15u), cc = col0 + (q4 & 1u) * 16u + (q4 >> 1) * 8u;
 #pragma unroll
             for (int i = 0; i < BM; ++i) {
                 const uint32_t r = row0 + i * 16u;
 #pragma unroll
                 for (int j = 0; j < BN; ++j) acc[i][j] += bias[j];
+                if constexpr (OUT16) {
 #pragma unroll
-                for (int j = 0; j + 1 < BN; j += 2) {
-                    const auto lo = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
-                    const auto hi = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][2], acc[i][j][3]), pack(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
-                    const grid_u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
-                    if (r < g.M && cc + j * 16u < g.N) *reinterpret_cast<grid_u32x4 *>(g.C + (uint64_t)r * g.N + cc + j * 16u) = v;
+                    for (int j = 0; j + 1 < BN; j += 2) {
+                        const auto lo = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
+                        const auto hi = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][2], acc[i][j][3]), pack(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
+                        const grid_u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+                        if (r < g.M && cc + j * 16u < g.N) *reinterpret_cast<grid_u32x4 *>(static_cast<uint16_t *>(g.C) + (uint64_t)r * g.N + cc + j * 16u) = v;
+                    }
                 }
-                if constexpr (BN % 2) {
-                    const uint32_t c1 = col0 + (BN - 1) * 16u + q4 * 4u;
-                    if (r < g.M && c1 < g.N)
-                        *reinterpret_cast<grid_u32x2 *>(g.C + (uint64_t)r * g.N + c1) = grid_u32x2{pack(acc[i][BN - 1][0], acc[i][BN - 1][1]), pack(acc[i][BN - 1][2], acc[i][BN - 1][3])};
-                }
+#pragma unroll
+                for (int j = OUT16 ? BN / 2 * 2 : 0; j < BN; ++j) store4(g, r, col0 + j * 16u + q4 * 4u, acc[i][j]);
             }
         }
     }
 };
 
-template <int DT, int WM, int WN, int GM, int GN, int GK, int S>
+template <int DT, bool OUT16, int WM, int WN, int GM, int GN, int GK, int S>
 __global__ __launch_bounds__(GM * GN * GK * 64, 2) void ft_grid(GridArgs g) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const GridTile t = grid_tile(blockIdx.x, g.rows, g.cols, g.group, g.num_xcds);
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(t.row * (GM * WM)), n0 = __builtin_amdgcn_readfirstlane(t.col * (GN * WN));
-    GridBody<DT, WM, WN, GM, GN, GK, S>::run(g, m0, n0, smem);
+    GridBody<DT, OUT16, WM, WN, GM, GN, GK, S>::run(g, m0, n0, smem);
 }
 
 }  // namespace ftk
 
-template <int DT, int WM, int WN, int GM, int GN, int GK, int S>
+template <int DT, bool OUT16, int WM, int WN, int GM, int GN, int GK, int S>
 static int launch(const ftk::GridArgs *g, void *stream) {
-    constexpr auto kernel = &ftk::ft_grid<DT, WM, WN, GM, GN, GK, S>;
+    constexpr auto kernel = &ftk::ft_grid<DT, OUT16, WM, WN, GM, GN, GK, S>;
     constexpr ftk::GridBodyInfo info = ftk::grid_info(WM, WN, GM, GN, GK, S);
     static_assert(info.lds <= 163840, "one CU's LDS");
     const hipError_t e = ftk::raise_lds_limit<kernel>();
@@ -290,12 +297,18 @@ static int launch(const ftk::GridArgs *g, void *stream) {
     return (int)hipGetLastError();
 }
 
-extern "C" int ft_launch_grid(const ftk::GridArgs *g, uint32_t body, int dt, void *stream) {
+template <int DT, bool OUT16>
+static int launch_body(const ftk::GridArgs *g, uint32_t body, void *stream) {
     switch (body) {
 #define FT_X(id, WM, WN, GM, GN, GK, S) \
-    case id: return dt ? launch<1, WM, WN, GM, GN, GK, S>(g, stream) : launch<0, WM, WN, GM, GN, GK, S>(g, stream);
+    case id: return launch<DT, OUT16, WM, WN, GM, GN, GK, S>(g, stream);
         FT_GRID_BODIES(FT_X)
 #undef FT_X
     default: return (int)hipErrorInvalidValue;
     }
+}
+
+extern "C" int ft_launch_grid(const ftk::GridArgs *g, uint32_t body, int dt, int out16, void *stream) {
+    if (dt) return out16 ? launch_body<1, true>(g, body, stream) : launch_body<1, false>(g, body, stream);
+    return out16 ? launch_body<0, true>(g, body, stream) : launch_body<0, false>(g, body, stream);
 }

@@ -611,29 +611,38 @@ void big_schedule(ft_plan *pl) {
     pl->big_full = (uint32_t)full; pl->big_half = (uint32_t)half;
 }
 
-// Matmuls with 16-bit results may be executed in one grid of equal tiles (grid_gemm.hip), whatever tiles the program has.  Which
-// tile: time in us = first + more * (w - 1) + k-tiles * (step + step_more * (w - 1)), w = tiles per CU on the busiest CU,
-// fitted to 253 shapes (1 to 4096 rows, 768 to 11008 columns, K of 768 to 4096) with every body timed; the least estimate is 0.2 %
-// from the fastest body in the mean, 8 % at worst.
-// Against the program's tiles and the blocks of 256 x 256, on the same shapes:
-//   - one tile per CU at most: faster than the tiles by a fifth in the mean, and than the blocks (1232 x 4096 x 4096 42 / 49 us,
-//     403 x 11008 x 4096 46 / 52, 1232 x 5120 x 2048 28.6 / 29.1), but for launches of few small tiles: up to 16 rows with a short
-//     reduce axis (768 x 768: 3.2 / 3.1), and a long reduce axis shared by fewer than 160 workgroups, which the program splits
-//     finer (48 x 768 x 3072 7.4 / 6.7, 200 x 768 x 3072 8.8 / 9.0, 16 x 4096 x 4096 11.7 / 10.9, 33 x 4096 x 4096 11.1 / 12.3);
-//   - two or three: where the blocks are not taken and the program has more than two workgroups per CU (800 x 11008 x 4096
-//     88 / 112, 2600 x 3072 x 768 17.5 / 20.4; with fewer 1600 x 5120 x 2048 43 / 39); more than three were not looked at.
-// fp32 results stay with the program's tiles, whose sums FT_PLAN_TABLE_ORDER gives again bit for bit.
+// Matmuls may be executed in one grid of equal tiles (grid_gemm.hip), whatever tiles the program has.  Which tile: time in us =
+// first + more * (w - 1) + k-tiles * (step + step_more * (w - 1)), and for fp32 results wide + wide_more * (w - 1) for the
+// longer stores, w = tiles per CU on the busiest CU.  Fitted to 1652 launches (826 shapes, both result types, 8 to 4096 rows, 512
+// to 11008 columns, K of 768 to 6144) with 23 bodies timed; the chosen body of the twelve kept is 0.9 % from the fastest in the mean.
+// Against the program's tiles and the blocks of 256 x 256 on the same launches, with the rules below 1.139 times as fast in
+// the mean, slower by more than 2 % in 8 launches, by 6 % at most:
+//   - one tile per CU at most: faster than the tiles by a fifth in the mean and than the blocks by a fourteenth (1230 x 4096 x
+//     4096 54 / 47 us), but for few tiles.  A long reduce axis shared by fewer than 160 workgroups the program splits finer
+//     (29 x 768 x 3072 7.2 / 8.7, 24 x 4984 x 5632 16.5 / 25); up to 16 rows with a short one are 3.2 / 3.3; and a body
+//     without groups wants a sixth of the CUs (19 x 1792 x 960 4.0 / 5.2);
+//   - two or three: where the blocks are not taken (with them 0.77 to 1.1 times) and the program has more than two
+//     workgroups per CU (2328 x 4096 x 4096 110 / 86; with fewer 1600 x 5120 x 2048 39 / 43); more were not looked at.
+// fp32 results, whose stores take twice as long, keep the program's tiles in three more cases:
+//   - up to 16 k-tiles, tiles of 96 x 128 and larger, and more workgroups than CUs in the program, which store while others
+//     multiply (688 x 3072 x 768 8.8 / 9.7, 975 x 2304 x 768 9.0 / 9.8; not always, 1232 x 3072 x 768 12.5 / 11.7);
+//   - fewer tiles than a third of the CUs, where little but latency is left (46 x 768 x 768 3.33 / 3.33; 77 rows 4.1 / 3.6);
+//   - 32 k-tiles or more, where tiles and blocks are what ft_plan_launch_form has always answered and FT_PLAN_TABLE_ORDER
+//     gives again bit for bit: the grid adds a split reduce axis in another order.  It would be the faster form of
+//     three in four of these launches (403 x 4096 x 4096 30.4 / 21.4; not 797 x 4096 x 4096 34.6 / 37.1).
 struct GridCost {
-    double first, more, step, step_more;
+    double first, more, step, step_more, wide, wide_more;
 };
 constexpr GridCost kGridCost[ftk::kNumGridBodies] = {
-    {1.76, 1.14, 0.129, 0.135}, {1.91, 1.63, 0.137, 0.097}, {2.20, 1.93, 0.151, 0.119}, {2.53, 2.26, 0.174, 0.145},
-    {2.23, 0.81, 0.192, 0.164}, {2.47, 1.11, 0.228, 0.205}, {2.76, 2.52, 0.263, 0.276}, {3.28, 2.68, 0.317, 0.386},
-    {4.00, 3.43, 0.344, 0.461}, {5.08, 5.22, 0.459, 0.628}, {5.29, 4.61, 0.583, 0.839}};
+    {2.11, 1.11, 0.139, 0.136, 0.01, 0.04}, {2.35, 1.42, 0.136, 0.111, 0.02, 0.05}, {2.43, 1.83, 0.163, 0.128, 0.01, 0.12},
+    {2.74, 1.83, 0.177, 0.175, 0.02, 0.21}, {2.29, 0.29, 0.201, 0.199, 0.32, 0.56}, {2.49, 0.04, 0.225, 0.298, 0.44, 0.91},
+    {2.68, 0.84, 0.253, 0.415, 0.59, 1.30}, {2.70, 1.41, 0.352, 0.494, 0.97, 2.13}, {3.19, 3.09, 0.379, 0.554, 0.73, 2.47},
+    {3.66, 8.16, 0.495, 0.607, 0.67, 3.55}, {3.85, 11.46, 0.622, 0.750, 1.17, 5.91}, {2.63, 1.61, 0.285, 0.375, 0.41, 1.03}};
 void grid_schedule(ft_plan *pl) {
     const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
-    if (pl->op.out_dtype != FT_OUT_SAME || K % 64 || K < 12 * 64 || N % 8 || N < 512 || M == 0 || P == 0) return;
+    if (K % 64 || K < 12 * 64 || N % 8 || N < 512 || M == 0 || P == 0) return;
     if (M * K >= (1ull << 30) || K * N >= (1ull << 30)) return;       // the copies address an operand with 32 bits
+    const bool wide = pl->op.out_dtype == FT_OUT_F32;
     double best = 0;
     uint64_t per_cu = 0;
     for (uint32_t i = 0; i < ftk::kNumGridBodies; ++i) {
@@ -641,7 +650,8 @@ void grid_schedule(ft_plan *pl) {
         const uint64_t rows = ceil_div(M, b.tm), cols = ceil_div(N, b.tn), w = ceil_div(rows * cols, P);
         if (w > 3 || K % (64 * b.gk)) continue;
         const GridCost &c = kGridCost[i];
-        const double cost = c.first + c.more * (double)(w - 1) + (double)(K / 64) * (c.step + c.step_more * (double)(w - 1));
+        const double more = (double)(w - 1);
+        const double cost = c.first + c.more * more + (double)(K / 64) * (c.step + c.step_more * more) + (wide ? c.wide + c.wide_more * more : 0.0);
         if (best == 0 || cost < best) {
             best = cost; per_cu = w;
             pl->grid_body = i; pl->grid_rows = (uint32_t)rows; pl->grid_cols = (uint32_t)cols;
@@ -649,9 +659,15 @@ void grid_schedule(ft_plan *pl) {
     }
     if (per_cu == 0) return;
     const ftk::GridBodyInfo &b = ftk::kGridBodies[pl->grid_body];
-    const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols;
-    if (per_cu > 1 && (pl->big || pl->st.n_tiles * pl->st.k_parts <= 2 * P)) return;
+    const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols, program = pl->st.n_tiles * pl->st.k_parts;
+    if (per_cu > 1 && (pl->big || program <= 2 * P)) return;
     if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
+    if (b.gk == 1 && tiles * 6 < P) return;
+    if (wide) {
+        if (K >= 32 * 64) return;
+        if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
+        if (tiles * 3 < P) return;
+    }
     // rows of tiles walked together: those with which an XCD's run of tiles touches the fewest rows of A and columns of B
     const uint64_t run = ceil_div(tiles, pl->num_xcds ? pl->num_xcds : 1);
     uint64_t least = ~0ull;

@@ -13,18 +13,20 @@ import synth_inputs as si
 from oracle import contraction as oc
 from oracle import epilogue as oe
 
-# (M, N, K, tm, tn, k-tiles of 64 in turn): two shapes or more for each body, one tile row short of full among them
-CASES = [(17, 1568, 2048, 32, 32, 4), (93, 2408, 3072, 32, 32, 4), (52, 2568, 768, 32, 32, 4),
-         (227, 1032, 2560, 16, 64, 4), (80, 3224, 768, 16, 64, 4),
-         (34, 1984, 896, 32, 64, 2), (263, 1160, 2176, 32, 64, 2), (135, 1984, 768, 32, 64, 2),
-         (799, 760, 2560, 48, 64, 2), (241, 2088, 2560, 48, 64, 2),
-         (297, 1016, 832, 64, 64, 1), (1250, 656, 896, 64, 64, 1), (160, 3304, 768, 64, 64, 1),
-         (1803, 624, 1088, 96, 64, 1), (329, 3784, 832, 96, 64, 1),
-         (2003, 1016, 832, 128, 64, 1), (1519, 1240, 768, 128, 64, 1), (996, 1944, 2048, 128, 64, 1),
-         (1904, 1328, 768, 96, 128, 1), (881, 3112, 896, 96, 128, 1), (2557, 1016, 832, 96, 128, 1),
-         (2567, 1432, 832, 128, 128, 1), (907, 3672, 768, 128, 128, 1),
-         (1182, 3304, 768, 128, 192, 1), (1117, 3936, 1088, 128, 192, 1), (2428, 3792, 2176, 128, 192, 1),
-         (2184, 3496, 832, 128, 256, 1), (2211, 2872, 768, 128, 256, 1)]
+S16, F32 = ft.FT_OUT_SAME, ft.FT_OUT_F32
+# (M, N, K, tm, tn, groups along the reduce axis, result type): every body with both result types, one tile row short of full among them
+CASES = [(17, 1096, 1024, 32, 32, 4, S16), (17, 1456, 1536, 32, 32, 4, S16), (33, 2144, 768, 32, 32, 4, F32),
+         (66, 2952, 768, 16, 64, 4, S16), (74, 2808, 1536, 16, 64, 4, S16), (97, 2112, 1024, 16, 64, 4, F32),
+         (17, 584, 896, 32, 64, 2, S16), (81, 3328, 768, 32, 64, 2, S16), (65, 2232, 896, 32, 64, 2, F32),
+         (351, 1792, 1536, 48, 64, 2, S16), (449, 1224, 2048, 48, 64, 2, S16), (689, 816, 896, 48, 64, 2, F32),
+         (17, 3432, 832, 64, 64, 1, S16), (129, 3304, 768, 64, 64, 1, S16), (127, 3496, 1088, 64, 64, 1, F32),
+         (577, 1736, 896, 96, 64, 1, S16), (479, 2960, 1088, 96, 64, 1, S16), (497, 2456, 832, 96, 64, 1, F32),
+         (655, 2680, 1024, 128, 64, 1, S16), (2065, 736, 2176, 128, 64, 1, S16), (2704, 528, 1920, 128, 64, 1, F32),
+         (577, 3912, 896, 96, 128, 1, S16), (767, 2744, 1024, 96, 128, 1, S16), (1343, 2152, 1280, 96, 128, 1, F32),
+         (783, 3832, 1024, 128, 128, 1, S16), (1553, 2128, 1088, 128, 128, 1, S16), (2192, 1760, 1920, 128, 128, 1, F32),
+         (1425, 2712, 768, 128, 192, 1, S16), (2177, 1880, 1088, 128, 192, 1, S16), (1537, 2688, 1920, 128, 192, 1, F32),
+         (2832, 2488, 1536, 128, 256, 1, S16), (1809, 3808, 2048, 128, 256, 1, S16), (2576, 2848, 1536, 128, 256, 1, F32),
+         (655, 2792, 896, 64, 128, 1, S16), (1023, 1632, 1088, 64, 128, 1, S16), (1153, 1616, 768, 64, 128, 1, F32)]
 
 
 def plan_of(M, N, K, dtype=ft.FT_F16, bias=False, flags=0, out=ft.FT_OUT_SAME):
@@ -36,12 +38,13 @@ def plan_of(M, N, K, dtype=ft.FT_F16, bias=False, flags=0, out=ft.FT_OUT_SAME):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [ft.FT_F16, ft.FT_BF16], ids=["f16", "bf16"])
-@pytest.mark.parametrize("M,N,K,tm,tn,gk", CASES)
-def test_every_body(M, N, K, tm, tn, gk, dtype):
+@pytest.mark.parametrize("M,N,K,tm,tn,gk,out", CASES)
+def test_every_body(M, N, K, tm, tn, gk, out, dtype):
     from gpu_util import check_epilogue, run_at
     g = np.random.default_rng([M, N, K, dtype])
     bias = g.standard_normal(N).astype(np.float32) if (M + dtype) % 2 else None
-    _, _, plan = plan_of(M, N, K, dtype, bias is not None)
+    _, _, plan = plan_of(M, N, K, dtype, bias is not None, out=out)
+    out16 = dtype if out == S16 else None
     f = ft.ft_plan_launch_form(plan)
     body = [b for b in host_shim.grid_bodies() if b[:3] == (tm, tn, gk)]
     assert f.form == ft.FT_FORM_GRID and body and (f.workgroups, f.lds_bytes) == (-(-M // tm) * -(-N // tn), body[0][4]), "another body than the test is about"
@@ -52,14 +55,14 @@ def test_every_body(M, N, K, tm, tn, gk, dtype):
     if bias is not None:
         ref = oe.add_bias(ref, bias)
     # (A and B on 16 bytes among NaNs: nothing beyond an operand may reach a result)
-    got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, dtype, off_a=8, off_b=24, off_c=8).reshape(M, N)
+    got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, out16, off_a=8, off_b=24, off_c=8).reshape(M, N)
     assert np.isfinite(got).all(), "uncovered outputs"
-    check_epilogue(got[rows], ref, refabs, bias, dtype, f"{M}x{N}x{K}")
-    again = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, dtype, off_a=8, off_b=24, off_c=8).reshape(M, N)
+    check_epilogue(got[rows], ref, refabs, bias, out16, f"{M}x{N}x{K}")
+    again = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, out16, off_a=8, off_b=24, off_c=8).reshape(M, N)
     assert np.array_equal(got, again)
     # off 16 bytes the same plan launches its tiles, within the same bounds
-    other = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_TILES, bias, dtype, off_a=3, off_b=8, off_c=8).reshape(M, N)
-    check_epilogue(other[rows], ref, refabs, bias, dtype, f"{M}x{N}x{K} tiles")
+    other = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_TILES, bias, out16, off_a=3, off_b=8, off_c=1).reshape(M, N)
+    check_epilogue(other[rows], ref, refabs, bias, out16, f"{M}x{N}x{K} tiles")
 
 
 @pytest.mark.gpu
@@ -119,4 +122,7 @@ def test_where_the_grid_is_taken():
         kw = {k: (1 << 20) + v for k, v in kw.items()}
         assert form(688, 2304, 768, **kw) == tiles
     assert form(403, 11008, 4096, a=(1 << 20) + 2) == blocks
-    assert form(688, 2304, 768, out=ft.FT_OUT_F32) == form(688, 2304, 768, flags=ft.FT_PLAN_TABLE_ORDER) == form(688, 2304, 768, flags=ft.FT_PLAN_PAD_BASELINE) == tiles
+    assert form(688, 2304, 768, flags=ft.FT_PLAN_TABLE_ORDER) == form(688, 2304, 768, flags=ft.FT_PLAN_PAD_BASELINE) == tiles
+    # fp32 results: few tiles, larger tiles beside a program of more workgroups than CUs, and long reduce axes stay where they were
+    assert form(688, 768, 768, out=F32) == form(429, 3072, 768, out=F32) == form(131, 3072, 768, out=F32) == form(800, 4096, 1984, out=F32) == grid
+    assert form(64, 768, 768, out=F32) == form(688, 3072, 768, out=F32) == form(429, 3072, 2048, out=F32) == tiles
