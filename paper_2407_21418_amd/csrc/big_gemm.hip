@@ -13,13 +13,18 @@
 //     and B one and a half, with the copies spread between the MFMAs;
 //   - hands the operands to the MFMA the other way round, so that a lane's four accumulator registers are four
 //     neighbouring columns of C: stores are 16 bytes per lane (16-bit outputs: after a swap between two blocks'
-//     lanes), where they were 4 or 2.
-// 8192 x 11008 x 4096 bf16: 650 -> 562 us; 4096^3: 113 -> 97; 8192^3: 883 -> 744.
+//     lanes), where they were 4 or 2;
+//   - copies with buffer loads and without a branch in the steady loop, the last three k-tiles run a copy of it (1500 x 11008 x
+//     4096 145.7 -> 139.5 us, 8192 x 11008 x 4096 544 -> 533).  A swizzle of A free of bank conflicts for these reads changed
+//     nothing: the LDS is not what the MFMAs wait for.
+// 8192 x 11008 x 4096 bf16, the tile bodies against the first form of this: 650 -> 562 us; 4096^3: 113 -> 97; 8192^3: 883 -> 744.
 //
 // A block is a CU's work for 60-90 us, so a last round of few blocks is expensive: the host deals the blocks that
 // would make it as halves of 128 rows (see big_schedule in host.cpp), a shorter body of the same design.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "big_gemm.h"
 #include "gemm_body.h"
@@ -43,9 +48,14 @@ template <int OFF> __device__ __forceinline__ big_u32x2 big_read_tr16(uint32_t a
     return v;
 }
 template <int N> __device__ __forceinline__ void big_wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-__device__ __forceinline__ void big_dma16(const void *gptr, unsigned char *lds_wave_base) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gptr,
-                                     (__attribute__((address_space(3))) void *)lds_wave_base, 16, 0, 0);
+template <int IMM> __device__ __forceinline__ void big_copy16(__amdgpu_buffer_rsrc_t r, unsigned char *lds_wave_base, uint32_t lane_off, uint32_t tile_off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds_wave_base, 16, (int)lane_off, (int)tile_off, IMM, 0);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t big_rsrc(const uint16_t *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p), 0, (int)bytes, 0x00020000);
+}
+template <int Q, int E, typename F> __device__ __forceinline__ void big_each(F f) {
+    if constexpr (Q < E) { f(std::integral_constant<int, Q>{}); big_each<Q + 1, E>(f); }
 }
 
 // One block of GM * WM rows by GN * WN columns.  SLOTS = 5: A and B tiles are equally large and take turns in five
@@ -59,6 +69,7 @@ struct BigBody {
     static constexpr int NR = BM + 2 * BN, NM = BM * BN;
     static_assert(!SLOTS || A_BYTES == B_BYTES, "five equal slots");
     static_assert(NW == 8 && TN >= 128 && (SLOTS ? 5 * A_BYTES : STAGES * STAGE) <= 163840, "eight waves, one CU's LDS");
+    static_assert(SLOTS || STAGES == 3, "the furthest copy is of tile t + 3");
     static constexpr int AHEAD = SLOTS ? LA : (STAGES - 2) * (LA + LB);   // copies in flight beyond the next tile, steady state
 
     struct Frag { big_u32x4 a[BM]; big_u32x2 b[BN][2]; };
@@ -95,8 +106,7 @@ struct BigBody {
         read_range<KS, M * NR * 4 / (NM * 3), (M + 1) * NR * 4 / (NM * 3)>(aa, ba, fill);
         if constexpr (COPY) {
             constexpr int L = LA + LB;
-#pragma unroll
-            for (int q = M * L / NM; q < (M + 1) * L / NM; ++q) copy(q);
+            big_each<M * L / NM, (M + 1) * L / NM>(copy);
         }
         mfma_one(use, acc, M);
         __builtin_amdgcn_sched_barrier(0);
@@ -107,14 +117,15 @@ struct BigBody {
         const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const uint32_t wm = wave / GN, wn = wave % GN;
         const uint32_t nk = g.K / 64u;
-        // copy assignments, as in gemm_fast.h: wave instruction i fills 1 KB of the tile; byte offsets inside an operand fit
-        // 32 bits, the k-tile moves the (scalar) base
+        // copy assignments, as in gemm_fast.h: wave instruction i fills 1 KB of the tile.  Buffer loads: a lane's offset stays, A's
+        // k-tile is the scalar offset, B's moves the descriptor (an operand of 4 GB is in reach); A's neighbouring kilobytes
+        // share one M0 through the immediate, which moves the source too; rows below A's end read as zeros by the bound
+        const __amdgpu_buffer_rsrc_t ar = big_rsrc(g.A + (uint64_t)m0 * g.K, (g.M - m0 < (uint32_t)TM ? g.M - m0 : (uint32_t)TM) * g.K * 2u);
         uint32_t off_a[LA], off_b[LB];
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const uint32_t row = wave * (LA * 8) + i * 8 + lane / 8u, kc = (lane & 7u) ^ swzA(row);
-            const uint32_t m = m0 + row < g.M ? m0 + row : g.M - 1u;  // clamp: garbage rows are never stored
-            off_a[i] = (m * g.K + kc * 8u) * 2u;
+            off_a[i] = (row * g.K + kc * 8u) * 2u - (i & 3) * 1024u;  // (K >= 64: not below zero)
         }
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
@@ -122,9 +133,14 @@ struct BigBody {
             const uint32_t col = n0 + (p ^ swzB<TN>(kr)) * 8u;
             off_b[i] = (kr * g.N + (col < g.N ? col : n0)) * 2u;      // clamp: garbage columns are never stored
         }
-        const char *const ab = reinterpret_cast<const char *>(g.A), *const bb = reinterpret_cast<const char *>(g.B);
-        auto copy_a = [&](uint32_t t, uint32_t slot, int i) { big_dma16(ab + (uint64_t)t * 128u + off_a[i], smem + slot + wave * (LA * 1024) + i * 1024); };
-        auto copy_b = [&](uint32_t t, uint32_t slot, int i) { big_dma16(bb + (uint64_t)t * (g.N * 128u) + off_b[i], smem + slot + wave * (LB * 1024) + i * 1024); };
+        auto copy_a = [&](uint32_t t, uint32_t slot, auto ic) {
+            constexpr int i = decltype(ic)::value;
+            big_copy16<(i & 3) * 1024>(ar, smem + slot + wave * (LA * 1024) + (i / 4) * 4096, off_a[i], t * 128u);
+        };
+        auto copy_b = [&](uint32_t t, uint32_t slot, auto ic) {
+            constexpr int i = decltype(ic)::value;
+            big_copy16<0>(big_rsrc(g.B + (uint64_t)t * (g.N * 64u), g.N * 128u), smem + slot + wave * (LB * 1024) + i * 1024, off_b[i], 0u);
+        };
         // fragment addresses (see gemm_fast.h)
         const uint32_t sbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
         const uint32_t ra = wm * WM + (lane & 15u);
@@ -155,12 +171,8 @@ struct BigBody {
 #pragma unroll
             for (int t = 0; t < TILES; ++t) {
                 if ((uint32_t)t < nk) {
-#pragma unroll
-                    for (int i = 0; i < LA; ++i) copy_a(t, pa, i);
-                    if (!SLOTS || t < 2) {
-#pragma unroll
-                        for (int i = 0; i < LB; ++i) copy_b(t, pb, i);
-                    }
+                    big_each<0, LA>([&](auto i) { copy_a(t, pa, i); });
+                    if (!SLOTS || t < 2) big_each<0, LB>([&](auto i) { copy_b(t, pb, i); });
                 }
                 pa = next(pa); pb = next(pb);
             }
@@ -174,18 +186,17 @@ struct BigBody {
 #pragma unroll
         for (int j = 0; j < BN; ++j) ba[j] = fb[j] + sb;
         read_range<0, 0, NR>(fa + sa, ba, f0);
-        for (uint32_t t = 0; t < nk; ++t) {
+        auto step = [&](uint32_t t, auto steady_c) {
+            constexpr bool STEADY = decltype(steady_c)::value;        // every copy of the steady state is due
             arrived(f0);
             __builtin_amdgcn_sched_barrier(0);
-            phase<1, false>((fa ^ 64u) + sa, ba, f1, f0, acc, [](int) {});
+            phase<1, false>((fa ^ 64u) + sa, ba, f1, f0, acc, [](auto) {});
             arrived(f1);
             __builtin_amdgcn_sched_barrier(0);
             // Tile t's LDS has been read by this wave; tile t + 1 must have landed.  In flight beyond it: A of t + 2 (slots), or
             // the stages up to t + STAGES - 1.
             const uint32_t behind = nk - 1u - t;                      // tiles after t
-            if (SLOTS ? behind >= 2u : behind >= (uint32_t)STAGES - 1u) big_wait_vm<AHEAD>();
-            else if (!SLOTS && STAGES >= 5 && behind >= 3u) big_wait_vm<2 * (LA + LB)>();
-            else if (!SLOTS && STAGES >= 4 && behind >= 2u) big_wait_vm<LA + LB>();
+            if (STEADY || (SLOTS ? behind >= 2u : behind >= (uint32_t)STAGES - 1u)) big_wait_vm<AHEAD>();
             else big_wait_vm<0>();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
@@ -194,19 +205,24 @@ struct BigBody {
             for (int j = 0; j < BN; ++j) ba[j] = fb[j] + nb;
             // (past the last tile the reads fetch what happens to be there, for nobody)
             if constexpr (SLOTS) {
-                const bool more_b = t + 2u < nk, more_a = t + 3u < nk;
-                phase<0, true>(fa + na, ba, f0, f1, acc, [&](int q) {
-                    if (q < LB) { if (more_b) copy_b(t + 2u, sa, q); }
-                    else if (more_a) copy_a(t + 3u, sb, q - LB);
+                const bool more_b = STEADY || t + 2u < nk;
+                phase<0, true>(fa + na, ba, f0, f1, acc, [&](auto q) {
+                    constexpr int Q = decltype(q)::value;
+                    if constexpr (Q < LB) { if (more_b) copy_b(t + 2u, sa, q); }
+                    else if constexpr (STEADY) copy_a(t + 3u, sb, std::integral_constant<int, Q - LB>{});
                 });
             } else {
-                const bool more = t + STAGES < nk;
-                phase<0, true>(fa + na, ba, f0, f1, acc, [&](int q) {
-                    if (more) { if (q < LA) copy_a(t + STAGES, sa, q); else copy_b(t + STAGES, sb, q - LA); }
+                phase<0, STEADY>(fa + na, ba, f0, f1, acc, [&](auto q) {
+                    constexpr int Q = decltype(q)::value;
+                    if constexpr (Q < LA) copy_a(t + STAGES, sa, q);
+                    else copy_b(t + STAGES, sb, std::integral_constant<int, Q - LA>{});
                 });
             }
             sa = na; sb = nb;
-        }
+        };
+        uint32_t t = 0;
+        for (; t + 3u < nk; ++t) step(t, std::true_type{});           // (A of t + 3, the furthest copy)
+        for (; t < nk; ++t) step(t, std::false_type{});
         arrived(f0);                                                  // nothing of the last reads outlives the loop
 
         // ---- epilogue: lane l holds row l % 16, columns 4 * (l / 16) .. + 3 of every 16 x 16 block -------------
