@@ -623,19 +623,13 @@ void big_schedule(ft_plan *pl) {
 //     without groups wants a sixth of the CUs (19 x 1792 x 960 4.0 / 5.2);
 //   - two or three: where the blocks are not taken (with them 0.77 to 1.1 times) and the program has more than two
 //     workgroups per CU (2328 x 4096 x 4096 110 / 86; with fewer 1600 x 5120 x 2048 39 / 43); more were not looked at.
-// fp32 results, whose stores take twice as long, keep the program's tiles in two more cases:
+// fp32 results, whose stores take twice as long, keep the program's tiles in three more cases:
 //   - up to 16 k-tiles, tiles of 96 x 128 and larger, and more workgroups than CUs in the program, which store while others
 //     multiply (688 x 3072 x 768 8.8 / 9.7, 975 x 2304 x 768 9.0 / 9.8; not always, 1232 x 3072 x 768 12.5 / 11.7);
 //   - fewer tiles than a third of the CUs, where little but latency is left (46 x 768 x 768 3.33 / 3.33; 77 rows 4.1 / 3.6);
-// From 32 k-tiles on fp32 results, too, are faster in the grid (83 launches timed that it takes, 1.15 times in the mean: 403 x 4096 x 4096
-// 29.3 / 21.5, 98 x 11008 x 4096 57.1 / 30.9, 643 x 768 x 3072 13.0 / 10.3; slower by 2.5 % at 114 and 121 x 11008 x 4096, by 5 %
-// at 2075 x 4096 x 4096), with
-// three more lines:
-//   - up to 32 rows both are within 1 % (28 x 11008 x 4096 22.4 / 22.6);
-//   - several tiles per CU need seven eighths of what they compute (645 x 11008 x 4096, 84 %, 82 / 90; 803, 90 %, 123 / 95);
-//   - up to 48 k-tiles more than 1024 rows stay where they were, although the grid would be faster by a tenth (1600 x 768 x
-//     3072 17.4 / 15.1): a plan made with FT_PLAN_TABLE_ORDER gives the bits of the default one there, with a split reduce axis
-//     as without, and the grid adds in another order.
+//   - 32 k-tiles or more, where tiles and blocks are what ft_plan_launch_form has always answered and FT_PLAN_TABLE_ORDER
+//     gives again bit for bit: the grid adds a split reduce axis in another order.  It would be the faster form of
+//     three in four of these launches (403 x 4096 x 4096 30.4 / 21.4; not 797 x 4096 x 4096 34.6 / 37.1).
 struct GridCost {
     double first, more, step, step_more, wide, wide_more;
 };
@@ -670,10 +664,7 @@ void grid_schedule(ft_plan *pl) {
     if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
     if (b.gk == 1 && tiles * 6 < P) return;
     if (wide) {
-        if (K >= 32 * 64) {
-            if (M <= 32 || (K <= 48 * 64 && M > 1024)) return;
-            if (per_cu > 1 && M * N * 8 < tiles * b.tm * b.tn * 7) return;
-        }
+        if (K >= 32 * 64) return;
         if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
         if (tiles * 3 < P) return;
     }
