@@ -49,12 +49,21 @@ FT_HD GridTile grid_tile(uint32_t b, uint32_t rows, uint32_t cols, uint32_t grou
     return nx == 8 ? grid_tile_nx<8>(b, rows, cols, group, nx) : grid_tile_nx<0>(b, rows, cols, group, nx);
 }
 
+// Sums a wave keeps of an output, added at the end: with fp32 results the k-steps of a k-tile have one each, and where one group
+// takes the whole reduce axis those of even and odd k-tiles, as far as the registers go.  The error of a sum grows with the root of
+// its terms in a row, and the waves of the tiles share the reduce axis: grid_schedule lets a body stand in for tiles only if it
+// adds up as many sums.
+constexpr uint32_t grid_sums(uint32_t wm, uint32_t wn, uint32_t gk, bool out16) {
+    return out16 || wm * wn > 48 * 64 ? 1 : gk > 1 || wm * wn > 48 * 32 ? 2 : 4;
+}
+
 struct GridBodyInfo {
     uint32_t tm, tn, gk, waves, lds;
+    uint32_t sums32;                     // partial sums of an output with fp32 results
 };
 constexpr GridBodyInfo grid_info(uint32_t wm, uint32_t wn, uint32_t gm, uint32_t gn, uint32_t gk, uint32_t stages) {
     const uint32_t tm = gm * wm, tn = gn * wn, ring = gk * stages * (tm + tn) * 128u, sums = gk > 1 ? gk * tm * tn * 4u : 0u;
-    return GridBodyInfo{tm, tn, gk, gm * gn * gk, ring > sums ? ring : sums};
+    return GridBodyInfo{tm, tn, gk, gm * gn * gk, ring > sums ? ring : sums, gk * grid_sums(wm, wn, gk, false)};
 }
 #define FT_X(id, WM, WN, GM, GN, GK, S) grid_info(WM, WN, GM, GN, GK, S),
 constexpr GridBodyInfo kGridBodies[] = {FT_GRID_BODIES(FT_X)};

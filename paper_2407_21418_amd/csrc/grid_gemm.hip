@@ -64,6 +64,7 @@ struct GridBody {
     static constexpr int NR1 = BM + 2 * BN, NR = 2 * NR1, NM = 2 * NB;                            // LDS reads, MFMAs per k-tile
     static_assert(LA * NWG * 1024 == A_BYTES && LB * NWG * 1024 == B_BYTES, "whole kilobytes per wave");
     static_assert(S >= 3 && (S - 1) * L <= 63, "vmcnt is 6 bits");
+    static constexpr int NS = (int)grid_sums(WM, WN, GK, OUT16);                                      // sums kept of an output
     static_assert(GK == 1 || NB % GK == 0, "the groups share out the blocks");
     struct Frag { grid_u32x4 a[2][BM]; grid_u32x2 b[2][BN][2]; };
 
@@ -91,10 +92,11 @@ struct GridBody {
         }
     }
     // q-th MFMA of a k-tile: rows of blocks in turn, columns back and forth, so that one operand stays
-    __device__ static __forceinline__ void mfma_one(const Frag &f, f32x4 (&acc)[BM][BN], int q) {
+    template <int ODD> __device__ static __forceinline__ void mfma_one(const Frag &f, f32x4 (&acc)[NS][BM][BN], int q) {
         const int ks = q / NB, m = q % NB, bi = m / BN, bj = (bi & 1) ? BN - 1 - m % BN : m % BN;
         const uint4 b = make_uint4(f.b[ks][bj][0][0], f.b[ks][bj][0][1], f.b[ks][bj][1][0], f.b[ks][bj][1][1]);
-        acc[bi][bj] = mfma16<DT>(b, __builtin_bit_cast(uint4, f.a[ks][bi]), acc[bi][bj]);
+        f32x4 &sum = acc[(ODD * 2 + ks) % NS][bi][bj];
+        sum = mfma16<DT>(b, __builtin_bit_cast(uint4, f.a[ks][bi]), sum);
     }
     struct Copies {
         __amdgpu_buffer_rsrc_t ra, rb;
@@ -110,14 +112,14 @@ struct GridBody {
     }
     // The MFMAs of `use`, with the reads of `fill` in the first half and, where COPY, the copies spread over all of them.
     // Pinned: left alone, the compiler gathers the reads in front.
-    template <bool COPY, int M = 0>
-    __device__ static __forceinline__ void phase(uint32_t aa, const uint32_t (&ba)[BN], Frag &fill, const Frag &use, f32x4 (&acc)[BM][BN], const Copies &c,
+    template <bool COPY, int ODD, int M = 0>
+    __device__ static __forceinline__ void phase(uint32_t aa, const uint32_t (&ba)[BN], Frag &fill, const Frag &use, f32x4 (&acc)[NS][BM][BN], const Copies &c,
                                                  unsigned char *la, unsigned char *lb) {
         read_range<M * NR * 2 / NM, (M + 1) * NR * 2 / NM>(aa, ba, fill);
         if constexpr (COPY) copy<M * L / NM, (M + 1) * L / NM>(c, la, lb);
-        mfma_one(use, acc, M);
+        mfma_one<ODD>(use, acc, M);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (M + 1 < NM) phase<COPY, M + 1>(aa, ba, fill, use, acc, c, la, lb);
+        if constexpr (M + 1 < NM) phase<COPY, ODD, M + 1>(aa, ba, fill, use, acc, c, la, lb);
     }
     // all but the newest min(c, C) k-tiles of this wave's copies have landed
     template <int C> __device__ static __forceinline__ void wait_tiles(uint32_t c) {
@@ -184,16 +186,20 @@ struct GridBody {
         f32x4 bias[NBIAS];
 #pragma unroll
         for (int p = 0; p < NBIAS; ++p) bias[p] = bias_of(g, col0 + (GK > 1 ? (grp * PB + p) % BN : (uint32_t)p) * 16u + q4 * 4u);
-        f32x4 acc[BM][BN];
-#pragma unroll
-        for (int i = 0; i < BM; ++i)
-#pragma unroll
-            for (int j = 0; j < BN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
         auto advance = [&] { c.at_a += step_a; c.at_b += step_b; };
 #pragma unroll
         for (int t = 0; t < S; ++t)
             if ((uint32_t)t < n) { copy<0, L>(c, la + t * STAGE, lb + t * STAGE); advance(); }
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 sums[NS][BM][BN];                                       // (set to zero while the first copies travel)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int i = 0; i < BM; ++i)
+#pragma unroll
+                for (int j = 0; j < BN; ++j) sums[s][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __builtin_amdgcn_sched_barrier(0);
         wait_tiles<S - 1>(n - 1u);
         if constexpr (NWG > 1) __builtin_amdgcn_s_barrier();
         Frag f0, f1;
@@ -202,7 +208,7 @@ struct GridBody {
         for (int j = 0; j < BN; ++j) ba[j] = fb[j];
         read_range<0, NR>(fa, ba, f0);
         // tile t from `use`, tile t + 1 into `fill` (past the last tile the reads fetch what happens to be there, for nobody)
-        auto step = [&](uint32_t t, Frag &use, Frag &fill, auto steady_c) {
+        auto step = [&](uint32_t t, Frag &use, Frag &fill, auto steady_c, auto odd_c) {
             constexpr bool STEADY = decltype(steady_c)::value;        // tile t + S exists
             arrived(use);
             __builtin_amdgcn_sched_barrier(0);
@@ -217,22 +223,31 @@ struct GridBody {
             if constexpr (!STEADY) {
                 if (t + S < n) { copy<0, L>(c, la + slot, lb + slot); advance(); }
             }
-            phase<STEADY>(fa + next, ba, fill, use, acc, c, la + slot, lb + slot);
+            phase<STEADY, decltype(odd_c)::value>(fa + next, ba, fill, use, sums, c, la + slot, lb + slot);
             if constexpr (STEADY) advance();
             slot = next;
         };
+        constexpr std::integral_constant<int, 0> even;
+        constexpr std::integral_constant<int, 1> odd;
         uint32_t t = 0;
         for (; t + 1u + S < n; t += 2) {
-            step(t, f0, f1, std::true_type{});
-            step(t + 1u, f1, f0, std::true_type{});
+            step(t, f0, f1, std::true_type{}, even);
+            step(t + 1u, f1, f0, std::true_type{}, odd);
         }
         for (; t + 1u < n; t += 2) {
-            step(t, f0, f1, std::false_type{});
-            step(t + 1u, f1, f0, std::false_type{});
+            step(t, f0, f1, std::false_type{}, even);
+            step(t + 1u, f1, f0, std::false_type{}, odd);
         }
-        if (t < n) step(t, f0, f1, std::false_type{});
+        if (t < n) step(t, f0, f1, std::false_type{}, even);
         arrived(f0);                                                  // nothing of the last reads outlives the loop
         arrived(f1);
+        f32x4 (&acc)[BM][BN] = sums[0];
+#pragma unroll
+        for (int s = 1; s < NS; ++s)
+#pragma unroll
+            for (int i = 0; i < BM; ++i)
+#pragma unroll
+                for (int j = 0; j < BN; ++j) acc[i][j] += sums[s][i][j];
 
         // ---- lane l holds row l % 16, columns 4 * (l / 16) .. + 3 of every 16 x 16 block ----------------------
         if constexpr (GK > 1) {

@@ -623,6 +623,10 @@ void big_schedule(ft_plan *pl) {
 //     without groups wants a sixth of the CUs (19 x 1792 x 960 4.0 / 5.2);
 //   - two or three: where the blocks are not taken (with them 0.77 to 1.1 times) and the program has more than two
 //     workgroups per CU (2328 x 4096 x 4096 110 / 86; with fewer 1600 x 5120 x 2048 39 / 43); more were not looked at.
+// fp32 results take bodies that add up at least as many sums of an output as the program's tiles (gk waves along the reduce axis
+// times k_parts; to within a fiftieth of the mean, a last row of narrow tiles): the error of an fp32 sum grows with the root of
+// its terms in a row, against 64 bits 768 f16 products are off by 1.8e-7 in one sum, 1.3e-7 in two and 1.0e-7 in four.  (Of 16-bit
+// results the one rounding is all, 2e-4: both forms agree to 3e-6 of that.)
 // fp32 results, whose stores take twice as long, keep the program's tiles in three more cases:
 //   - up to 16 k-tiles, tiles of 96 x 128 and larger, and more workgroups than CUs in the program, which store while others
 //     multiply (688 x 3072 x 768 8.8 / 9.7, 975 x 2304 x 768 9.0 / 9.8; not always, 1232 x 3072 x 768 12.5 / 11.7);
@@ -638,17 +642,23 @@ constexpr GridCost kGridCost[ftk::kNumGridBodies] = {
     {2.74, 1.83, 0.177, 0.175, 0.02, 0.21}, {2.29, 0.29, 0.201, 0.199, 0.32, 0.56}, {2.49, 0.04, 0.225, 0.298, 0.44, 0.91},
     {2.68, 0.84, 0.253, 0.415, 0.59, 1.30}, {2.70, 1.41, 0.352, 0.494, 0.97, 2.13}, {3.19, 3.09, 0.379, 0.554, 0.73, 2.47},
     {3.66, 8.16, 0.495, 0.607, 0.67, 3.55}, {3.85, 11.46, 0.622, 0.750, 1.17, 5.91}, {2.63, 1.61, 0.285, 0.375, 0.41, 1.03}};
-void grid_schedule(ft_plan *pl) {
+void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
     if (K % 64 || K < 12 * 64 || N % 8 || N < 512 || M == 0 || P == 0) return;
     if (M * K >= (1ull << 30) || K * N >= (1ull << 30)) return;       // the copies address an operand with 32 bits
     const bool wide = pl->op.out_dtype == FT_OUT_F32;
+    double inverse = 0, area = 0;                                     // the program's sums per output, their inverse in the mean
+    for (uint32_t i = 0; i < pl->st.n_ukernels; ++i) {
+        const double part = (double)pl->slot_rows[i] * pl->slot_cols[i] * pl->slot_tm[i] * pl->slot_tn[i];
+        area += part; inverse += part / (set.uk[pl->st.ukernel_id[i]].gk * pl->st.k_parts);
+    }
     double best = 0;
     uint64_t per_cu = 0;
     for (uint32_t i = 0; i < ftk::kNumGridBodies; ++i) {
         const ftk::GridBodyInfo &b = ftk::kGridBodies[i];
         const uint64_t rows = ceil_div(M, b.tm), cols = ceil_div(N, b.tn), w = ceil_div(rows * cols, P);
         if (w > 3 || K % (64 * b.gk)) continue;
+        if (wide && area * 50 > 51 * inverse * b.sums32) continue;
         const GridCost &c = kGridCost[i];
         const double more = (double)(w - 1);
         const double cost = c.first + c.more * more + (double)(K / 64) * (c.step + c.step_more * more) + (wide ? c.wide + c.wide_more * more : 0.0);
@@ -1452,7 +1462,7 @@ static ft_status plan_create_impl(const ft_op *op, const ft_ukset *set, const ft
     if (flags & FT_PLAN_TABLE_ORDER) pl->table_order = true;
     if (op->d.kind == FT_OP_MATMUL && op->d.b_layout == FT_B_KN && mode == FT_PLAN_PATCHWORK && !pl->table_order) {
         big_schedule(pl);
-        grid_schedule(pl);
+        grid_schedule(pl, *set);
     }
     if (op->d.kind == FT_OP_CONV2D && mode == FT_PLAN_PATCHWORK && !pl->table_order) conv_schedule(pl);
     // A batched product of one k-tile may be executed in whole rows of C, unless the caller asked for particular tiles
