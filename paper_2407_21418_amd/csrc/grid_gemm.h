@@ -31,6 +31,7 @@ struct GridArgs {
     uint32_t rows, cols, tiles;          // tiles = rows * cols workgroups
     uint32_t group;                      // rows of tiles walked together
     uint32_t num_xcds;
+    uint32_t stream;                     // rows of an fp32 C lie on 64-byte blocks: they are stored past the caches
 };
 
 // workgroup b's tile: every XCD (workgroup b runs on XCD b % nx) takes one contiguous run of the tiles in groups of `group` rows,

@@ -133,17 +133,66 @@ struct GridBody {
         if constexpr (DT == DT_F16) return (uint32_t)out_cvt<OUT_F16>(x) | ((uint32_t)out_cvt<OUT_F16>(y) << 16);
         else return __builtin_bit_cast(uint32_t, __builtin_convertvector(grid_f32x2{x, y}, grid_bf16x2));
     }
+    // fp32 results whose rows lie on 64-byte blocks (an instruction fills 16 of them) bypass the caches, as the tiles' do: kept in L2
+    // they are written back while the next launch asks for its first tiles.  Operands and C from HBM, kept / this / the program's
+    // tiles, us: 1009 x 3072 x 768 13.5 / 10.2 / 10.6, 666 x 3072 x 768 11.5 / 8.7 / 9.0; in the caches 10.6 / 9.6 / 10.1, 9.0 / 8.1 / 8.6.
+    // Parts of blocks are kept, to meet in L2 (past it a launch takes up to 1.5 times as long), and so are 16-bit results, which the next
+    // Matmul reads: an encoder's twelve layers on 688 rows, kept / past the caches, 380 / 410 with the weights in the last-level cache,
+    // 466 / 461 with weights from HBM.
     // four neighbouring columns from c on
-    __device__ static __forceinline__ void store4(const GridArgs &g, uint32_t r, uint32_t c, f32x4 v) {
+    template <bool STREAM> __device__ static __forceinline__ void store4(const GridArgs &g, uint32_t r, uint32_t c, f32x4 v) {
         if (r >= g.M || c >= g.N) return;
         const uint64_t at = (uint64_t)r * g.N + c;
         if constexpr (OUT16) *reinterpret_cast<grid_u32x2 *>(static_cast<uint16_t *>(g.C) + at) = grid_u32x2{pack(v[0], v[1]), pack(v[2], v[3])};
+        else if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(static_cast<float *>(g.C) + at));
         else *reinterpret_cast<f32x4 *>(static_cast<float *>(g.C) + at) = v;
     }
     __device__ static __forceinline__ f32x4 bias_of(const GridArgs &g, uint32_t c) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (g.bias != nullptr && c < g.N) __builtin_memcpy(&v, g.bias + c, 16);
         return v;
+    }
+
+    // lane l holds row l % 16, columns 4 * (l / 16) .. + 3 of every 16 x 16 block
+    template <bool STREAM>
+    __device__ static __forceinline__ void finish(const GridArgs &g, f32x4 (&acc)[BM][BN], const f32x4 *bias, const unsigned char *smem, uint32_t row0, uint32_t col0,
+                                                  uint32_t grp, uint32_t wave, uint32_t lane) {
+        const uint32_t q4 = lane >> 4;
+        row0 += lane & 15u;
+        if constexpr (GK > 1) {
+            // added in group order; group g finishes blocks g * PB ..
+            constexpr int PB = NB / GK;
+            const f32x4 *const x = reinterpret_cast<const f32x4 *>(smem);
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                const uint32_t b = grp * PB + p;
+                f32x4 s = x[(wave * NB + b) * 64u + lane];
+#pragma unroll
+                for (int q = 1; q < GK; ++q) s += x[((q * NWG + wave) * NB + b) * 64u + lane];
+                s += bias[p];
+                store4<STREAM>(g, row0 + (b / BN) * 16u, col0 + (b % BN) * 16u + q4 * 4u, s);
+            }
+        } else {
+            // 16-bit results, two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them
+            const uint32_t cc = col0 + (q4 & 1u) * 16u + (q4 >> 1) * 8u;
+#pragma unroll
+            for (int i = 0; i < BM; ++i) {
+                const uint32_t r = row0 + i * 16u;
+#pragma unroll
+                for (int j = 0; j < BN; ++j) acc[i][j] += bias[j];
+                if constexpr (OUT16) {
+#pragma unroll
+                    for (int j = 0; j + 1 < BN; j += 2) {
+                        const auto lo = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
+                        const auto hi = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][2], acc[i][j][3]), pack(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
+                        const grid_u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+                        if (r < g.M && cc + j * 16u < g.N) *reinterpret_cast<grid_u32x4 *>(static_cast<uint16_t *>(g.C) + (uint64_t)r * g.N + cc + j * 16u) = v;
+                    }
+                }
+#pragma unroll
+                for (int j = OUT16 ? BN / 2 * 2 : 0; j < BN; ++j) store4<STREAM>(g, r, col0 + j * 16u + q4 * 4u, acc[i][j]);
+            }
+        }
     }
 
     __device__ static __forceinline__ void run(const GridArgs &g, uint32_t m0, uint32_t n0, unsigned char *smem) {
@@ -249,45 +298,15 @@ struct GridBody {
 #pragma unroll
                 for (int j = 0; j < BN; ++j) acc[i][j] += sums[s][i][j];
 
-        // ---- lane l holds row l % 16, columns 4 * (l / 16) .. + 3 of every 16 x 16 block ----------------------
-        if constexpr (GK > 1) {
-            // the groups' sums, added in group order; group g finishes blocks g * PB ..
+        if constexpr (GK > 1) {                                       // the groups' sums through LDS
             __syncthreads();
             f32x4 *const x = reinterpret_cast<f32x4 *>(smem);
 #pragma unroll
             for (int b = 0; b < NB; ++b) x[((grp * NWG + wave) * NB + b) * 64u + lane] = acc[b / BN][b % BN];
             __syncthreads();
-#pragma unroll
-            for (int p = 0; p < PB; ++p) {
-                const uint32_t b = grp * PB + p;
-                f32x4 s = x[(wave * NB + b) * 64u + lane];
-#pragma unroll
-                for (int q = 1; q < GK; ++q) s += x[((q * NWG + wave) * NB + b) * 64u + lane];
-                s += bias[p];
-                const uint32_t r = m0 + wm * WM + (b / BN) * 16u + (lane & 15u), cc = col0 + (b % BN) * 16u + q4 * 4u;
-                store4(g, r, cc, s);
-            }
-        } else {
-            // 16-bit results, two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them
-            const uint32_t row0 = m0 + wm * WM + (lane & 15u), cc = col0 + (q4 & 1u) * 16u + (q4 >> 1) * 8u;
-#pragma unroll
-            for (int i = 0; i < BM; ++i) {
-                const uint32_t r = row0 + i * 16u;
-#pragma unroll
-                for (int j = 0; j < BN; ++j) acc[i][j] += bias[j];
-                if constexpr (OUT16) {
-#pragma unroll
-                    for (int j = 0; j + 1 < BN; j += 2) {
-                        const auto lo = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
-                        const auto hi = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][2], acc[i][j][3]), pack(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
-                        const grid_u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
-                        if (r < g.M && cc + j * 16u < g.N) *reinterpret_cast<grid_u32x4 *>(static_cast<uint16_t *>(g.C) + (uint64_t)r * g.N + cc + j * 16u) = v;
-                    }
-                }
-#pragma unroll
-                for (int j = OUT16 ? BN / 2 * 2 : 0; j < BN; ++j) store4(g, r, col0 + j * 16u + q4 * 4u, acc[i][j]);
-            }
         }
+        if (!OUT16 && g.stream) finish<!OUT16>(g, acc, bias, smem, m0 + wm * WM, col0, grp, wave, lane);
+        else finish<false>(g, acc, bias, smem, m0 + wm * WM, col0, grp, wave, lane);
     }
 };
 

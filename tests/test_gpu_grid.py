@@ -66,6 +66,31 @@ def test_every_body(M, N, K, tm, tn, gk, out, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,tm,tn,out", [(103, 2304, 768, 16, 64, F32), (17, 4096, 768, 32, 32, F32), (183, 3088, 768, 48, 64, F32), (690, 768, 768, 48, 64, F32), (1195, 784, 768, 64, 64, F32),
+                                             (660, 3072, 768, 96, 128, F32), (1141, 3072, 768, 128, 128, F32), (1329, 3072, 768, 128, 192, F32),
+                                             (441, 2304, 768, 64, 64, S16), (689, 2336, 768, 128, 64, S16), (927, 2304, 768, 96, 128, S16), (1279, 3072, 768, 128, 128, S16),
+                                             (1558, 3072, 768, 128, 192, S16), (689, 768, 3072, 48, 64, S16)])
+def test_rows_of_c_on_64_byte_blocks(M, N, K, tm, tn, out):
+    """C on a 64-byte block with rows of whole blocks (fp32 is stored past the caches there) and 16 bytes behind
+    one: the same bits, and nothing beside C."""
+    from gpu_util import check_epilogue, run_at
+    dtype = M % 2
+    g = np.random.default_rng([M, N, K, 3])
+    bias = g.standard_normal(N).astype(np.float32)
+    _, _, plan = plan_of(M, N, K, dtype, True, out=out)
+    out16 = dtype if out == S16 else None
+    assert N * (2 if out == S16 else 4) % 64 == 0 and ft.ft_plan_launch_form(plan).workgroups == -(-M // tm) * -(-N // tn), "another body than the test is about"
+    A = si.normal_bits(g, (M, K), 1.0, dtype)
+    B = si.normal_bits(g, (K, N), 0.02, dtype)
+    rows = np.array(sorted({0, M - 1} | {r for e in range(0, M, tm) for r in (e - 1, e) if 0 <= r < M and (e < 3 * tm or e > M - 2 * tm)}))
+    ref, refabs = oc.matmul(A, B, dtype, rows=rows, want_abs=True)
+    got = [run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, out16, off_a=8, off_b=24, off_c=c).reshape(M, N) for c in (0, 4 if out == F32 else 8)]
+    assert np.isfinite(got[0]).all(), "uncovered outputs"
+    check_epilogue(got[0][rows], oe.add_bias(ref, bias), refabs, bias, out16, f"{M}x{N}x{K}")
+    assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [ft.FT_F16, ft.FT_BF16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("M,N,K", [(1009, 2304, 768), (1850, 768, 768), (1524, 2304, 768), (282, 3072, 768), (688, 768, 768), (1194, 768, 768), (440, 2304, 768),
                                    (105, 3072, 768), (143, 2304, 768), (326, 1496, 1344)])
