@@ -614,26 +614,37 @@ void big_schedule(ft_plan *pl) {
 // Matmuls may be executed in one grid of equal tiles (grid_gemm.hip), whatever tiles the program has.  Which tile: time in us =
 // first + more * (w - 1) + k-tiles * (step + step_more * (w - 1)), and for fp32 results wide + wide_more * (w - 1) for the
 // longer stores, w = tiles per CU on the busiest CU.  Fitted to 1652 launches (826 shapes, both result types, 8 to 4096 rows, 512
-// to 11008 columns, K of 768 to 6144) with 23 bodies timed; the chosen body of the twelve kept is 0.9 % from the fastest in the mean.
-// Against the program's tiles and the blocks of 256 x 256 on the same launches, with the rules below 1.139 times as fast in
-// the mean, slower by more than 2 % in 8 launches, by 6 % at most:
-//   - one tile per CU at most: faster than the tiles by a fifth in the mean and than the blocks by a fourteenth (1230 x 4096 x
-//     4096 54 / 47 us), but for few tiles.  A long reduce axis shared by fewer than 160 workgroups the program splits finer
-//     (29 x 768 x 3072 7.2 / 8.7, 24 x 4984 x 5632 16.5 / 25); up to 16 rows with a short one are 3.2 / 3.3; and a body
-//     without groups wants a sixth of the CUs (19 x 1792 x 960 4.0 / 5.2);
-//   - two or three: where the blocks are not taken (with them 0.77 to 1.1 times) and the program has more than two
-//     workgroups per CU (2328 x 4096 x 4096 110 / 86; with fewer 1600 x 5120 x 2048 39 / 43); more were not looked at.
+// to 11008 columns, K of 768 to 6144; everything in the caches) with 23 bodies timed; the chosen body of the twelve kept is 0.9 %
+// from the fastest in the mean.
 // fp32 results take bodies that add up at least as many sums of an output as the program's tiles (gk waves along the reduce axis
 // times k_parts; to within a fiftieth of the mean, a last row of narrow tiles): the error of an fp32 sum grows with the root of
 // its terms in a row, against 64 bits 768 f16 products are off by 1.8e-7 in one sum, 1.3e-7 in two and 1.0e-7 in four.  (Of 16-bit
 // results the one rounding is all, 2e-4: both forms agree to 3e-6 of that.)
-// fp32 results, whose stores take twice as long, keep the program's tiles in three more cases:
+// Against the program's tiles and the blocks of 256 x 256, 2544 launches of those ranges with operands and C from HBM / in the caches:
+// 2436 in the grid, 0.72 / 0.65 of the time in the mean, longer by more than 2 % in 137 / 14, by 24 / 13 % at most.  What stays with
+// tiles and blocks, us, they / the grid, from HBM (and in the caches):
+//   - with 16-bit results next to nothing of one tile per CU and less, but for few tiles (against the blocks 0.95 of the time in the mean of
+//     105 launches, 1.04 at most; 1230 x 4096 x 4096 53.8 / 49.4): a long reduce axis shared by no more than 160 workgroups, which the
+//     program splits finer (29 x 768 x 3072 7.0 / 8.5, 24 x 4984 x 5632 17.2 / 26.2, 105 x 2560 x 6016 20.6 / 28.5), up to 16 rows with
+//     a short one (12 x 3072 x 768 4.1 / 4.2), and a body without groups on less than a sixth of the CUs (19 x 1792 x 960 4.2 / 4.8);
+//   - programs of split-k tiles that the device holds at once: against a body of fewer than four groups, if a CU then reads twice as many
+//     rows and columns of the operands (14 x 4824 x 1984 9.7 / 11.8, 3 x 3816 x 1728 6.9 / 9.6; 58 launches 1.18 (1.02) of the time; up to
+//     16 k-tiles they are in the grid all the same, 11 launches 1.12 (1.01)), and split again over workgroups at 64 k-tiles or more
+//     (62 x 4096 x 4096 16.5 / 18.2 (12.3 / 12.0), 264 x 664 x 6144 16.1 / 20.1 (15.0 / 18.3); 15 launches 1.10 (1.01));
+//   - two or three tiles per CU where the blocks are taken (with them 0.77 to 1.1 times), where the program has no more than two workgroups
+//     per CU (1600 x 5120 x 2048 44.8 / 46.2 (38.3 / 43.7); with more 2328 x 4096 x 4096 109 / 86.7) and where a CU reads a quarter more
+//     (648 x 11008 x 4096 78.9 / 86.1 (71.9 / 74.2), 750 rows, 0.88 times as much, 122 / 95.1); more were not looked at;
+//   - with 16-bit results and up to 16 k-tiles, bodies of 128 x 192 and larger on less than three quarters of the CUs against tiles of
+//     128 x 128 and larger (1370 x 3072 x 768 11.7 / 14.4 (10.8 / 11.5); 12 launches 1.13 (0.99), above that line 1.00 (0.86)).
+// fp32 results keep the program's tiles in three more cases:
 //   - up to 16 k-tiles, tiles of 96 x 128 and larger, and more workgroups than CUs in the program, which store while others
-//     multiply (688 x 3072 x 768 8.8 / 9.7, 975 x 2304 x 768 9.0 / 9.8; not always, 1232 x 3072 x 768 12.5 / 11.7);
-//   - fewer tiles than a third of the CUs, where little but latency is left (46 x 768 x 768 3.33 / 3.33; 77 rows 4.1 / 3.6);
-//   - 32 k-tiles or more, where tiles and blocks are what ft_plan_launch_form has always answered and FT_PLAN_TABLE_ORDER
-//     gives again bit for bit: the grid adds a split reduce axis in another order.  It would be the faster form of
-//     three in four of these launches (403 x 4096 x 4096 30.4 / 21.4; not 797 x 4096 x 4096 34.6 / 37.1).
+//     multiply (688 x 3072 x 768 8.8 / 8.8 (8.4 / 8.2), 975 x 2304 x 768 8.7 / 8.6 (8.4 / 8.1); 1232 x 3072 x 768, whose form a test
+//     compares bit by bit with table order, would be faster, 12.4 / 11.6 (11.5 / 10.5));
+//   - fewer tiles than a third of the CUs, where little but latency is left (64 x 768 x 768 3.8 / 4.0 (3.5 / 3.3), 85 rows 4.1 / 4.0
+//     (3.6 / 3.4));
+//   - 32 k-tiles or more.  The grid would be the faster form of most of these (403 x 4096 x 4096 35.8 / 28.5 (28.4 / 20.6), 643 x 768 x 3072
+//     13.0 / 10.3, 98 x 11008 x 4096 57.3 / 31.0; not 648 x 11008 x 4096 83.8 / 89.6): tests/test_launch_forms.py holds 403 x 4096 x 4096 to the
+//     tiles and 403 x 11008 x 4096 to the blocks.
 struct GridCost {
     double first, more, step, step_more, wide, wide_more;
 };
@@ -647,11 +658,18 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     if (K % 64 || K < 12 * 64 || N % 8 || N < 512 || M == 0 || P == 0) return;
     if (M * K >= (1ull << 30) || K * N >= (1ull << 30)) return;       // the copies address an operand with 32 bits
     const bool wide = pl->op.out_dtype == FT_OUT_F32;
-    double inverse = 0, area = 0;                                     // the program's sums per output, their inverse in the mean
+    // of the program: its sums per output (their inverse in the mean), and the rows of A and columns of B that a CU reads
+    const uint64_t program = pl->st.n_tiles * pl->st.k_parts;
+    double inverse = 0, area = 0, reads = 0, most = 0;
+    bool split_k = true;
     for (uint32_t i = 0; i < pl->st.n_ukernels; ++i) {
-        const double part = (double)pl->slot_rows[i] * pl->slot_cols[i] * pl->slot_tm[i] * pl->slot_tn[i];
-        area += part; inverse += part / (set.uk[pl->st.ukernel_id[i]].gk * pl->st.k_parts);
+        const uint32_t gk = set.uk[pl->st.ukernel_id[i]].gk, extents = pl->slot_tm[i] + pl->slot_tn[i];
+        const double tiles = (double)pl->slot_rows[i] * pl->slot_cols[i], part = tiles * pl->slot_tm[i] * pl->slot_tn[i];
+        area += part; inverse += part / (gk * pl->st.k_parts);
+        reads += tiles * extents; most = std::max(most, (double)extents / pl->st.k_parts);
+        split_k &= gk == 4;
     }
+    reads = std::max(reads / (double)std::min(program, P), most);
     double best = 0;
     uint64_t per_cu = 0;
     for (uint32_t i = 0; i < ftk::kNumGridBodies; ++i) {
@@ -669,15 +687,17 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     }
     if (per_cu == 0) return;
     const ftk::GridBodyInfo &b = ftk::kGridBodies[pl->grid_body];
-    const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols, program = pl->st.n_tiles * pl->st.k_parts;
-    if (per_cu > 1 && (pl->big || program <= 2 * P)) return;
-    if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
+    const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols;
+    const double more_reads = (double)(per_cu * (b.tm + b.tn)) / reads;
+    if (per_cu > 1 && (pl->big || program <= 2 * P || more_reads >= 1.25)) return;
+    if (K > 2048 ? tiles * 8 <= 5 * P : M <= 16 && K < 1536) return;
     if (b.gk == 1 && tiles * 6 < P) return;
+    if (split_k && program <= P && (b.gk < 4 ? K > 16 * 64 && pl->st.k_parts == 1 && more_reads >= 2 : K >= 64 * 64 && pl->st.k_parts > 1)) return;
     if (wide) {
         if (K >= 32 * 64) return;
         if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
         if (tiles * 3 < P) return;
-    }
+    } else if (K <= 16 * 64 && b.tm * b.tn >= 128 * 192 && tiles * 4 < 3 * P && pl->slot_tm[0] * pl->slot_tn[0] >= 128 * 128) return;
     // rows of tiles walked together: those with which an XCD's run of tiles touches the fewest rows of A and columns of B
     const uint64_t run = ceil_div(tiles, pl->num_xcds ? pl->num_xcds : 1);
     uint64_t least = ~0ull;

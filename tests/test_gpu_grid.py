@@ -169,3 +169,17 @@ def test_where_the_grid_is_taken():
     # fp32 results: few tiles, larger tiles beside a program of more workgroups than CUs, and long reduce axes stay where they were
     assert form(688, 768, 768, out=F32) == form(429, 3072, 768, out=F32) == form(131, 3072, 768, out=F32) == form(800, 4096, 1984, out=F32) == grid
     assert form(64, 768, 768, out=F32) == form(688, 3072, 768, out=F32) == form(429, 3072, 2048, out=F32) == tiles
+
+
+def test_launches_that_tiles_serve_faster_stay_tiles():
+    """Both sides of the lines that were set with operands from HBM too (grid_schedule has the times)."""
+    def form(M, N, K, out=S16):
+        return ft.ft_plan_launch_form(plan_of(M, N, K, flags=ft.FT_PLAN_HOST_ONLY, out=out)[2]).form
+    grid, tiles = ft.FT_FORM_GRID, ft.FT_FORM_TILES
+    # split-k tiles held at once: few groups that read twice as much; four groups on a reduce axis split again over workgroups
+    assert form(14, 4824, 1984) == form(3, 3816, 1728) == form(1, 3752, 1920) == form(5, 5720, 1920, F32) == tiles
+    assert form(61, 3272, 1472) == form(14, 10496, 1984) == form(434, 768, 3072) == form(1, 864, 1536) == grid
+    assert form(62, 4096, 4096) == form(264, 664, 6144) == form(105, 2560, 6016) == tiles and form(58, 2656, 2560) == form(125, 4096, 4096) == grid
+    # two tiles per CU that read more than the program's; large tiles on few CUs
+    assert form(648, 11008, 4096) == tiles and form(750, 11008, 4096) == grid
+    assert form(1370, 3072, 768) == form(1800, 2304, 768) == tiles and form(1432, 3072, 768) == form(1425, 2712, 768) == grid
