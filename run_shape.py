@@ -13,6 +13,12 @@ import sys
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
 
+def form_name(ft, form):
+    """What a launch of this form (FT_FORM_*) runs."""
+    names = {ft.FT_FORM_TILES: "tiles", ft.FT_FORM_ROWS: "rows", ft.FT_FORM_BLOCKS: "blocks", ft.FT_FORM_PATCHES: "patches", ft.FT_FORM_GRID: "grid"}
+    return names.get(form, "form %d" % form)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--m", type=int, required=True)
@@ -76,7 +82,7 @@ def main():
     desc = " + ".join("%dx(%dx%d w%dx%d gk%d s%d)" % (c, u.tm, u.tn, u.wm, u.wn, u.gk, u.stages) for u, c in prog)
     form = ft.ft_plan_launch_form(plan, pa[0], pb[0], pc[0])
     if form.form != ft.FT_FORM_TILES:
-        desc = "%s (launched as %s: %d workgroups)" % (desc, ("", "rows", "blocks", "patches")[form.form], form.workgroups)
+        desc = "%s (launched as %s: %d workgroups)" % (desc, form_name(ft, form.form), form.workgroups)
     print("%dx%dx%d %s: %s, %d tiles x %d parts, class %d, lds %d: %.2f us, %.1f TFLOP/s, %.0f GB/s" % (
         a.m, a.n, a.k, a.dtype, desc, st.n_tiles, st.k_parts, st.kernel_class, form.lds_bytes, ms * 1e3,
         2.0 * a.m * a.n * a.k / ms / 1e9, bytes_alg / ms / 1e6), flush=True)

@@ -106,6 +106,13 @@ def test_empty_grouped_and_bad_arguments():
     assert ft.lib().ft_plan_launch_form(None, None, None, None, ft.ft_launch_form()) == ft.FT_ERR_INVALID_ARG
 
 
+def test_every_form_has_a_name_where_it_is_printed():
+    import run_shape
+    forms = {v for k, v in vars(ft).items() if k.startswith("FT_FORM_")}
+    assert len({run_shape.form_name(ft, f) for f in forms}) == len(forms) >= 5 and form(matmul(272, 768, 768)).form in forms
+    assert run_shape.form_name(ft, max(forms) + 1)
+
+
 def test_launchers_raise_the_limit_before_they_ask_for_lds():
     """Whole rows of 128 fp32 columns off a 64-byte block ask for more than the 64 KB a kernel gets by itself; so do blocks,
     patches and the tiles.  Every file that launches with dynamic LDS raises the limit."""
