@@ -50,12 +50,23 @@ def measured_traffic(kernel):
         return None
 
 
+def launch_of(ft, uks, plan, A=0, B=0, C=0):
+    """(form, kernel, output elements computed) of a launch of this fp16 plan: a launch may be executed in another form than its
+    program's tiles, and what runs is that.  Kernels have the names they have in the committed counter profile."""
+    f, st = ft.ft_plan_launch_form(plan, A, B, C), ft.ft_plan_stats_get(plan)
+    if f.form == ft.FT_FORM_TILES:
+        two_team = st.n_ukernels > 0 and ft.ft_ukset_get(uks, st.ukernel_id[0]).gk == 2
+        return f.form, ("ft_dispatch_dt0_pp_c%d" if two_team else "ft_dispatch_dt0_c%d") % st.kernel_class, f.computed_elems
+    names = {ft.FT_FORM_GRID: "ft_grid", ft.FT_FORM_BLOCKS: "ft_big", ft.FT_FORM_ROWS: "ft_row_runs", ft.FT_FORM_PATCHES: "ft_conv_patch"}
+    return f.form, names.get(f.form, "form %d" % f.form), f.computed_elems
+
+
 def geomean(xs):
     return math.exp(sum(math.log(x) for x in xs) / len(xs))
 
 
 def private_l2_floor_bytes(ft, np, plan, K, num_xcds):
-    """Bytes one launch of this plan must move across the L2 <-> fabric boundary when every XCD has
+    """Bytes one launch of this plan's tiles must move across the L2 <-> fabric boundary when every XCD has
     its own L2 and nothing is fetched twice by the same XCD: each XCD reads once the rows of A and the
     columns of B that its tiles touch (workgroup b runs on XCD b % num_xcds), and C is written once.
     Partial tiles of a reduce-axis split are not counted (the parts of a tile share an XCD)."""
@@ -187,7 +198,8 @@ def main():
         pa, pb, pc = [t.data_ptr() for t in As], [t.data_ptr() for t in Bs], [t.data_ptr() for t in Cs]
         torch.cuda.synchronize()
         st = ft.ft_plan_stats_get(r["plan"])
-        sb = ft.ft_plan_stats_get(r["base"])
+        uks = ops[(N, K)][1]
+        form, k, computed = launch_of(ft, uks, r["plan"], pa[0], pb[0], pc[0])
         # warm-up (untimed), then exactly `steps` timed launches per variant
         timed(r["plan"], pa, pb, pc, max(1, args.warmup), graph=False)
         ms_cold = timed(r["plan"], pa, pb, pc, args.steps)
@@ -225,13 +237,12 @@ def main():
                  tflops_cold=flops / ms_cold / 1e9, tflops_warm=flops / ms_warm / 1e9,
                  tflops_base=flops / ms_base / 1e9, gbs_cold=bytes_alg / ms_cold / 1e6,
                  roof_frac_cold=t_roof * 1e3 / ms_cold, n_tiles=st.n_tiles, n_ukernels=st.n_ukernels,
-                 kernel_class=st.kernel_class, useful=st.useful_elems, covered=st.covered_elems,
-                 base_covered=sb.covered_elems, base_tiles=sb.n_tiles)
-        two_team = st.n_ukernels > 0 and ft.ft_ukset_get(ops[(N, K)][1], st.ukernel_id[0]).gk == 2
-        k = ("ft_dispatch_dt0_pp_c%d" if two_team else "ft_dispatch_dt0_c%d") % st.kernel_class
-        r["kernel"] = k
-        r["bytes_private_l2_floor"] = private_l2_floor_bytes(ft, np, r["plan"], K, hw.num_xcds)
-        per_class_floor[k] = per_class_floor.get(k, 0.0) + r["bytes_private_l2_floor"] * args.steps
+                 kernel_class=st.kernel_class, useful=st.useful_elems, form=form, kernel=k, covered=computed,
+                 base_covered=launch_of(ft, uks, r["base"], pa[0], pb[0], pc[0])[2], base_tiles=ft.ft_plan_stats_get(r["base"]).n_tiles)
+        # from the tiles' descriptors and launch order: only tiles have it
+        r["bytes_private_l2_floor"] = private_l2_floor_bytes(ft, np, r["plan"], K, hw.num_xcds) if form == ft.FT_FORM_TILES else None
+        if r["bytes_private_l2_floor"] is not None:
+            per_class_floor[k] = per_class_floor.get(k, 0.0) + r["bytes_private_l2_floor"] * args.steps
         per_class_time[k] = per_class_time.get(k, 0.0) + ms_cold * args.steps
         per_class_flops[k] = per_class_flops.get(k, 0.0) + flops * args.steps
         per_class_launches[k] = per_class_launches.get(k, 0) + args.steps
@@ -328,8 +339,8 @@ def main():
                      "hbm_attainable_gbs": {"read": round(stream_read, 1), "write": round(stream_write, 1), "copy": round(stream_copy, 1),
                                             "note": "plain streaming kernels over 1 GiB (ft_stream_rate), this run"},
                      "frac_of_attainable": round(achieved_gbs / stream_copy, 5) if hbm_bound else None,
-                     "traffic_floor_private_l2": round(per_class_floor[dom] / per_class_launches[dom]),
-                     "traffic_floor_note": "bytes per launch if each of the 8 XCDs (private L2s) fetches the A rows and "
+                     "traffic_floor_private_l2": round(per_class_floor[dom] / per_class_launches[dom]) if dom in per_class_floor else None,
+                     "traffic_floor_note": "launches of tiles only: bytes per launch if each of the 8 XCDs (private L2s) fetches the A rows and "
                                            "B columns of its own tiles exactly once and C is written once, from the "
                                            "plans' launch order; traffic above it is what the L2s re-fetch or the "
                                            "reduce-axis split exchanges",

@@ -113,6 +113,17 @@ def test_every_form_has_a_name_where_it_is_printed():
     assert run_shape.form_name(ft, max(forms) + 1)
 
 
+def test_the_benchmark_reports_what_a_launch_runs():
+    """Kernel and computed outputs are the launch form's, not those of the program that is not run."""
+    import bench
+    op, uks, plan = matmul(528, 3072, 768)
+    st = ft.ft_plan_stats_get(plan)
+    tiles, kernel, computed = bench.launch_of(ft, uks, plan, C0, C0, C0 + 4)
+    assert (tiles, kernel, computed) == (ft.FT_FORM_TILES, "ft_dispatch_dt0_%sc%d" % ("pp_" if ft.ft_ukset_get(uks, st.ukernel_id[0]).gk == 2 else "", st.kernel_class), st.covered_elems)
+    grid, kernel, computed = bench.launch_of(ft, uks, plan, C0, C0, C0)
+    assert (grid, kernel, computed) == (ft.FT_FORM_GRID, "ft_grid", form((op, uks, plan)).computed_elems) and computed > st.covered_elems
+
+
 def test_launchers_raise_the_limit_before_they_ask_for_lds():
     """Whole rows of 128 fp32 columns off a 64-byte block ask for more than the 64 KB a kernel gets by itself; so do blocks,
     patches and the tiles.  Every file that launches with dynamic LDS raises the limit."""
