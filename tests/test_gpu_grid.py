@@ -65,6 +65,21 @@ def test_every_body(M, N, K, tm, tn, gk, out, dtype):
     check_epilogue(other[rows], ref, refabs, bias, out16, f"{M}x{N}x{K} tiles")
 
 
+# with 16-bit results: every group's ring many times round, on reduce axes a program has (32 to 64 k-tiles), and one to sixteen rows
+LONG = [(95, 1136, 2048, 32, 32, 4), (33, 4688, 3072, 16, 64, 4), (65, 3392, 2048, 32, 64, 2), (257, 2032, 2560, 48, 64, 2),
+        (671, 1592, 2304, 96, 64, 1), (513, 2952, 3072, 128, 64, 1), (863, 2552, 2048, 96, 128, 1), (1793, 2104, 3328, 128, 128, 1),
+        (1, 11008, 4096, 16, 64, 4), (7, 11008, 4096, 16, 64, 4), (16, 11008, 4096, 16, 64, 4), (1, 512, 2048, 32, 32, 4),
+        (5, 1280, 2048, 32, 32, 4), (688, 768, 3072, 48, 64, 2), (403, 4096, 4096, 128, 64, 1), (750, 11008, 4096, 128, 192, 1),
+        (2328, 4096, 4096, 128, 192, 1), (1949, 3896, 3520, 128, 256, 1), (511, 2040, 3712, 64, 64, 1)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [ft.FT_F16, ft.FT_BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("M,N,K,tm,tn,gk", LONG)
+def test_long_reduce_axes_and_few_rows(M, N, K, tm, tn, gk, dtype):
+    test_every_body(M, N, K, tm, tn, gk, S16, dtype)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,tm,tn,out", [(103, 2304, 768, 16, 64, F32), (17, 4096, 768, 32, 32, F32), (183, 3088, 768, 48, 64, F32), (690, 768, 768, 48, 64, F32), (1195, 784, 768, 64, 64, F32),
                                              (660, 3072, 768, 96, 128, F32), (1141, 3072, 768, 128, 128, F32), (1329, 3072, 768, 128, 192, F32),
