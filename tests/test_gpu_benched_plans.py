@@ -13,7 +13,7 @@ import synth_inputs as si
 from oracle import contraction as oc
 from oracle import planner as P
 
-from gpu_util import check, dev_bits, run, stream
+from gpu_util import check, dev_bits, run, run_at, stream
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +42,8 @@ def test_every_benched_gemm_in_both_plans(M, N, K):
         want = b"".join(d.pack() for d in P.plan(oop, ouk, (1, M, N, K), mode, hw=ohw).descs)
         assert ft.ft_plan_descriptors(plan) == want, f"plan bytes differ from the oracle: {M}x{N}x{K} mode {mode}"
         check(run(plan, p["A"], p["B"], M * N), ref, refabs, f"benched {M}x{N}x{K} mode {mode}")
+        if ft.ft_plan_launch_form(plan).form != ft.FT_FORM_TILES:      # launched in another form: the program's tiles too (C off 16 bytes)
+            check(run_at(plan, p["A"], p["B"], M * N, ft.FT_F16, ft.FT_FORM_TILES, off_a=8, off_b=8, off_c=1), ref, refabs, f"benched {M}x{N}x{K} tiles")
 
 
 def test_benched_uKernel_sets_match_the_oracle():

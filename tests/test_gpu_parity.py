@@ -10,7 +10,7 @@ import synth_inputs as si
 from oracle import contraction as oc
 from oracle import planner as P
 
-from gpu_util import GUARD, REL_TOL, alloc_out, check, check_epilogue, dev_bits, matmul_op, out_view, run, run_epilogue, stream
+from gpu_util import GUARD, REL_TOL, alloc_out, check, check_epilogue, dev_bits, matmul_op, out_view, run, run_at, run_epilogue, stream
 from oracle import epilogue as oe
 
 pytestmark = pytest.mark.gpu
@@ -368,9 +368,10 @@ def test_launch_on_a_side_stream_and_relaunch():
 @pytest.mark.parametrize("out16,with_bias", [(False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("M", [1, 77, 300, 1232])
 def test_matmul_bias_and_narrow_output(M, out16, with_bias, dtype):
-    """C = A B (+ bias), stored as fp32 or rounded once to the inputs' 16-bit type.  M = 1 and 77 run
+    """C = A B (+ bias), stored as fp32 or rounded once to the inputs' 16-bit type.  M = 1 and 77 have
     split-k bodies, 300 a two-uKernel program, 1232 large tiles with an edge; N is not a multiple of
-    any tile width, so column-edge wave tiles take the predicated store."""
+    any tile width, so column-edge wave tiles take the predicated store.  Plans of the planner may be launched
+    in the grid of equal tiles; those in table order and C off 16 bytes run the program's tiles."""
     N, K = 760, 768
     g = np.random.default_rng(1000 * M + 10 * dtype + 2 * out16 + with_bias)
     A = si.normal_bits(g, (M, K), 1.0, dtype)
@@ -383,10 +384,14 @@ def test_matmul_bias_and_narrow_output(M, out16, with_bias, dtype):
     ref, refabs = oc.matmul(A, B, dtype, want_abs=True)
     if with_bias:
         ref = oe.add_bias(ref, bias)
-    for mode in (ft.FT_PLAN_PATCHWORK, ft.FT_PLAN_PAD_BASELINE):
+    for mode in (ft.FT_PLAN_PATCHWORK, ft.FT_PLAN_PAD_BASELINE, ft.FT_PLAN_TABLE_ORDER):
         plan = ft.ft_plan_create(op, s, ft.ft_shape(m=M), mode)
         got = run_epilogue(plan, A, B, M * N, bias=bias, out16=dtype if out16 else None)
         check_epilogue(got, ref, refabs, bias, dtype if out16 else None, f"epilogue M={M} out16={out16} bias={with_bias} mode {mode}")
+        assert mode == ft.FT_PLAN_PATCHWORK or ft.ft_plan_launch_form(plan).form == ft.FT_FORM_TILES
+        if mode == ft.FT_PLAN_PATCHWORK:
+            got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_TILES, bias, dtype if out16 else None, off_a=8, off_b=8, off_c=1)
+            check_epilogue(got, ref, refabs, bias, dtype if out16 else None, f"epilogue M={M} out16={out16} bias={with_bias} tiles")
 
 
 def test_epilogue_argument_checks():

@@ -61,8 +61,9 @@ def test_noalloc_back_to_back_on_one_stream_without_host_waits():
         assert np.array_equal(out_view(buf, M * N), want), M
 
 
-def test_noalloc_with_bias_and_without_split():
-    M, N, K = 300, 760, 768
+@pytest.mark.parametrize("N,form", [(760, ft.FT_FORM_GRID), (504, ft.FT_FORM_TILES)], ids=["grid", "tiles"])
+def test_noalloc_with_bias_and_without_split(N, form):
+    M, K = 300, 768
     g = np.random.default_rng(5)
     A = si.normal_bits(g, (M, K), 1.0, ft.FT_BF16)
     B = si.normal_bits(g, (K, N), 0.05, ft.FT_BF16)
@@ -71,6 +72,7 @@ def test_noalloc_with_bias_and_without_split():
     s = ft.ft_ukernels_derive(op)
     plan = ft.ft_plan_create(op, s, ft.ft_shape(m=M), ft.FT_PLAN_PATCHWORK | ft.FT_PLAN_HOST_ONLY)
     ref_plan = ft.ft_plan_create(op, s, ft.ft_shape(m=M))
+    assert ft.ft_plan_launch_form(plan).form == form and ft.ft_plan_stats_get(plan).k_parts == 1
     dA, dB, dbias = dev_bits(A), dev_bits(B), torch.from_numpy(bias).cuda()
     outs = []
     for which in (0, 1):
