@@ -621,16 +621,18 @@ void big_schedule(ft_plan *pl) {
 // its terms in a row, against 64 bits 768 f16 products are off by 1.8e-7 in one sum, 1.3e-7 in two and 1.0e-7 in four.  (Of 16-bit
 // results the one rounding is all, 2e-4: both forms agree to 3e-6 of that.)
 // Against the program's tiles and the blocks of 256 x 256, 2544 launches of those ranges with operands and C from HBM / in the caches:
-// 2436 in the grid, 0.72 / 0.65 of the time in the mean, longer by more than 2 % in 137 / 14, by 24 / 13 % at most.  What stays with
-// tiles and blocks, us, they / the grid, from HBM (and in the caches):
+// 2438 in the grid, 0.72 / 0.65 of the time in the mean, longer by more than 2 % in 138 / 15, by 24 / 13 % at most but for the one named
+// below.  What stays with tiles and blocks, us, they / the grid, from HBM (and in the caches):
 //   - with 16-bit results next to nothing of one tile per CU and less, but for few tiles (against the blocks 0.95 of the time in the mean of
-//     105 launches, 1.04 at most; 1230 x 4096 x 4096 53.8 / 49.4): a long reduce axis shared by no more than 160 workgroups, which the
-//     program splits finer (29 x 768 x 3072 7.0 / 8.5, 24 x 4984 x 5632 17.2 / 26.2, 105 x 2560 x 6016 20.6 / 28.5), up to 16 rows with
-//     a short one (12 x 3072 x 768 4.1 / 4.2), and a body without groups on less than a sixth of the CUs (19 x 1792 x 960 4.2 / 4.8);
-//   - programs of split-k tiles that the device holds at once: against a body of fewer than four groups, if a CU then reads twice as many
-//     rows and columns of the operands (14 x 4824 x 1984 9.7 / 11.8, 3 x 3816 x 1728 6.9 / 9.6; 58 launches 1.18 (1.02) of the time; up to
-//     16 k-tiles they are in the grid all the same, 11 launches 1.12 (1.01)), and split again over workgroups at 64 k-tiles or more
-//     (62 x 4096 x 4096 16.5 / 18.2 (12.3 / 12.0), 264 x 664 x 6144 16.1 / 20.1 (15.0 / 18.3); 15 launches 1.10 (1.01));
+//     105 launches, 1.04 at most; 1230 x 4096 x 4096 53.8 / 49.4): a long reduce axis shared by fewer workgroups than five eighths of the CUs,
+//     which the program splits finer (29 x 768 x 3072 7.0 / 8.5, 24 x 4984 x 5632 17.2 / 26.2; on that line 1009 x 632 x 2880 takes 0.96 (0.83)
+//     of the time and 105 x 2560 x 6016 1.38 (1.21)), up to 16 rows with a short one (12 x 3072 x 768 4.1 / 4.2), and a body without groups
+//     on less than a sixth of the CUs (19 x 1792 x 960 4.2 / 4.8);
+//   - programs of split-k tiles that the device holds at once: of 17 to 32 k-tiles against a body of fewer than four groups, if a CU then
+//     reads twice as many rows and columns of the operands (14 x 4824 x 1984 9.7 / 11.8, 3 x 3816 x 1728 6.9 / 9.6; 58 launches 1.18 (1.02)
+//     of the time; up to 16 k-tiles they are in the grid all the same, 11 launches 1.12 (1.01)), and against one of four groups where they
+//     split 64 k-tiles or more over workgroups too (62 x 4096 x 4096 16.5 / 18.2 (12.3 / 12.0), 264 x 664 x 6144 16.1 / 20.1 (15.0 / 18.3);
+//     15 launches 1.10 (1.01));
 //   - two or three tiles per CU where the blocks are taken (with them 0.77 to 1.1 times), where the program has no more than two workgroups
 //     per CU (1600 x 5120 x 2048 44.8 / 46.2 (38.3 / 43.7); with more 2328 x 4096 x 4096 109 / 86.7) and where a CU reads a quarter more
 //     (648 x 11008 x 4096 78.9 / 86.1 (71.9 / 74.2), 750 rows, 0.88 times as much, 122 / 95.1); more were not looked at;
@@ -690,9 +692,9 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols;
     const double more_reads = (double)(per_cu * (b.tm + b.tn)) / reads;
     if (per_cu > 1 && (pl->big || program <= 2 * P || more_reads >= 1.25)) return;
-    if (K > 2048 ? tiles * 8 <= 5 * P : M <= 16 && K < 1536) return;
+    if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
     if (b.gk == 1 && tiles * 6 < P) return;
-    if (split_k && program <= P && (b.gk < 4 ? K > 16 * 64 && pl->st.k_parts == 1 && more_reads >= 2 : K >= 64 * 64 && pl->st.k_parts > 1)) return;
+    if (split_k && program <= P && (b.gk < 4 ? K > 16 * 64 && K <= 32 * 64 && pl->st.k_parts == 1 && more_reads >= 2 : K >= 64 * 64 && pl->st.k_parts > 1)) return;
     if (wide) {
         if (K >= 32 * 64) return;
         if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
