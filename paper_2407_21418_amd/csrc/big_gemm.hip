@@ -2,8 +2,8 @@
 //
 // What bounds a large product on this device is power: the MFMAs alone run at 2.4 PFLOP/s on zeros and at 1.7-1.8
 // (32x32x16) or 2.07 (16x16x32) on N(0,1) operands, the loop below at 1.65 on zeros and 1.4-1.5 on N(0,1).  (Counters of 8192 x
-// 11008 x 4096 bf16, six launches in a row: the clock falls from 1.88 to 1.54 GHz, the matrix cores are busy for 76 % of the
-// cycles; LDS is active for 48 % of them, four tenths of that bank conflicts.)  Against
+// 11008 x 4096 bf16, six launches in a row: the clock falls from 1.84 to 1.49 GHz, the matrix cores are busy for 80 % of the
+// cycles; LDS is active for 51 % of them, four tenths of that bank conflicts.)  Against
 // the tile bodies (gemm_fast.h, 1.1-1.2 PFLOP/s on the same 256 x 256 tile) it
 //   - uses v_mfma_f32_16x16x32, which does the same products for less power than 32x32x16;
 //   - keeps the fragments of one k-step in registers while the MFMAs of the other run, so that no MFMA waits for

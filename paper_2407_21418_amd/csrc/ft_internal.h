@@ -65,7 +65,7 @@ struct ft_plan {
     // large products (big_gemm.hip): a launch executes blocks of 256 x 256, some of them as halves of 128 rows
     bool big;
     uint32_t big_rows, big_cols, big_full, big_half;
-    // Matmuls of the middle range with 16-bit results (grid_gemm.hip): a launch executes one grid of equal tiles
+    // Matmuls of the middle range (grid_gemm.hip): a launch executes one grid of equal tiles
     bool grid;
     uint32_t grid_body, grid_rows, grid_cols, grid_group;
     // 3 x 3 convolutions of 64 input channels (conv_patch.hip): tiles of conv_th x conv_tw output pixels, at most

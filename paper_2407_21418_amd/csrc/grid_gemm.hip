@@ -8,14 +8,16 @@
 //   - the copies are buffer loads into LDS: the lane's offset never changes, the k-tile is the instruction's scalar offset,
 //     neighbouring kilobytes share one M0 through the instruction's immediate (which moves the source too: the lane's offset
 //     takes it back), rows below the operand's end read as zeros by the descriptor's bound, so nothing is clamped or predicated;
-//   - the steady loop has one form of every wait and no branch; the last STAGES tiles run a copy of it without copies;
+//   - the steady loop has one form of every wait and no branch; the last tiles, STAGES + 1 at most, run a copy of it in which a copy, if
+//     one is still due, stands in front of the MFMAs;
 //   - both k-steps of a tile are in registers before its first MFMA; the next tile's are read beside them, so there is one
 //     barrier and one wait for LDS per k-tile;
 //   - MFMAs are 16x16x32, operands handed over the other way round (a lane's four registers are four neighbouring columns).
-// Beyond that a CU pulls its operand panels through one path at about 46 bytes a cycle, the tile's bytes set the time.
-// f16, us, the program's tiles against this: 688 x 2304 x 768 8.5 / 6.4, x 768 x 768 6.9 / 4.7, x 3072 x 768 8.7 / 7.5,
-// x 768 x 3072 12.9 / 11.3, 1600 x 768 x 3072 17.0 / 14.2; with fp32 results 688 x 768 x 768
-// 7.4 / 5.5, 429 x 3072 x 768 8.4 / 6.7, 131 x 3072 x 768 6.5 / 4.9 (16 bytes per lane straight from the accumulators).
+// Beyond that a CU pulls its operand panels through one path at 33 to 40 bytes a cycle (a k-tile's bytes over the steps of kGridCost in
+// host.cpp), the tile's bytes set the time; the matrix cores are busy for 13 to 44 % of it and the LDS for a third at most.
+// f16, everything in the caches, us, the program's tiles against this: 688 x 2304 x 768 8.0 / 6.2, x 768 x 768 6.9 / 4.6, x 3072 x 768
+// 8.1 / 7.3, x 768 x 3072 12.9 / 10.9, 1600 x 768 x 3072 16.9 / 14.2; with fp32 results 688 x 768 x 768 6.8 / 4.9, 429 x 3072 x 768
+// 7.9 / 6.1, 131 x 3072 x 768 5.9 / 4.4 (16 bytes per lane straight from the accumulators).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,7 +49,7 @@ template <int IMM> __device__ __forceinline__ void grid_copy16(__amdgpu_buffer_r
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds_wave_base, 16, (int)lane_off, (int)tile_off, IMM, 0);
 }
 // Swizzle of A's 16-byte chunks: a wave reads 16 rows at four neighbouring chunks, for which row & 7 lets the LDS serve 252 bytes a
-// cycle (eight waves reading; swzA, made for 32 rows at two chunks, 128).
+// cycle (eight waves reading; swzA, made for 32 rows at two chunks, 128); the counters show no bank conflicts.
 __device__ __forceinline__ uint32_t grid_swzA(uint32_t row) { return row & 7u; }
 // Swizzle of B's 16-byte chunks: as swzB, and closed within rows of 24 chunks (groups of eight, neighbouring rows 32 banks apart).
 template <int TN> __device__ __forceinline__ uint32_t grid_swzB(uint32_t row) {
