@@ -2,7 +2,7 @@
 #pragma once
 #include <stdint.h>
 
-#include "tile_order.h"
+#include "tile_order.h"          // FT_HD
 
 namespace ftk {
 
@@ -22,33 +22,49 @@ namespace ftk {
     X(10, 64, 64, 2, 4, 1, 3)                                                                      \
     X(11, 32, 32, 2, 4, 1, 4)
 
+// Which tile a workgroup takes: every XCD (workgroup b runs on XCD b % nx) has one contiguous run of the tiles, walked in bands of
+// `group` rows, column by column.  Packed into six words with the reciprocals of the divisors, so that all a workgroup needs to ask
+// for its first k-tiles is in registers when it starts (see ft_grid); at most kGridTilesMax tiles and 255 XCDs.
+struct GridOrder {
+    uint32_t share;                      // tiles of an XCD | XCDs that have one more << 16 | XCDs << 24
+    uint32_t band;                       // tiles of a band | its rows << 16
+    uint32_t last;                       // bands of that many rows | rows of what is left below them << 16
+    uint32_t per_band, per_rows, per_last;          // ceil(2^31 / tiles of a band, rows of a band, rows of the last one)
+};
+struct GridTile {
+    uint32_t row, col;
+};
+constexpr uint32_t kGridTilesMax = 32767;
+inline GridOrder grid_order(uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx) {
+    const uint32_t n = rows * cols, low = rows % group;
+    auto per = [](uint32_t d) -> uint32_t { return d ? (0x80000000u + d - 1u) / d : 0u; };
+    return GridOrder{n / nx | (n % nx) << 16 | nx << 24, group * cols | group << 16, rows / group | low << 16, per(group * cols), per(group), per(low)};
+}
+// x / d, per = ceil(2^31 / d): exact for x, d < 2^15 (x * (per * d - 2^31) < 2^31)
+FT_HD uint32_t grid_div(uint32_t x, uint32_t per) { return (uint32_t)((uint64_t)(x * 2u) * per >> 32); }
+FT_HD GridTile grid_tile(const GridOrder &o, uint32_t b) {
+    const uint32_t nx = o.share >> 24, more = o.share >> 16 & 255u;
+    uint32_t x, q;
+    if (nx == 8) { x = b & 7u; q = b >> 3; }
+    else { x = b % nx; q = b / nx; }
+    const uint32_t u = x * (o.share & 0xffffu) + (x < more ? x : more) + q;
+    const uint32_t i = grid_div(u, o.per_band), w = u - i * (o.band & 0xffffu);
+    const bool low = i >= (o.last & 0xffffu);
+    const uint32_t col = grid_div(w, low ? o.per_last : o.per_rows);
+    return GridTile{i * (o.band >> 16) + w - col * (low ? o.last >> 16 : o.band >> 16), col};
+}
+FT_HD GridTile grid_tile(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx) { return grid_tile(grid_order(rows, cols, group, nx), b); }
+
 struct GridArgs {
     const uint16_t *A;
     const uint16_t *B;
     void *C;                             // fp32 or the inputs' 16-bit type
     const float *bias;                   // one per column, or NULL
     uint32_t M, N, K;
-    uint32_t rows, cols, tiles;          // tiles = rows * cols workgroups
-    uint32_t group;                      // rows of tiles walked together
-    uint32_t num_xcds;
+    uint32_t tiles;                      // workgroups
+    GridOrder order;
     uint32_t stream;                     // rows of an fp32 C lie on 64-byte blocks: they are stored past the caches
 };
-
-// workgroup b's tile: every XCD (workgroup b runs on XCD b % nx) takes one contiguous run of the tiles in groups of `group` rows,
-// column by column
-struct GridTile {
-    uint32_t row, col;
-};
-template <uint32_t NX> FT_HD GridTile grid_tile_nx(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx_in) {
-    const uint32_t nx = NX ? NX : nx_in, n = rows * cols, x = b % nx, base = n / nx, rem = n % nx;
-    uint32_t bi;
-    GridTile t;
-    grouped_coords(x * base + (x < rem ? x : rem) + b / nx, rows, cols, group, &bi, &t.row, &t.col);
-    return t;
-}
-FT_HD GridTile grid_tile(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx) {
-    return nx == 8 ? grid_tile_nx<8>(b, rows, cols, group, nx) : grid_tile_nx<0>(b, rows, cols, group, nx);
-}
 
 // Sums a wave keeps of an output, added at the end: with fp32 results the k-steps of a k-tile have one each, and where one group
 // takes the whole reduce axis those of even and odd k-tiles, as far as the registers go.  The error of a sum grows with the root of

@@ -690,6 +690,7 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     if (per_cu == 0) return;
     const ftk::GridBodyInfo &b = ftk::kGridBodies[pl->grid_body];
     const uint64_t tiles = (uint64_t)pl->grid_rows * pl->grid_cols;
+    if (tiles > ftk::kGridTilesMax || pl->num_xcds > 255) return;     // (what a workgroup's packed arguments hold)
     const double more_reads = (double)(per_cu * (b.tm + b.tn)) / reads;
     if (per_cu > 1 && (pl->big || program <= 2 * P || more_reads >= 1.25)) return;
     if (K > 2048 ? tiles * 8 < 5 * P : M <= 16 && K < 1536) return;
