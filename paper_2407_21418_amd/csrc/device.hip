@@ -374,7 +374,7 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.M = a.M; r.N = a.N; r.K = a.K;
         r.tiles = plan->grid_rows * plan->grid_cols;
         r.order = ftk::grid_order(plan->grid_rows, plan->grid_cols, plan->grid_group, plan->num_xcds);
-        r.stream = !out16 && reinterpret_cast<uintptr_t>(C) % 64 == 0 && a.N % 16 == 0;
+        r.through = reinterpret_cast<uintptr_t>(C) % 64 == 0 && (uint64_t)a.N * (out16 ? 2 : 4) % 64 == 0;
         const int rc = ft_launch_grid(&r, plan->grid_body, (int)plan->op.dtype, out16, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;

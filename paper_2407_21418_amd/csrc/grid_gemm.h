@@ -63,7 +63,7 @@ struct GridArgs {
     uint32_t M, N, K;
     uint32_t tiles;                      // workgroups
     GridOrder order;
-    uint32_t stream;                     // rows of an fp32 C lie on 64-byte blocks: they are stored past the caches
+    uint32_t through;                    // rows of C lie on 64-byte blocks: they are written through the L2
 };
 
 // Sums a wave keeps of an output, added at the end: with fp32 results the k-steps of a k-tile have one each, and where one group

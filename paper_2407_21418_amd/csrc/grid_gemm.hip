@@ -145,19 +145,34 @@ struct GridBody {
         if constexpr (DT == DT_F16) return (uint32_t)out_cvt<OUT_F16>(x) | ((uint32_t)out_cvt<OUT_F16>(y) << 16);
         else return __builtin_bit_cast(uint32_t, __builtin_convertvector(grid_f32x2{x, y}, grid_bf16x2));
     }
-    // fp32 results whose rows lie on 64-byte blocks (an instruction fills 16 of them) bypass the caches, as the tiles' do: kept in L2
-    // they are written back while the next launch asks for its first tiles.  Operands and C from HBM, kept / this / the program's
-    // tiles, us: 1009 x 3072 x 768 13.5 / 10.2 / 10.6, 666 x 3072 x 768 11.5 / 8.7 / 9.0; in the caches 10.6 / 9.6 / 10.1, 9.0 / 8.1 / 8.6.
-    // Parts of blocks are kept, to meet in L2 (past it a launch takes up to 1.5 times as long), and so are 16-bit results, which the next
-    // Matmul reads: an encoder's twelve layers on 688 rows, kept / past the caches, 380 / 410 with the weights in the last-level cache,
-    // 466 / 461 with weights from HBM.
+    // Where the rows of C lie on 64-byte blocks and an instruction fills whole ones, results are written through the L2 (sc1): as dirty
+    // lines they would be written back when the launch ends, and the next one waits for that.  16-bit results stay in the
+    // last-level cache, where the next Matmul finds them: 1500 x 2304 x 768 9.5 -> 8.8 us, 688 x 3072 x 768 7.9 -> 7.6, operands and C from
+    // HBM 10.3 -> 9.5 and 8.8 -> 8.4; an encoder's twelve layers on 688 rows 404 -> 394 with weights from HBM, 378 -> 368 without (streamed
+    // 444, 429).  fp32 results are streamed as well (sc1 nt): 800 x 4096 x 1984 18.7 -> 18.0, 688 x 768 x 768 5.0 -> 4.9, from HBM 18.8 -> 17.8
+    // and 5.2 -> 5.1; without the hint 19.6 from HBM.  Parts of blocks are kept, to meet in L2 (1500 x 3080 x 768, 16-bit, from HBM 13.1 kept,
+    // 15.0 written through; 1432 x 3072 x 768, whose waves are 48 columns wide, 12.5 and 14.3; groups, which store 32 bytes of a row,
+    // up to 4 % slower).
+    static constexpr bool WHOLE = !OUT16 || (GK == 1 && WN % 32 == 0);
+    static constexpr int POLICY = OUT16 ? 16 : 18;                     // cache-policy bits: sc1, sc1 | nt
+    static constexpr uint32_t ES = OUT16 ? 2 : 4;
+    struct Out {                                                      // a wave's part of C
+        __amdgpu_buffer_rsrc_t r;                                     // ends with the last row there is
+        uint32_t row_bytes, first, columns;                           // first: this lane's row; columns of C from the wave's first one on
+    };
+    // 16 or 8 bytes at column c of the wave's part, 16 * i rows below the lane's first.  The row goes into the lane's offset: a 16-byte
+    // buffer store with its offset in a scalar register still reads its last register when the next instruction may write it
+    // already, and the compiler, which keeps the two apart otherwise, takes that form for safe (gfx950: rows 12 to 15 of a block
+    // got another block's last column).
+    template <bool THROUGH, typename V> __device__ static __forceinline__ void store(const Out &o, uint32_t i, uint32_t c, V v) {
+        const uint32_t at = c < o.columns ? o.first + i * 16u * o.row_bytes + c * ES : 0x80000000u;  // (past the end: dropped)
+        if constexpr (sizeof(V) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(grid_u32x4, v), o.r, (int)at, 0, THROUGH ? POLICY : 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(v, o.r, (int)at, 0, THROUGH ? POLICY : 0);
+    }
     // four neighbouring columns from c on
-    template <bool STREAM> __device__ static __forceinline__ void store4(const GridArgs &g, uint32_t r, uint32_t c, f32x4 v) {
-        if (r >= g.M || c >= g.N) return;
-        const uint64_t at = (uint64_t)r * g.N + c;
-        if constexpr (OUT16) *reinterpret_cast<grid_u32x2 *>(static_cast<uint16_t *>(g.C) + at) = grid_u32x2{pack(v[0], v[1]), pack(v[2], v[3])};
-        else if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(static_cast<float *>(g.C) + at));
-        else *reinterpret_cast<f32x4 *>(static_cast<float *>(g.C) + at) = v;
+    template <bool THROUGH> __device__ static __forceinline__ void store4(const Out &o, uint32_t i, uint32_t c, f32x4 v) {
+        if constexpr (OUT16) store<THROUGH>(o, i, c, grid_u32x2{pack(v[0], v[1]), pack(v[2], v[3])});
+        else store<THROUGH>(o, i, c, v);
     }
     __device__ static __forceinline__ f32x4 bias_of(const GridArgs &g, uint32_t c) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -166,11 +181,13 @@ struct GridBody {
     }
 
     // lane l holds row l % 16, columns 4 * (l / 16) .. + 3 of every 16 x 16 block
-    template <bool STREAM>
+    template <bool THROUGH>
     __device__ static __forceinline__ void finish(const GridArgs &g, f32x4 (&acc)[BM][BN], const f32x4 *bias, const unsigned char *smem, uint32_t row0, uint32_t col0,
                                                   uint32_t grp, uint32_t wave, uint32_t lane) {
-        const uint32_t q4 = lane >> 4;
-        row0 += lane & 15u;
+        if (row0 >= g.M || col0 >= g.N) return;
+        const uint32_t q4 = lane >> 4, row_bytes = g.N * ES, rows = g.M - row0 < (uint32_t)WM ? g.M - row0 : (uint32_t)WM;
+        const Out o = {__builtin_amdgcn_make_buffer_rsrc(static_cast<char *>(g.C) + ((uint64_t)row0 * g.N + col0) * ES, 0, (int)((rows - 1u) * row_bytes + (g.N - col0) * ES), 0x00020000),
+                       row_bytes, (lane & 15u) * row_bytes, g.N - col0};
         if constexpr (GK > 1) {
             // added in group order; group g finishes blocks g * PB ..
             constexpr int PB = NB / GK;
@@ -182,14 +199,13 @@ struct GridBody {
 #pragma unroll
                 for (int q = 1; q < GK; ++q) s += x[((q * NWG + wave) * NB + b) * 64u + lane];
                 s += bias[p];
-                store4<STREAM>(g, row0 + (b / BN) * 16u, col0 + (b % BN) * 16u + q4 * 4u, s);
+                store4<THROUGH>(o, b / BN, (b % BN) * 16u + q4 * 4u, s);
             }
         } else {
             // 16-bit results, two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them
-            const uint32_t cc = col0 + (q4 & 1u) * 16u + (q4 >> 1) * 8u;
+            const uint32_t cc = (q4 & 1u) * 16u + (q4 >> 1) * 8u;
 #pragma unroll
             for (int i = 0; i < BM; ++i) {
-                const uint32_t r = row0 + i * 16u;
 #pragma unroll
                 for (int j = 0; j < BN; ++j) acc[i][j] += bias[j];
                 if constexpr (OUT16) {
@@ -197,12 +213,11 @@ struct GridBody {
                     for (int j = 0; j + 1 < BN; j += 2) {
                         const auto lo = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
                         const auto hi = __builtin_amdgcn_permlane16_swap(pack(acc[i][j][2], acc[i][j][3]), pack(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
-                        const grid_u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
-                        if (r < g.M && cc + j * 16u < g.N) *reinterpret_cast<grid_u32x4 *>(static_cast<uint16_t *>(g.C) + (uint64_t)r * g.N + cc + j * 16u) = v;
+                        store<THROUGH>(o, i, j * 16u + cc, grid_u32x4{lo[0], hi[0], lo[1], hi[1]});
                     }
                 }
 #pragma unroll
-                for (int j = OUT16 ? BN / 2 * 2 : 0; j < BN; ++j) store4<STREAM>(g, r, col0 + j * 16u + q4 * 4u, acc[i][j]);
+                for (int j = OUT16 ? BN / 2 * 2 : 0; j < BN; ++j) store4<THROUGH>(o, i, j * 16u + q4 * 4u, acc[i][j]);
             }
         }
     }
@@ -328,7 +343,7 @@ struct GridBody {
             for (int b = 0; b < NB; ++b) x[((grp * NWG + wave) * NB + b) * 64u + lane] = acc[b / BN][b % BN];
             __syncthreads();
         }
-        if (!OUT16 && g.stream) finish<!OUT16>(g, acc, bias, smem, m0 + wm * WM, col0, grp, wave, lane);
+        if (WHOLE && g.through) finish<WHOLE>(g, acc, bias, smem, m0 + wm * WM, col0, grp, wave, lane);
         else finish<false>(g, acc, bias, smem, m0 + wm * WM, col0, grp, wave, lane);
     }
 };
@@ -340,11 +355,11 @@ struct GridBody {
 // same arguments read from memory: 6.33, 4.79, 7.68.  (In fours: the host spends 10 ns on every argument of a launch.)
 template <int DT, bool OUT16, int WM, int WN, int GM, int GN, int GK, int S>
 __global__ __launch_bounds__(GM * GN * GK * 64, 2) void ft_grid(const uint16_t *A, const uint16_t *B, grid_u32x4 knm_share, grid_u32x4 band_last_per, uint32_t per_last,
-                                                                uint32_t stream, void *C, const float *bias) {
+                                                                uint32_t through, void *C, const float *bias) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const GridTile t = grid_tile(GridOrder{knm_share[3], band_last_per[0], band_last_per[1], band_last_per[2], band_last_per[3], per_last}, blockIdx.x);
     GridArgs g;
-    g.A = A; g.B = B; g.C = C; g.bias = bias; g.K = knm_share[0]; g.N = knm_share[1]; g.M = knm_share[2]; g.stream = stream;
+    g.A = A; g.B = B; g.C = C; g.bias = bias; g.K = knm_share[0]; g.N = knm_share[1]; g.M = knm_share[2]; g.through = through;
     GridBody<DT, OUT16, WM, WN, GM, GN, GK, S>::run(g, t.row, t.col, smem);
 }
 
@@ -359,7 +374,7 @@ static int launch(const ftk::GridArgs *g, void *stream) {
     if (e != hipSuccess) return (int)e;
     hipLaunchKernelGGL(kernel, dim3(g->tiles), dim3(info.waves * 64), info.lds, static_cast<hipStream_t>(stream), g->A, g->B,
                        ftk::grid_u32x4{g->K, g->N, g->M, g->order.share}, ftk::grid_u32x4{g->order.band, g->order.last, g->order.per_band, g->order.per_rows},
-                       g->order.per_last, g->stream, g->C, g->bias);
+                       g->order.per_last, g->through, g->C, g->bias);
     return (int)hipGetLastError();
 }
 
