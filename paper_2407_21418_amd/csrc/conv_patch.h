@@ -32,5 +32,6 @@ FT_CONV_HD uint32_t conv_patch_bytes(uint32_t rows) { return (rows + 7u) / 8u * 
 
 }  // namespace ftk
 
-// bm: 16-pixel blocks per wave, 1..4 (tiles of up to 64 * bm pixels)
-extern "C" int ft_launch_conv(const ftk::ConvArgs *args, int dt, int out16, int bm, uint32_t lds_bytes, void *stream);
+// bm: 16-pixel blocks per wave, 1..4 (tiles of up to 64 * bm pixels); keep: results stay in the L2 (2), in the last-level cache (1) or in
+// neither (0)
+extern "C" int ft_launch_conv(const ftk::ConvArgs *args, int dt, int out16, int bm, int keep, uint32_t lds_bytes, void *stream);

@@ -4,8 +4,8 @@
 // pulls nine times its image through the CUs' vector memory path, and the k loop runs at the rate of that path.  Here a
 // workgroup keeps the filter taps of 64 output channels in LDS (72 KB) and walks over tiles of up to 256 output pixels: a
 // tile's patch of the image is fetched once, halo and zero padding included, and every tap reads its rows of A from the
-// patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 to 74 us with fp32 results, 88 to 60 with 16-bit ones; 8 x 56 x 56: 10.8
-// to 9.9; 8 x 28 x 28: 6.6 to 5.2.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
+// patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 to 65 us with fp32 results, 88 to 62 with 16-bit ones; 8 x 56 x 56: 10.8
+// to 8.2; 8 x 28 x 28: 6.6 to 4.9.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
 // 2.2 GHz, and 1.5 us of copies, waits and barrier (counters: matrix cores busy for 54 % of the cycles on 224 x 224); the
 // smallest launches are bound by their latencies: taps and patch 1.5 us, nine taps 1.3 (27 % on 56 x 56).
 //   - One workgroup of eight waves per CU, the patch of the next tile arriving while this one is computed: no wait and no
@@ -14,6 +14,11 @@
 //     needs the same barriers and lost 0.5 us; copies spread over the taps, as the stores are, changed nothing.)
 //   - The results of a tile leave while the next one is computed, a store or two per tap: a CU's vector memory path is in
 //     order, and a burst of stores would hold up the waves and the next patch behind it.
+//     Where a pixel's channels lie on 64-byte blocks they are written through the L2: as dirty lines they would be written back
+//     when the launch ends and while other tiles are read.  Those of more than a quarter of the last-level cache are streamed past it
+//     too (KEEP).  fp32 results, kept / written through / streamed as well, us: 8 x 56 x 56 9.8 / 8.2 / 8.2, 8 x 75 x 75 12.5 / 10.5 /
+//     10.9, 8 x 112 x 112 23.5 / 21.3 / 21.8, 8 x 145 x 145 38.7 / 41.6 / 32.4, 8 x 224 x 224 78.0 / 80.1 / 65.4; 16-bit results 8.1 / 7.5 /
+//     7.5, 11.0 / 9.7 / 9.7, 21.2 / 20.0 / 20.3, 30.3 / 29.4 / 29.3, 64.0 / 66.3 / 61.7.
 //   - A pixel's 64 channels are one 128-byte row of LDS, its 16-byte chunks at chunk ^ (x & 7), x the column in the patch: 16
 //     neighbouring pixels are read without a bank conflict whatever column a tap makes them start at (counted: none on
 //     224 x 224, tiles 16 wide; 23 % of the LDS cycles on 56 x 56, where 16 pixels of a tile 28 wide lie in two of its rows), and
@@ -43,7 +48,8 @@ __device__ __forceinline__ void conv_dma16(const void *gptr, unsigned char *lds_
 }
 
 // Eight waves, 4 of BM x 16 pixels by 2 of 32 channels.
-template <int DT, bool OUT16, int BM>
+// KEEP: where results stay, 2 in the L2, 1 in the last-level cache, 0 in neither.
+template <int DT, bool OUT16, int BM, int KEEP>
 struct ConvBody {
     static constexpr int GN = 2, WM = BM * 16, WN = 32, BN = 2, TN = 64;
     static constexpr int NR = BM + 2 * BN, NM = BM * BN;
@@ -217,7 +223,7 @@ struct ConvBody {
                 const auto hi = __builtin_amdgcn_permlane16_swap(pack(old[i][0][2], old[i][0][3]), pack(old[i][1][2], old[i][1][3]), false, false);
                 v = conv_u32x4{lo[0], hi[0], lo[1], hi[1]};
             } else v = __builtin_bit_cast(conv_u32x4, old[i][j]);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)o, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)o, 0, KEEP == 2 ? 0 : KEEP == 1 ? 16 : 18);        // sc1, sc1 | nt
         };
 
         conv_wait_vm<0>();
@@ -273,36 +279,45 @@ struct ConvBody {
     }
 };
 
-template <int DT, bool OUT16, int BM>
+template <int DT, bool OUT16, int BM, int KEEP>
 __global__ __launch_bounds__(512, 1) void ft_conv_patch(ConvArgs g) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     // workgroup b runs on XCD b % num_xcds: an XCD takes one contiguous run of the walkers, and with it neighbouring tiles
     // (whose patches overlap) at a time
     const uint32_t nx = g.num_xcds, b = blockIdx.x, n = g.walkers * g.cols, x = b % nx, q = n / nx, r = n % nx;
     const uint32_t u = x * q + (x < r ? x : r) + b / nx;
-    ConvBody<DT, OUT16, BM>::run(g, __builtin_amdgcn_readfirstlane(u / g.cols), __builtin_amdgcn_readfirstlane(u % g.cols * 64u), smem);
+    ConvBody<DT, OUT16, BM, KEEP>::run(g, __builtin_amdgcn_readfirstlane(u / g.cols), __builtin_amdgcn_readfirstlane(u % g.cols * 64u), smem);
 }
 
 }  // namespace ftk
 
-template <int DT, bool OUT16, int BM>
+template <int DT, bool OUT16, int BM, int KEEP>
 static int launch(const ftk::ConvArgs *g, uint32_t lds_bytes, void *stream) {
-    const hipError_t e = ftk::raise_lds_limit<&ftk::ft_conv_patch<DT, OUT16, BM>>();
+    constexpr auto kernel = &ftk::ft_conv_patch<DT, OUT16, BM, KEEP>;
+    const hipError_t e = ftk::raise_lds_limit<kernel>();
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((ftk::ft_conv_patch<DT, OUT16, BM>), dim3(g->walkers * g->cols), dim3(512), lds_bytes, static_cast<hipStream_t>(stream), *g);
+    hipLaunchKernelGGL(kernel, dim3(g->walkers * g->cols), dim3(512), lds_bytes, static_cast<hipStream_t>(stream), *g);
     return (int)hipGetLastError();
 }
+template <int DT, bool OUT16, int BM>
+static int launch_keep(const ftk::ConvArgs *g, int keep, uint32_t lds_bytes, void *stream) {
+    switch (keep) {
+        case 0: return launch<DT, OUT16, BM, 0>(g, lds_bytes, stream);
+        case 1: return launch<DT, OUT16, BM, 1>(g, lds_bytes, stream);
+        default: return launch<DT, OUT16, BM, 2>(g, lds_bytes, stream);
+    }
+}
 template <int DT, bool OUT16>
-static int launch_bm(const ftk::ConvArgs *g, int bm, uint32_t lds_bytes, void *stream) {
+static int launch_bm(const ftk::ConvArgs *g, int bm, int keep, uint32_t lds_bytes, void *stream) {
     switch (bm) {
-        case 1: return launch<DT, OUT16, 1>(g, lds_bytes, stream);
-        case 2: return launch<DT, OUT16, 2>(g, lds_bytes, stream);
-        case 3: return launch<DT, OUT16, 3>(g, lds_bytes, stream);
-        default: return launch<DT, OUT16, 4>(g, lds_bytes, stream);
+        case 1: return launch_keep<DT, OUT16, 1>(g, keep, lds_bytes, stream);
+        case 2: return launch_keep<DT, OUT16, 2>(g, keep, lds_bytes, stream);
+        case 3: return launch_keep<DT, OUT16, 3>(g, keep, lds_bytes, stream);
+        default: return launch_keep<DT, OUT16, 4>(g, keep, lds_bytes, stream);
     }
 }
 
-extern "C" int ft_launch_conv(const ftk::ConvArgs *g, int dt, int out16, int bm, uint32_t lds_bytes, void *stream) {
-    if (dt) return out16 ? launch_bm<1, true>(g, bm, lds_bytes, stream) : launch_bm<1, false>(g, bm, lds_bytes, stream);
-    return out16 ? launch_bm<0, true>(g, bm, lds_bytes, stream) : launch_bm<0, false>(g, bm, lds_bytes, stream);
+extern "C" int ft_launch_conv(const ftk::ConvArgs *g, int dt, int out16, int bm, int keep, uint32_t lds_bytes, void *stream) {
+    if (dt) return out16 ? launch_bm<1, true>(g, bm, keep, lds_bytes, stream) : launch_bm<1, false>(g, bm, keep, lds_bytes, stream);
+    return out16 ? launch_bm<0, true>(g, bm, keep, lds_bytes, stream) : launch_bm<0, false>(g, bm, keep, lds_bytes, stream);
 }

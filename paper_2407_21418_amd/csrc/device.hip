@@ -350,7 +350,9 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.tiles_y = g.tiles_y; r.tiles_x = g.tiles_x; r.tiles = g.tiles;
         r.cols = g.cols; r.walkers = g.walkers;
         r.num_xcds = plan->num_xcds;
-        const int rc = ft_launch_conv(&r, (int)plan->op.dtype, out16, (int)plan->conv_bm, g.lds_bytes, hip_stream);
+        const uint64_t pixel_bytes = (uint64_t)a.N * (out16 ? 2 : 4);
+        const int keep = reinterpret_cast<uintptr_t>(C) % 64 || pixel_bytes % 64 ? 2 : a.M * pixel_bytes <= (64u << 20) ? 1 : 0;     // (a quarter of the last-level cache)
+        const int rc = ft_launch_conv(&r, (int)plan->op.dtype, out16, (int)plan->conv_bm, keep, g.lds_bytes, hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
     }

@@ -81,3 +81,33 @@ def test_patches_anywhere_in_memory(n, h, w, co, pad, out):
         got = run_at(plan, X, Wt, M * co, dtype, form, bias, out16, off_c=off_c).reshape(M, co)
         assert np.isfinite(got).all(), "uncovered outputs"
         check_epilogue(got[pix], ref, refabs, bias, out16, f"{n}x{h}x{w} -> {co}, padding {pad}, form {form}")
+
+
+@pytest.mark.parametrize("n,size,co,out", [(8, 41, 128, ft.FT_OUT_F32), (8, 41, 32, ft.FT_OUT_SAME), (8, 145, 128, ft.FT_OUT_F32), (8, 183, 128, ft.FT_OUT_SAME)])
+def test_stores_past_the_caches_leave_the_same_bits(n, size, co, out):
+    """Pixels on 64-byte blocks are written through the L2, up to 64 MB of them, and streamed beyond; 16 bytes behind a block
+    they are kept.  Sampled pixels against the oracle, all of them against each other."""
+    dtype = ft.FT_F16
+    g = np.random.default_rng([n, size, co])
+    X = si.normal_bits(g, (n, size, size, 64), 1.0, dtype)
+    Wt = si.normal_bits(g, (3, 3, 64, co), 0.04, dtype)
+    op = ft.ft_op_register(ft.ft_op_desc(kind=ft.FT_OP_CONV2D, dtype=dtype, c_in=64, c_out=co, r=3, s=3, stride=1, pad=1, m_lo=1, m_hi=1 << 22, out_dtype=out))
+    plan = ft.ft_plan_create(op, ft.ft_ukernels_derive(op), ft.ft_shape(img_n=n, img_h=size, img_w=size))
+    M, per16 = n * size * size, 4 if out == ft.FT_OUT_F32 else 8
+    assert (M * co * 16 // per16 > 64 << 20) == (size > 100) and co * 16 // per16 % 64 == 0, "another side of the line than the test is about"
+    dX, dW = dev_bits(X), dev_bits(Wt)
+    got = []
+    for off in (0, per16):
+        Y = torch.full((M * co + 2 * GUARD,), 7.0, dtype=torch.float32 if out == ft.FT_OUT_F32 else torch.float16, device="cuda")
+        body = Y[GUARD + off:GUARD + off + M * co]
+        body.fill_(float("nan"))
+        assert body.data_ptr() % 64 == (16 if off else 0) and ft.ft_plan_launch_form(plan, dX.data_ptr(), dW.data_ptr(), body.data_ptr()).form == ft.FT_FORM_PATCHES
+        ft.ft_launch(plan, dX.data_ptr(), dW.data_ptr(), body.data_ptr(), stream())
+        torch.cuda.synchronize()
+        assert bool((Y[:GUARD + off] == 7.0).all()) and bool((Y[GUARD + off + M * co:] == 7.0).all()), "write outside Y"
+        got.append(body.view(M, co))
+    assert torch.equal(got[0], got[1])
+    pix = np.array(sorted({0, M - 1} | {int(x) for x in g.integers(0, M, 100)}))
+    ref, refabs = oc.conv2d_nhwc(X, Wt, dtype, pad=1, pixels=pix, want_abs=True)
+    check_epilogue(got[0][torch.from_numpy(pix).cuda()].double().cpu().numpy(), ref.reshape(len(pix), co), refabs.reshape(len(pix), co), None,
+                   None if out == ft.FT_OUT_F32 else dtype, f"{n}x{size}x{size} -> {co}")
