@@ -12,6 +12,7 @@ struct BigArgs {
     void *C;
     const float *bias;
     uint32_t out16;                      // C in the inputs' 16-bit type
+    uint32_t through;                    // rows of an fp32 C lie on 64-byte blocks: they are streamed and written through the L2
     uint32_t M, N, K;
     uint32_t rows, cols;                 // grid of 256-row blocks; the strip of at most 128 rows below it is not counted
     uint32_t group;                      // rows of blocks walked together

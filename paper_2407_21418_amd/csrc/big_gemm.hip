@@ -243,18 +243,27 @@ struct BigBody {
             }
         }
         if (!g.out16) {
-            // (plain stores: streamed 64-byte segments measured 3 % slower over the whole launch)
-            float *const C = static_cast<float *>(g.C);
+            // Rows on 64-byte blocks (an instruction fills 16 of them) are streamed and written through the L2 (sc1 nt): nothing is
+            // left to write back when the launch ends, or beside the next block's copies.  Kept / this, bf16, us: 4096^3 103.5 /
+            // 99.9, 2500 x 4096 x 4096 76.2 / 72.9, 600 x 11008 x 4096 62.0 / 55.8, 3000 x 11008 x 4096 236.6 / 231.8; streamed but not written
+            // through 105.4, 75.7, 57.8, 241.  (16-bit results are kept: 8192 x 11008 x 4096 517 / 519, written through alone 529.)
+            const uint32_t row_bytes = g.N * 4u, lane_row = (lane & 15u) * row_bytes, r0 = m0 + wm * WM;
+            if (r0 < g.M && col0 < g.N) {
+                const uint32_t rows = g.M - r0 < (uint32_t)WM ? g.M - r0 : (uint32_t)WM, columns = g.N - col0;
+                const __amdgpu_buffer_rsrc_t rc =
+                    __builtin_amdgcn_make_buffer_rsrc(static_cast<float *>(g.C) + ((uint64_t)r0 * g.N + col0), 0, (int)((rows - 1u) * row_bytes + columns * 4u), 0x00020000);
+                auto store = [&](auto policy) {
 #pragma unroll
-            for (int i = 0; i < BM; ++i) {
-                const uint32_t r = row0 + i * 16u;
-                if (r < g.M) {
+                    for (int i = 0; i < BM; ++i)
 #pragma unroll
-                    for (int j = 0; j < BN; ++j) {
-                        const uint32_t c = col0 + j * 16u + q4 * 4u;
-                        if (c < g.N) *reinterpret_cast<f32x4 *>(C + (uint64_t)r * g.N + c) = acc[i][j];
-                    }
-                }
+                        for (int j = 0; j < BN; ++j) {
+                            const uint32_t c = j * 16u + q4 * 4u;     // (rows go into the lane's offset, see grid_gemm.hip)
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(big_u32x4, acc[i][j]), rc, (int)(c < columns ? lane_row + i * 16u * row_bytes + c * 4u : 0x80000000u),
+                                                                   0, decltype(policy)::value);
+                        }
+                };
+                if (g.through) store(std::integral_constant<int, 18>{});
+                else store(std::integral_constant<int, 0>{});
             }
         } else {
             // two neighbouring blocks: after the swap of odd and even 16-lane rows a lane holds 8 columns of one of them

@@ -361,6 +361,7 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         std::memset(&r, 0, sizeof(r));
         r.A = a.A; r.B = a.B; r.C = C; r.bias = bias;
         r.out16 = out16;
+        r.through = reinterpret_cast<uintptr_t>(C) % 64 == 0 && a.N % 16 == 0;
         r.M = a.M; r.N = a.N; r.K = a.K;
         r.rows = plan->big_rows; r.cols = plan->big_cols; r.group = 4;
         r.n_full = plan->big_full; r.n_half = plan->big_half;
