@@ -7,6 +7,11 @@ there is no fallback path.
 import ctypes as C
 import os
 
+try:
+    from . import _pycalls      # ft_plan_cached, ft_launch and ft_launch_epilogue without ctypes (csrc/pycalls.cpp)
+except ImportError:             # not built yet, or for another interpreter: the functions below do the same
+    _pycalls = None
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FTUNER_LIB names another build of the same library (e.g. the development variant with timestamps)
 LIB_PATH = os.environ.get("FTUNER_LIB") or os.path.join(_HERE, "libftuner.so")
@@ -28,10 +33,8 @@ u32, u64, u16 = C.c_uint32, C.c_uint64, C.c_uint16
 
 class _S(C.Structure):
     def __init__(self, **kw):
-        super().__init__()
         self.struct_size = C.sizeof(self)
-        for k, v in kw.items():
-            setattr(self, k, v)
+        super().__init__(**kw)
 
     def as_dict(self):
         out = {}
@@ -150,6 +153,8 @@ def lib():
         for name, (res, args) in SYMBOLS.items():
             fn = getattr(l, name)
             fn.restype, fn.argtypes = res, args
+        if _pycalls is not None:
+            _pycalls.bind(*(C.cast(fn, _P).value for fn in (l.ft_plan_cached, l.ft_launch, l.ft_launch_epilogue)))
         _lib = l
     return _lib
 
@@ -355,3 +360,10 @@ def ft_launch_timed(p: Plan, A, B, Cs, stream: int, iters: int, graph: bool = Fa
     _check(fn(p.ptr, arr(A), arr(B), arr(Cs), n, stream, iters, C.byref(ms)),
            "ft_launch_timed_graph" if graph else "ft_launch_timed")
     return ms.value
+
+
+# A serving loop makes these three for every Matmul: the native ones read the usual arguments themselves and hand every other call to
+# the functions above.
+if _pycalls is not None:
+    _pycalls.slow(_check, ft_shape, CachedPlan, ft_plan_cached, ft_launch, ft_launch_epilogue)
+    ft_plan_cached, ft_launch, ft_launch_epilogue = _pycalls.ft_plan_cached, _pycalls.ft_launch, _pycalls.ft_launch_epilogue

@@ -7,6 +7,7 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -188,6 +189,11 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
         use = _resource_usage(obj + ".log") if trace and os.path.exists(obj + ".log") else check_scratch(obj)   # (development variants are not held to it)
         if use and (verbose or remarks):
             print(f"  {os.path.basename(obj)}: {use}", flush=True)
+    if not trace:                             # the calls of a serving loop as CPython functions (host code, no HIP)
+        src, so = os.path.join(CSRC, "pycalls.cpp"), os.path.join(HERE, "_pycalls.so")
+        if not incremental or _stale(so, [src, os.path.join(INC, "ftuner.h")]):
+            _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INC, "-I", sysconfig.get_paths()["include"], src, "-o", so],
+                 os.path.join(OUT, "pycalls.log"))
     link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + [o for o, _ in steps]
     _run(link, os.path.join(OUT, "link.log"))
     if verbose:
