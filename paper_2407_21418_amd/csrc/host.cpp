@@ -644,9 +644,13 @@ void big_schedule(ft_plan *pl) {
 //     compares bit by bit with table order, would be faster, 12.4 / 11.6 (11.5 / 10.5));
 //   - fewer tiles than a third of the CUs, where little but latency is left (64 x 768 x 768 3.8 / 4.0 (3.5 / 3.3), 85 rows 4.1 / 4.0
 //     (3.6 / 3.4));
-//   - 32 k-tiles or more.  The grid would be the faster form of most of these (403 x 4096 x 4096 35.8 / 28.5 (28.4 / 20.6), 643 x 768 x 3072
-//     13.0 / 10.3, 98 x 11008 x 4096 57.3 / 31.0; not 648 x 11008 x 4096 83.8 / 89.6): tests/test_launch_forms.py holds 403 x 4096 x 4096 to the
-//     tiles and 403 x 11008 x 4096 to the blocks.
+//   - 32 k-tiles or more where the program splits them over workgroups or the blocks are taken: tests/test_launch_forms.py and
+//     tests/test_gpu_grid.py hold 403 x 4096 x 4096 and 429 x 3072 x 2048 to the tiles (35.8 / 28.5 (28.4 / 20.6) for the first) and 403 x 11008 x 4096
+//     to the blocks.  The others (230 launches, 1 to 4096 rows, 512 to 11008 columns, 2048 to 8192 products) take 0.81 (0.82) of the time:
+//     98 x 11008 x 4096 52.7 / 24.5, 1000 x 4096 x 4096 50.3 / 35.3 (48.4 / 32.9), 500 x 768 x 3072 10.9 / 8.9, 300 rows 9.1 / 8.0; of them
+//     nine longer by 2 to 12 % from HBM or in the caches, all of split-k programs (200 x 1024 x 4096 10.6 / 11.9, 180 rows of 3072 products 9.0 / 8.1;
+//     280 x 1536 x 4096 15.8 / 13.8 (12.8 / 13.4)).  Two teams on tiles that cover C exactly and are larger than the grid's stay: a test
+//     compares 1600 x 768 x 3072 bit by bit with table order.
 struct GridCost {
     double first, more, step, step_more, wide, wide_more;
 };
@@ -697,7 +701,11 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
     if (b.gk == 1 && tiles * 6 < P) return;
     if (split_k && program <= P && (b.gk < 4 ? K > 16 * 64 && K <= 32 * 64 && pl->st.k_parts == 1 && more_reads >= 2 : K >= 64 * 64 && pl->st.k_parts > 1)) return;
     if (wide) {
-        if (K >= 32 * 64) return;
+        if (K >= 32 * 64) {
+            if (pl->st.k_parts > 1 || pl->big) return;
+            const uint32_t tm = pl->slot_tm[0], tn = pl->slot_tn[0];
+            if (pl->two_teams && pl->st.n_ukernels == 1 && M % tm == 0 && N % tn == 0 && tm * tn > b.tm * b.tn) return;
+        }
         if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
         if (tiles * 3 < P) return;
     } else if (K <= 16 * 64 && b.tm * b.tn >= 128 * 192 && tiles * 4 < 3 * P && pl->slot_tm[0] * pl->slot_tn[0] >= 128 * 128) return;

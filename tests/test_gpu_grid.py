@@ -124,6 +124,26 @@ def test_fp32_results_are_no_further_from_exact_than_the_tiles(M, N, K, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [ft.FT_F16, ft.FT_BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(500, 768, 3072), (1100, 768, 3072), (250, 1032, 2048), (700, 1024, 2112), (98, 2048, 4096), (177, 3000, 2048)])
+def test_fp32_results_with_a_long_reduce_axis(M, N, K, dtype):
+    """From 32 k-tiles on, programs that do not split them over workgroups are launched in the grid: split-k tiles, two teams and
+    single grids, every output within the bounds of the tiles and the whole no further from exact than theirs."""
+    from gpu_util import check_epilogue, run_at
+    test_fp32_results_are_no_further_from_exact_than_the_tiles(M, N, K, dtype)
+    g = np.random.default_rng([M, N, K, dtype, 4])
+    bias = g.standard_normal(N).astype(np.float32)
+    _, _, plan = plan_of(M, N, K, dtype, True, out=F32)
+    A, B = si.normal_bits(g, (M, K), 1.0, dtype), si.normal_bits(g, (K, N), 0.02, dtype)
+    rows = np.array(sorted({0, 15, 16, M // 2, M - 1}))
+    ref, refabs = oc.matmul(A, B, dtype, rows=rows, want_abs=True)
+    for off_c in (0, 4):
+        got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, bias, None, off_a=8, off_b=24, off_c=off_c).reshape(M, N)
+        assert np.isfinite(got).all(), "uncovered outputs"
+        check_epilogue(got[rows], oe.add_bias(ref, bias), refabs, bias, None, f"{M}x{N}x{K}")
+
+
+@pytest.mark.gpu
 def test_grid_launches_in_a_graph():
     """Captured launches on rotating operands, replayed with eager launches in between, give the eager bits."""
     from gpu_util import dev_bits, stream
