@@ -5,7 +5,7 @@
 // workgroup keeps the filter taps of 64 output channels in LDS (72 KB) and walks over tiles of up to 256 output pixels: a
 // tile's patch of the image is fetched once, halo and zero padding included, and every tap reads its rows of A from the
 // patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 to 65 us with fp32 results, 88 to 62 with 16-bit ones; 8 x 56 x 56: 10.8
-// to 8.2; 8 x 28 x 28: 6.6 to 4.9.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
+// to 7.6; 8 x 28 x 28: 6.6 to 4.5.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
 // 2.2 GHz, and 1.5 us of copies, waits and barrier (counters: matrix cores busy for 54 % of the cycles on 224 x 224); the
 // smallest launches are bound by their latencies: taps and patch 1.5 us, nine taps 1.3 (27 % on 56 x 56).
 //   - One workgroup of eight waves per CU, the patch of the next tile arriving while this one is computed: no wait and no
@@ -24,6 +24,9 @@
 //     224 x 224, tiles 16 wide; 23 % of the LDS cycles on 56 x 56, where 16 pixels of a tile 28 wide lie in two of its rows), and
 //     a tap's rows differ from those of the tap above by a constant.
 //   - Operands are handed to the MFMAs the other way round, so that a lane holds four neighbouring channels of one pixel.
+//   - Before its first copies a lane finds six pixels' rows and columns in the patch, and four of its outputs': divisions by reciprocals from
+//     the host (conv_div), as two waves to a SIMD need half a microsecond for the general ones: 8 x 28 x 28 4.9 -> 4.5 us, 8 x 37 x 37 6.0
+//     -> 5.4, 8 x 56 x 56 8.2 -> 7.6, larger ones 0.3 less.
 // The host picks the tile, and the layers that are left to the gather (see conv_schedule).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -118,9 +121,9 @@ struct ConvBody {
         }
     }
     __device__ static __forceinline__ Tile tile_at(const ConvArgs &g, uint32_t t) {
-        const uint32_t tx = t % g.tiles_x, u = t / g.tiles_x, ty = u % g.tiles_y;
-        return Tile{(uint32_t)__builtin_amdgcn_readfirstlane(u / g.tiles_y), (uint32_t)__builtin_amdgcn_readfirstlane(ty * g.th),
-                    (uint32_t)__builtin_amdgcn_readfirstlane(tx * g.tw)};
+        const uint32_t u = g.per_x ? grid_div(t, g.per_x) : t / g.tiles_x, img = g.per_x ? grid_div(u, g.per_y) : u / g.tiles_y;
+        return Tile{(uint32_t)__builtin_amdgcn_readfirstlane(img), (uint32_t)__builtin_amdgcn_readfirstlane((u - img * g.tiles_y) * g.th),
+                    (uint32_t)__builtin_amdgcn_readfirstlane((t - u * g.tiles_x) * g.tw)};
     }
 
     __device__ static __forceinline__ void run(const ConvArgs &g, uint32_t first, uint32_t n0, unsigned char *smem) {
@@ -132,7 +135,7 @@ struct ConvBody {
         uint32_t px_yx[kConvCopies], px_off[kConvCopies];             // (LDS chunk of a pixel's channels: chunk ^ (x & 7))
 #pragma unroll
         for (uint32_t i = 0; i < kConvCopies; ++i) {
-            const uint32_t row = (i * 8u + wave) * 8u + lane / 8u, y = row / pw, x = row % pw;
+            const uint32_t row = (i * 8u + wave) * 8u + lane / 8u, y = conv_div(row, g.per_pw), x = row - y * pw;
             px_yx[i] = (row < patch_rows ? y : 0xffffu) << 16 | x;  // (past the patch: outside every image)
             px_off[i] = (y * g.W + x) * 128u + ((lane ^ x) & 7u) * 16u;
         }
@@ -167,7 +170,7 @@ struct ConvBody {
         uint32_t a0[3][BM], out_yx[BM], out_off[BM];
 #pragma unroll
         for (int i = 0; i < BM; ++i) {
-            const uint32_t px = wm * WM + i * 16u + j16, yy = px / g.tw, x = px - yy * g.tw, y = yy < g.th ? yy : 0u;
+            const uint32_t px = wm * WM + i * 16u + j16, yy = conv_div(px, g.per_tw), x = px - yy * g.tw, y = yy < g.th ? yy : 0u;
 #pragma unroll
             for (uint32_t s = 0; s < 3u; ++s) {
                 const uint32_t col = x + s, row = y * pw + col;
@@ -284,9 +287,12 @@ __global__ __launch_bounds__(512, 1) void ft_conv_patch(ConvArgs g) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     // workgroup b runs on XCD b % num_xcds: an XCD takes one contiguous run of the walkers, and with it neighbouring tiles
     // (whose patches overlap) at a time
-    const uint32_t nx = g.num_xcds, b = blockIdx.x, n = g.walkers * g.cols, x = b % nx, q = n / nx, r = n % nx;
-    const uint32_t u = x * q + (x < r ? x : r) + b / nx;
-    ConvBody<DT, OUT16, BM, KEEP>::run(g, __builtin_amdgcn_readfirstlane(u / g.cols), __builtin_amdgcn_readfirstlane(u % g.cols * 64u), smem);
+    const uint32_t nx = g.num_xcds, b = blockIdx.x, n = g.walkers * g.cols;
+    uint32_t x, u;
+    if (nx == 8) { x = b & 7u; u = x * (n >> 3) + (x < (n & 7u) ? x : n & 7u) + (b >> 3); }
+    else { x = b % nx; u = x * (n / nx) + (x < n % nx ? x : n % nx) + b / nx; }
+    const uint32_t walker = grid_div(u, g.per_cols);
+    ConvBody<DT, OUT16, BM, KEEP>::run(g, __builtin_amdgcn_readfirstlane(walker), __builtin_amdgcn_readfirstlane((u - walker * g.cols) * 64u), smem);
 }
 
 }  // namespace ftk

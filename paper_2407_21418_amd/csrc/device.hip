@@ -349,6 +349,9 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.th = plan->conv_th; r.tw = plan->conv_tw;
         r.tiles_y = g.tiles_y; r.tiles_x = g.tiles_x; r.tiles = g.tiles;
         r.cols = g.cols; r.walkers = g.walkers;
+        r.per_pw = ftk::conv_per(r.tw + 2u); r.per_tw = ftk::conv_per(r.tw);
+        r.per_cols = ftk::grid_per(r.cols);
+        r.per_x = g.tiles <= ftk::kGridTilesMax ? ftk::grid_per(g.tiles_x) : 0u; r.per_y = ftk::grid_per(g.tiles_y);
         r.num_xcds = plan->num_xcds;
         const uint64_t pixel_bytes = (uint64_t)a.N * (out16 ? 2 : 4);
         const int keep = reinterpret_cast<uintptr_t>(C) % 64 || pixel_bytes % 64 ? 2 : a.M * pixel_bytes <= (64u << 20) ? 1 : 0;     // (a quarter of the last-level cache)

@@ -37,11 +37,8 @@ struct GridTile {
 constexpr uint32_t kGridTilesMax = 32767;
 inline GridOrder grid_order(uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx) {
     const uint32_t n = rows * cols, low = rows % group;
-    auto per = [](uint32_t d) -> uint32_t { return d ? (0x80000000u + d - 1u) / d : 0u; };
-    return GridOrder{n / nx | (n % nx) << 16 | nx << 24, group * cols | group << 16, rows / group | low << 16, per(group * cols), per(group), per(low)};
+    return GridOrder{n / nx | (n % nx) << 16 | nx << 24, group * cols | group << 16, rows / group | low << 16, grid_per(group * cols), grid_per(group), grid_per(low)};
 }
-// x / d, per = ceil(2^31 / d): exact for x, d < 2^15 (x * (per * d - 2^31) < 2^31)
-FT_HD uint32_t grid_div(uint32_t x, uint32_t per) { return (uint32_t)((uint64_t)(x * 2u) * per >> 32); }
 FT_HD GridTile grid_tile(const GridOrder &o, uint32_t b) {
     const uint32_t nx = o.share >> 24, more = o.share >> 16 & 255u;
     uint32_t x, q;

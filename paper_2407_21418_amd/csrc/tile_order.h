@@ -116,6 +116,10 @@ FT_HD TileOfWorkgroup tile_of_workgroup(const LaunchOrder &o, uint32_t b) {
     return o.nx == 8 ? tile_of_workgroup_nx<8>(o, b) : tile_of_workgroup_nx<0>(o, b);
 }
 
+// x / d, per = ceil(2^31 / d): exact for x, d < 2^15 (x * (per * d - 2^31) < 2^31)
+inline uint32_t grid_per(uint32_t d) { return d ? (0x80000000u + d - 1u) / d : 0u; }
+FT_HD uint32_t grid_div(uint32_t x, uint32_t per) { return (uint32_t)((uint64_t)(x * 2u) * per >> 32); }
+
 // Plans with more than two uKernel shapes (second-axis strips) are walked in table order, dealt to
 // the XCDs in chunks of kTableChunk consecutive descriptors: neighbouring tiles of a row band stay
 // on one XCD (the halves of a cache line of C that two of them share meet in one L2) and every XCD
