@@ -22,13 +22,9 @@ struct ConvArgs {
     uint32_t tiles_y, tiles_x, tiles;    // tiles of an image, tiles of all images
     uint32_t cols;                       // 64-channel blocks of N
     uint32_t walkers, num_xcds;          // workgroups = walkers * cols; walker i takes tiles i, i + walkers, ...
-    uint32_t per_pw, per_tw;             // ceil(2^20 / (tw + 2)), ceil(2^20 / tw): see conv_div
+    uint32_t per_pw, per_tw;             // ceil(2^20 / (tw + 2)), ceil(2^20 / tw): see small_div
     uint32_t per_cols, per_x, per_y;     // ceil(2^31 / cols, tiles_x, tiles_y): see grid_div; per_x is 0 for more tiles than that divides
 };
-
-// x / d for x < 512 and d <= 512, per = ceil(2^20 / d): exact, since x * (per * d - 2^20) < 2^20; a multiplication of 24 bits
-FT_CONV_HD uint32_t conv_per(uint32_t d) { return ((1u << 20) + d - 1u) / d; }
-FT_CONV_HD uint32_t conv_div(uint32_t x, uint32_t per) { return ((x & 0xffffffu) * (per & 0xffffffu)) >> 20; }
 
 // pixels of the patch a th x tw tile of outputs needs
 FT_CONV_HD uint32_t conv_patch_rows(uint32_t th, uint32_t tw) { return (th + 2u) * (tw + 2u); }

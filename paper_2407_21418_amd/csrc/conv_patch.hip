@@ -25,7 +25,7 @@
 //     a tap's rows differ from those of the tap above by a constant.
 //   - Operands are handed to the MFMAs the other way round, so that a lane holds four neighbouring channels of one pixel.
 //   - Before its first copies a lane finds six pixels' rows and columns in the patch, and four of its outputs': divisions by reciprocals from
-//     the host (conv_div), as two waves to a SIMD need half a microsecond for the general ones: 8 x 28 x 28 4.9 -> 4.5 us, 8 x 37 x 37 6.0
+//     the host (small_div), as two waves to a SIMD need half a microsecond for the general ones: 8 x 28 x 28 4.9 -> 4.5 us, 8 x 37 x 37 6.0
 //     -> 5.4, 8 x 56 x 56 8.2 -> 7.6, larger ones 0.3 less.
 // The host picks the tile, and the layers that are left to the gather (see conv_schedule).
 #include <hip/hip_runtime.h>
@@ -135,7 +135,7 @@ struct ConvBody {
         uint32_t px_yx[kConvCopies], px_off[kConvCopies];             // (LDS chunk of a pixel's channels: chunk ^ (x & 7))
 #pragma unroll
         for (uint32_t i = 0; i < kConvCopies; ++i) {
-            const uint32_t row = (i * 8u + wave) * 8u + lane / 8u, y = conv_div(row, g.per_pw), x = row - y * pw;
+            const uint32_t row = (i * 8u + wave) * 8u + lane / 8u, y = small_div(row, g.per_pw), x = row - y * pw;
             px_yx[i] = (row < patch_rows ? y : 0xffffu) << 16 | x;  // (past the patch: outside every image)
             px_off[i] = (y * g.W + x) * 128u + ((lane ^ x) & 7u) * 16u;
         }
@@ -170,7 +170,7 @@ struct ConvBody {
         uint32_t a0[3][BM], out_yx[BM], out_off[BM];
 #pragma unroll
         for (int i = 0; i < BM; ++i) {
-            const uint32_t px = wm * WM + i * 16u + j16, yy = conv_div(px, g.per_tw), x = px - yy * g.tw, y = yy < g.th ? yy : 0u;
+            const uint32_t px = wm * WM + i * 16u + j16, yy = small_div(px, g.per_tw), x = px - yy * g.tw, y = yy < g.th ? yy : 0u;
 #pragma unroll
             for (uint32_t s = 0; s < 3u; ++s) {
                 const uint32_t col = x + s, row = y * pw + col;

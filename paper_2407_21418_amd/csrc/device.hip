@@ -314,6 +314,7 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.rb_log2 = form.run_rb_log2;
         r.runs = form.run_shares;
         r.n_runs = plan->st.batch * form.run_shares;
+        r.per_pitch = ftk::small_per(ftk::run_kn_pitch(a.N));
         const int rc = ft_launch_runs(&r, (int)plan->op.dtype, nk, ftk::run_lds(a.N, r.rb_log2, out16 ? 2 : 4, nk), hip_stream);
         if (rc != 0) return hip_fail((hipError_t)rc);
         return FT_OK;
@@ -349,7 +350,7 @@ static ft_status launch_common(const ft_plan *plan, const void *A, const void *B
         r.th = plan->conv_th; r.tw = plan->conv_tw;
         r.tiles_y = g.tiles_y; r.tiles_x = g.tiles_x; r.tiles = g.tiles;
         r.cols = g.cols; r.walkers = g.walkers;
-        r.per_pw = ftk::conv_per(r.tw + 2u); r.per_tw = ftk::conv_per(r.tw);
+        r.per_pw = ftk::small_per(r.tw + 2u); r.per_tw = ftk::small_per(r.tw);
         r.per_cols = ftk::grid_per(r.cols);
         r.per_x = g.tiles <= ftk::kGridTilesMax ? ftk::grid_per(g.tiles_x) : 0u; r.per_y = ftk::grid_per(g.tiles_y);
         r.num_xcds = plan->num_xcds;

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "tile_order.h"
+
 #if defined(__HIP__)
 #define FT_RUN_HD __attribute__((host)) __attribute__((device)) inline
 #else
@@ -21,6 +23,7 @@ struct RunArgs {
     uint32_t M, N, K;
     uint32_t runs, rb_log2;              // shares per batch entry; rows of a share = 32 << rb_log2
     uint32_t n_runs;                     // shares of the launch
+    uint32_t per_pitch;                  // ceil(2^20 / run_kn_pitch(N)): see small_div
     uint32_t num_xcds;
 };
 

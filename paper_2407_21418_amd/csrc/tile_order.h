@@ -116,6 +116,10 @@ FT_HD TileOfWorkgroup tile_of_workgroup(const LaunchOrder &o, uint32_t b) {
     return o.nx == 8 ? tile_of_workgroup_nx<8>(o, b) : tile_of_workgroup_nx<0>(o, b);
 }
 
+// x / d in a multiplication of 24 bits, per = ceil(2^20 / d): exact for x < 512 and d <= 512, and for x < 4096 and 4 <= d <= 64
+// (x * (per * d - 2^20) < 2^20, x * per < 2^32)
+FT_HD uint32_t small_per(uint32_t d) { return ((1u << 20) + d - 1u) / d; }
+FT_HD uint32_t small_div(uint32_t x, uint32_t per) { return ((x & 0xffffffu) * (per & 0xffffffu)) >> 20; }
 // x / d, per = ceil(2^31 / d): exact for x, d < 2^15 (x * (per * d - 2^31) < 2^31)
 inline uint32_t grid_per(uint32_t d) { return d ? (0x80000000u + d - 1u) / d : 0u; }
 FT_HD uint32_t grid_div(uint32_t x, uint32_t per) { return (uint32_t)((uint64_t)(x * 2u) * per >> 32); }

@@ -5,9 +5,13 @@ import random
 import host_shim
 
 
-def test_conv_div():
-    div = host_shim.load().shim_conv_div
+def test_small_div():
+    div = host_shim.load().shim_small_div
     assert all(div(x, d) == x // d for d in range(1, 513) for x in range(512))
+    assert all(div(x, d) == x // d for d in range(4, 65) for x in range(4096))
+    # whole rows divide chunks of 64 rows by a pitch, convolutions pixels of 384 by the width of a patch
+    pitches = [host_shim.load().shim_run_pitch(n) for n in range(8, 321)]
+    assert 4 <= min(pitches) and max(pitches) <= 64 and 64 * max(pitches) <= 4096
 
 
 def test_grid_div():
