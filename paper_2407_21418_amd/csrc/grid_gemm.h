@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "tile_order.h"          // FT_HD
 
 namespace ftk {
@@ -51,6 +53,23 @@ FT_HD GridTile grid_tile(const GridOrder &o, uint32_t b) {
     return GridTile{i * (o.band >> 16) + w - col * (low ? o.last >> 16 : o.band >> 16), col};
 }
 FT_HD GridTile grid_tile(uint32_t b, uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx) { return grid_tile(grid_order(rows, cols, group, nx), b); }
+
+// Rows of A and columns of B that the XCD with the most of them reads in that walk.  A run begins in the middle of one band and ends
+// in another: rows of different bands are different ones, columns meet again.
+inline uint32_t grid_reads(uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx, uint32_t tm, uint32_t tn) {
+    const uint32_t n = rows * cols, band = group * cols, share = n / nx, more = n % nx;
+    uint32_t most = 0;
+    for (uint32_t x = 0, s = 0; x < nx && s < n; ++x) {
+        const uint32_t e = s + share + (x < more ? 1 : 0), i = s / band, j = (e - 1) / band;          // its first tile, the one after its last, their bands
+        const uint32_t hi = std::min(group, rows - i * group), hj = std::min(group, rows - j * group);
+        const uint32_t si = s - i * band, ej = e - j * band;
+        const uint32_t r = i == j ? std::min(hi, e - s) : std::min(hi, hi * cols - si) + (j - i - 1) * group + std::min(hj, ej);
+        const uint32_t c = i == j ? (ej - 1) / hi - si / hi + 1 : j - i > 1 ? cols : std::min(cols, cols - si / hi + (ej - 1) / hj + 1);
+        most = std::max(most, r * tm + c * tn);
+        s = e;
+    }
+    return most;
+}
 
 struct GridArgs {
     const uint16_t *A;
