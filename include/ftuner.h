@@ -363,7 +363,10 @@ void ft_plan_destroy(ft_plan *plan);
  *   FT_FORM_PATCHES  image patches (3 x 3 Conv2d of 64 input channels; C 16-byte aligned)
  *   FT_FORM_GRID     one grid of equal tiles (Matmuls of the middle range; A, B, C 16-byte aligned)
  * Forced programs, pad baselines, grouped plans and FT_PLAN_TABLE_ORDER always launch tiles.  Every form keeps
- * fp32 sums; the order of a sum's terms, and with it the last bits of a result, depends on the form. */
+ * fp32 sums; the order of a sum's terms, and with it the last bits of a result, depends on the form and, in
+ * FT_FORM_GRID and FT_FORM_TILES, on the place of the result in C.  Launches of one plan in one form on the same
+ * values give the same bits in every place of C, wherever operands and C lie and on whatever stream.  Equal rows of A
+ * in different places of one launch, and the same rows in launches of another M, may differ in the last bits. */
 enum { FT_FORM_TILES = 0, FT_FORM_ROWS = 1, FT_FORM_BLOCKS = 2, FT_FORM_PATCHES = 3, FT_FORM_GRID = 4 };
 typedef struct ft_launch_form {
     uint32_t struct_size;

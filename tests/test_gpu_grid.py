@@ -144,6 +144,35 @@ def test_fp32_results_with_a_long_reduce_axis(M, N, K, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,tm,out", [(201, 768, 3072, 32, S16), (688, 768, 3072, 48, S16), (688, 3072, 768, 96, S16), (700, 4096, 4096, 96, S16), (272, 768, 3072, 32, F32),
+                                          (1009, 2304, 768, 96, F32)])
+def test_what_of_the_last_bits_depends_on(M, N, K, tm, out):
+    """Equal rows of A: launches on other streams, addresses and buffers repeat the bits of every place; within a row of tiles all rows are
+    equal; between rows of tiles, which add up the k-tiles in orders of their own, each sum of K terms is within K ulp of sum |a||b| of
+    the exact one (2^-24 a rounding; half an ulp of the result more where it is rounded to 16 bits)."""
+    from gpu_util import run_at
+    dtype = M % 2
+    g = np.random.default_rng([M, N, K, 5])
+    _, _, plan = plan_of(M, N, K, dtype, out=out)
+    out16 = dtype if out == S16 else None
+    f = ft.ft_plan_launch_form(plan)
+    assert f.form == ft.FT_FORM_GRID and f.workgroups % -(-M // tm) == 0, "another body than the test is about"
+    row = si.normal_bits(g, (1, K), 1.0, dtype)
+    A, B = np.repeat(row, M, 0), si.normal_bits(g, (K, N), 0.02, dtype)
+    got = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, None, out16, off_a=8, off_b=8, off_c=8).reshape(M, N)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        again = run_at(plan, A, B, M * N, dtype, ft.FT_FORM_GRID, None, out16, off_a=24, off_b=64, off_c=32 if out == S16 else 16).reshape(M, N)
+    assert np.array_equal(got, again)
+    for r in range(0, M, tm):
+        assert (got[r:r + tm] == got[r]).all(), f"rows {r} to {r + tm}"
+    ref, refabs = oc.matmul(row, B, dtype, want_abs=True)
+    bound = refabs * K * 2.0 ** -24
+    if out16 is not None:
+        bound = bound + (np.abs(ref) + bound) * (2.0 ** -11 if dtype == ft.FT_F16 else 2.0 ** -8) + 2.0 ** -25
+    assert (np.abs(got - ref) <= bound).all()
+
+
+@pytest.mark.gpu
 def test_grid_launches_in_a_graph():
     """Captured launches on rotating operands, replayed with eager launches in between, give the eager bits."""
     from gpu_util import dev_bits, stream
