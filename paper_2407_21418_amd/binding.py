@@ -2,14 +2,19 @@
 
 Only marshals arguments.  The library must have been built (python -m
 paper_2407_21418_amd.build, or __graft_entry__.build()); a missing library is an error,
-there is no fallback path.
+nothing else computes in its place.  ft_plan_cached, ft_launch and ft_launch_epilogue are native
+functions (csrc/pycalls.cpp) where those were built for this interpreter, else they go through
+ctypes as all others do.
 """
 import ctypes as C
+import importlib
 import os
 
 try:
-    from . import _pycalls      # ft_plan_cached, ft_launch and ft_launch_epilogue without ctypes (csrc/pycalls.cpp)
-except ImportError:             # not built yet, or for another interpreter: the functions below do the same
+    _pycalls = importlib.import_module(__package__ + "._pycalls")
+except ModuleNotFoundError as e:        # not built, or for another interpreter; one that is there and does not load is an error
+    if e.name != __package__ + "._pycalls":
+        raise
     _pycalls = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))

@@ -5,6 +5,7 @@ library to paper_2407_21418_amd/libftuner.so.
 """
 import concurrent.futures as cf
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -14,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libftuner.so")
+PYCALLS = os.path.join(HERE, "_pycalls" + sysconfig.get_config_var("EXT_SUFFIX"))    # (another interpreter does not take it for its own)
 INC = os.path.join(os.path.dirname(HERE), "include")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -84,15 +86,40 @@ def check_scratch(obj):
     return use
 
 
-def _stale(obj, srcs):
-    if not os.path.exists(obj):
+def _stale(obj, srcs, cmd, log):
+    """Whether an object is missing, older than a source, or made by another command (its log begins with that)."""
+    if not os.path.exists(obj) or not os.path.exists(log):
         return True
+    with open(log) as f:
+        if f.readline().rstrip("\n") != " ".join(cmd):
+            return True
     t = os.path.getmtime(obj)
     return any(os.path.getmtime(s) > t for s in srcs)
 
 
+def build_pycalls(incremental=False, verbose=True):
+    """The calls of a serving loop as CPython functions (host code, no HIP).  False, and a word of it, where there is no g++ or no header
+    of this interpreter: the package then makes these calls through ctypes."""
+    plain = os.path.join(HERE, "_pycalls.so")                         # (any interpreter would load it)
+    if os.path.exists(plain):
+        os.remove(plain)
+    src, inc = os.path.join(CSRC, "pycalls.cpp"), sysconfig.get_paths()["include"]
+    lacks = [what for what, there in (("g++", shutil.which("g++")), ("Python.h", os.path.exists(os.path.join(inc, "Python.h")))) if not there]
+    if lacks:
+        if os.path.exists(PYCALLS):
+            os.remove(PYCALLS)                                        # (of sources that may have changed)
+        print("  %s not built, its calls go through ctypes: no %s" % (os.path.basename(PYCALLS), ", no ".join(lacks)), flush=True)
+        return False
+    cmd, log = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INC, "-I", inc, src, "-o", PYCALLS], os.path.join(OUT, "pycalls.log")
+    if not incremental or _stale(PYCALLS, [src, os.path.join(INC, "ftuner.h")], cmd, log):
+        dt = _run(cmd, log)
+        if verbose:
+            print(f"  built {os.path.basename(PYCALLS)} in {dt:.1f}s", flush=True)
+    return True
+
+
 def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False):
-    """incremental=True recompiles only objects older than the sources they include.
+    """incremental=True recompiles only objects older than the sources they include or made by another command.
     trace=True builds the development variant libftuner_trace.so (-DFT_TRACE: workgroups leave
     timestamps, see FT_MARK) from objects of its own; the product library is not touched."""
     global OUT, LIB, COMMON
@@ -178,7 +205,7 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
     todo = [(o, c) for o, c in steps if c is not None]
     if incremental:
         src_of = lambda cmd: cmd[cmd.index("-c") + 1]
-        todo = [(o, c) for o, c in todo if _stale(o, hdrs + [src_of(c)])]
+        todo = [(o, c) for o, c in todo if _stale(o, hdrs + [src_of(c)], c, o + ".log")]
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         futs = {ex.submit(_run, cmd, obj + ".log"): obj for obj, cmd in todo}
         for fut in cf.as_completed(futs):
@@ -189,11 +216,8 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
         use = _resource_usage(obj + ".log") if trace and os.path.exists(obj + ".log") else check_scratch(obj)   # (development variants are not held to it)
         if use and (verbose or remarks):
             print(f"  {os.path.basename(obj)}: {use}", flush=True)
-    if not trace:                             # the calls of a serving loop as CPython functions (host code, no HIP)
-        src, so = os.path.join(CSRC, "pycalls.cpp"), os.path.join(HERE, "_pycalls.so")
-        if not incremental or _stale(so, [src, os.path.join(INC, "ftuner.h")]):
-            _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INC, "-I", sysconfig.get_paths()["include"], src, "-o", so],
-                 os.path.join(OUT, "pycalls.log"))
+    if not trace:
+        build_pycalls(incremental, verbose)
     link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + [o for o, _ in steps]
     _run(link, os.path.join(OUT, "link.log"))
     if verbose:
