@@ -191,9 +191,9 @@ def build(verbose=True, remarks=True, jobs=None, incremental=False, trace=False)
         # them in the library (1.29 to 1.49 ms for one unchanged attention operator on an EPYC host). Aligned to a cache
         # line it stays at 1.29 ms in each layout tried; functions alone aligned, 1.53 ms.
         align = ["-falign-functions=64", "-falign-loops=64"] if src == "host.cpp" else []
-        # (the grid's kernels find their first arguments in registers: see ft_grid)
+        # (the grid's kernels find their first six arguments in registers, fourteen words: see ft_grid)
         if src == "grid_gemm.hip":
-            align = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
+            align = ["-mllvm", "-amdgpu-kernarg-preload-count=6"]
         steps.append((obj, [HIPCC] + COMMON + align + ["-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj]))
     jobs = jobs or min(8, len(steps))
     if trace:

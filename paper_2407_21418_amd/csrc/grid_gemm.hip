@@ -348,8 +348,9 @@ struct GridBody {
     }
 };
 
-// What a workgroup needs before its first copies comes first and not in a structure: the build asks for these thirteen words in
-// registers (amdgpu-kernarg-preload-count), which the command processor fills before the first wave starts.  With one structure
+// What a workgroup needs before its first copies comes first and not in a structure: the build asks for the first six arguments in
+// registers (amdgpu-kernarg-preload-count), which the command processor fills before the first wave starts.  They are fourteen words, as
+// many as there is room for: a longer list would leave its last ones in memory without a word.  With one structure
 // read from memory and the divisions of its general form a workgroup knew its tile 0.45 us after it began; now, with everything in
 // the last-level cache, 688 x 2304 x 768 6.26 -> 6.09 us, x 768 x 768 4.70 -> 4.52, x 3072 x 768 7.65 -> 7.41 (16-bit results).  The
 // same arguments read from memory: 6.33, 4.79, 7.68.  (In fours: the host spends 10 ns on every argument of a launch.)
