@@ -71,6 +71,30 @@ inline uint32_t grid_reads(uint32_t rows, uint32_t cols, uint32_t group, uint32_
     return most;
 }
 
+// Rows of tiles walked together: those with which a run of an XCD's length that begins at the top of a band touches the fewest rows of
+// A and columns of B, unless the XCD that reads the most reads a sixth less in higher bands, of equal ones the highest: a run that
+// goes from one band into the next has the columns of both, and one in a low last band most columns there are.  us, the first choice /
+// this: 7 rows of 16 tiles 220 x 512 x 2048 6.5 / 4.95, 9 of 24 272 x 768 x 3072 8.8 / 8.3, 18 of 12 560 x 768 x 3072 10.6 / 8.9, 8 of 24 688 x 3072 x
+// 768 7.7 / 7.6 and with fp32 results 8.6 / 8.5 (in the caches 8.5 / 8.4), 10 of 24 454 x 1536 x 2048 9.0 / 8.7, 20 of 12 2518 x 2304 x 768 14.3 / 14.05.
+// Lower bands are no choice, whatever they would save: each reads B again, and fewer rows of tiles fetch a window of it for one another (8 rows
+// of 24 in bands of 4 for 6, a third less to read, 688 x 3072 x 768 7.9, with fp32 results 8.8; bands of 2 for 6, 2976 x 768 x 768 8.7 / 9.0; the
+// exception seen is bands of 2 for 5, 29 rows of 8, 2691 x 512 x 3072 16.1 / 15.2).  On differences below a sixth the two are as often wrong
+// as right (11 rows of 16, 384 rows and columns for 448, 330 x 512 x 4096 9.35 / 10.9).
+inline uint32_t grid_band(uint32_t rows, uint32_t cols, uint32_t nx, uint32_t tm, uint32_t tn) {
+    const uint64_t run = ((uint64_t)rows * cols + nx - 1) / nx;
+    uint64_t least = ~0ull;
+    uint32_t first = 1;
+    for (uint32_t g = 1; g <= rows; ++g) {
+        const uint64_t columns = (run + g - 1) / g, passes = (columns + cols - 1) / cols;
+        const uint64_t touched = g * passes * tm + std::min<uint64_t>(columns, cols) * tn;
+        if (touched < least) { least = touched; first = g; }
+    }
+    uint32_t fewest = ~0u, height = 0;
+    for (uint32_t g = first + 1; g <= rows; ++g)
+        if (const uint32_t most = grid_reads(rows, cols, g, nx, tm, tn); most <= fewest) { fewest = most; height = g; }
+    return height && fewest * 6 < grid_reads(rows, cols, first, nx, tm, tn) * 5 ? height : first;
+}
+
 struct GridArgs {
     const uint16_t *A;
     const uint16_t *B;

@@ -708,27 +708,7 @@ void grid_schedule(ft_plan *pl, const ft_ukset &set) {
         if (K <= 16 * 64 && b.tm * b.tn >= 96 * 128 && program > P && pl->st.k_parts == 1) return;
         if (tiles * 3 < P) return;
     } else if (K <= 16 * 64 && b.tm * b.tn >= 128 * 192 && tiles * 4 < 3 * P && pl->slot_tm[0] * pl->slot_tn[0] >= 128 * 128) return;
-    // rows of tiles walked together: those with which a run of an XCD's length that begins at the top of a band touches the fewest rows of
-    // A and columns of B ...
-    const uint64_t run = ceil_div(tiles, pl->num_xcds);
-    uint64_t least = ~0ull;
-    for (uint32_t g = 1; g <= pl->grid_rows; ++g) {
-        const uint64_t columns = ceil_div(run, g), passes = ceil_div(columns, pl->grid_cols);
-        const uint64_t touched = g * passes * b.tm + std::min<uint64_t>(columns, pl->grid_cols) * b.tn;
-        if (touched < least) { least = touched; pl->grid_group = g; }
-    }
-    // ... unless the XCD that reads the most reads a sixth less in bands of another height: a run that goes from one band into the next has
-    // the columns of both, and one in a low last band most columns there are.  68 of 228 launches change (16 to 3000 rows, 512 to 11008
-    // columns, both result types) and take 0.93 (0.92 in the caches) of the time, 1.02 at most of what repeats: 7 rows of 16 tiles 220 x 512 x 2048
-    // 6.5 / 4.95 us (6.4 / 4.45), 9 of 24 272 x 768 x 3072 8.8 / 8.2, 13 of 16 403 x 1024 x 4096 13.4 / 10.05, 6 of 40 350 x 2560 x 5120 23.1 / 21.2
-    // (22.8 / 18.0), 18 of 12 1683 x 768 x 3072 14.1 / 13.2.  On smaller differences the two are as often wrong as right (the least of
-    // the busiest XCD everywhere: 11 rows of 16, 384 rows and columns for 448, 330 x 512 x 4096 9.35 / 10.9), and bands of one row, which
-    // read B again for each, are slower than they count (25 rows of 8, 1600 x 512 x 4096 13.8 / 14.8).
-    const auto reads_of = [&](uint32_t g) { return ftk::grid_reads(pl->grid_rows, pl->grid_cols, g, pl->num_xcds, b.tm, b.tn); };
-    uint32_t fewest = ~0u, height = 0;
-    for (uint32_t g = 2; g <= pl->grid_rows; ++g)
-        if (const uint32_t most = reads_of(g); most < fewest) { fewest = most; height = g; }
-    if (height && fewest * 6 < reads_of(pl->grid_group) * 5) pl->grid_group = height;
+    pl->grid_group = ftk::grid_band(pl->grid_rows, pl->grid_cols, pl->num_xcds, b.tm, b.tn);
     pl->grid = true;
 }
 

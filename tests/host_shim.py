@@ -47,6 +47,7 @@ uint32_t shim_small_div(uint32_t x, uint32_t d) { return ftk::small_div(x, ftk::
 uint32_t shim_grid_reads(uint32_t rows, uint32_t cols, uint32_t group, uint32_t nx, uint32_t tm, uint32_t tn) {
     return ftk::grid_reads(rows, cols, group, nx, tm, tn);
 }
+uint32_t shim_grid_band(uint32_t rows, uint32_t cols, uint32_t nx, uint32_t tm, uint32_t tn) { return ftk::grid_band(rows, cols, nx, tm, tn); }
 uint32_t shim_grid_div(uint32_t x, uint32_t d) { return ftk::grid_div(x, ftk::grid_per(d)); }
 uint32_t shim_patch_bytes(uint32_t th, uint32_t tw) { return ftk::conv_patch_bytes(ftk::conv_patch_rows(th, tw)); }
 }
@@ -71,7 +72,7 @@ def load():
     lib.shim_grid_bodies.argtypes, lib.shim_grid_bodies.restype = [], u32
     lib.shim_grid_body.argtypes, lib.shim_grid_body.restype = [u32, p], None
     for name, args in (("run_lds", [u32, u32, u32, C.c_int]), ("run_rb_log2", [u32, u32, u64, u32, C.c_int, u32]), ("run_pitch", [u32]), ("patch_bytes", [u32, u32]),
-                       ("small_div", [u32, u32]), ("grid_div", [u32, u32]), ("grid_reads", [u32] * 6)):
+                       ("small_div", [u32, u32]), ("grid_div", [u32, u32]), ("grid_reads", [u32] * 6), ("grid_band", [u32] * 5)):
         fn = getattr(lib, "shim_" + name)
         fn.argtypes, fn.restype = args, u32
     return lib
