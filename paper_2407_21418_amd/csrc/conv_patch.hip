@@ -4,10 +4,10 @@
 // pulls nine times its image through the CUs' vector memory path, and the k loop runs at the rate of that path.  Here a
 // workgroup keeps the filter taps of 64 output channels in LDS (72 KB) and walks over tiles of up to 256 output pixels: a
 // tile's patch of the image is fetched once, halo and zero padding included, and every tap reads its rows of A from the
-// patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 to 65 us with fp32 results, 88 to 62 with 16-bit ones; 8 x 56 x 56: 10.8
-// to 7.6; 8 x 28 x 28: 6.6 to 4.5.  A tile of 256 pixels takes 2.6 us of MFMAs and reads, of which the MFMAs alone are 2.1 at
-// 2.2 GHz, and 1.5 us of copies, waits and barrier (counters: matrix cores busy for 54 % of the cycles on 224 x 224); the
-// smallest launches are bound by their latencies: taps and patch 1.5 us, nine taps 1.3 (27 % on 56 x 56).
+// patch, shifted.  8 x 224 x 224 x 64 -> 128: 89 us with the gather, 64 to 67 here with fp32 results, 87 and 60 with 16-bit ones; 8 x 56 x 56:
+// 10.5 and 7.6; 8 x 28 x 28: 6.2 and 4.5.  On 224 x 224, thirteen rounds of tiles of 256 pixels, a round takes 4.9 us: 4.1 without the stores, of
+// which the MFMAs are 3.0, LDS reads 0.5 and copies, waits and barrier 0.5, and 0.8 of stores that nothing hides (counters: matrix cores
+// busy for 53 % of the cycles at 2.1 GHz); the smallest launches are bound by their latencies: taps and patch 1.5 us, nine taps 1.3 (27 % on 56 x 56).
 //   - One workgroup of eight waves per CU, the patch of the next tile arriving while this one is computed: no wait and no
 //     barrier inside a tile.  (A form that streamed the taps through a ring, two workgroups per CU, spent 0.57 us per tap
 //     on 0.21 us of MFMAs: its barrier per tap and the taps' latency.  Starting a single tile before all taps have landed

@@ -572,13 +572,14 @@ bool better(const Program &a, const Program &b) {      // Top-1 order: SIA, then
 // whole round, so blocks may also be dealt as two halves of 128 rows: of the numbers of halved blocks the one with the
 // shortest schedule is taken.  A half takes 0.55 of a block (measured at K = 4096: 48 against 87 us).
 // Taken where the device is busy for at least 60 % of that schedule and 45 % of what it computes is wanted; below
-// that the program's smaller tiles are faster (K = 4096, blocks against tiles: 403 x 11008 54 against 61 us at 67 % busy,
-// 1200 x 4096 53 against 54 at 62 %; 1100 x 4096 53 against 49 at 56 %, 700 x 11008 86 against 84 at 50 %), and from twelve
-// k-tiles on (8192 x 3072 x 768: 43 against 52 us), so that the first copies and the stores of a block do not dominate;
-// halves alone want 32 (2048 x 3072 x 768: 17.6 against 15.7 us, x 2048: 29 against 32).  fp32 results take twice as long to
+// that the program's smaller tiles are faster (K = 4096, fp32 results, blocks / tiles, us: 403 x 11008 53 / 64 at 67 % busy,
+// 1200 x 4096 54 / 65 at 62 %; 1100 x 4096 57 / 54 at 56 %, 700 x 11008 96 / 84 at 50 %), and from twelve
+// k-tiles on (8192 x 3072 x 768, 16-bit results: 43 / 48), so that the first copies and the stores of a block do not dominate;
+// halves alone want 32 (2048 x 3072 x 768, 16-bit results: 16.5 / 15.1, x 2048: 27.9 / 31.3).  fp32 results take twice as long to
 // store, which nothing hides in a CU's one block; up to 24 k-tiles they are left to the program's tiles unless the device is
-// busy for 85 % of the schedule (621 shapes timed in both forms, blocks against tiles: 5000 x 4096 x 768 52.6 / 44.4 us, 6000 x
-// 8192 x 768 91 / 97), and for more than one round if those tiles are as large (8192 x 8192 x 1024 179 / 158).
+// busy for 85 % of the schedule (5000 x 4096 x 768 44.1 / 43.0, 6000 x 8192 x 768 89 / 99), and for more than one round if those tiles
+// are as large.  That last was so in 621 shapes timed before the blocks streamed their fp32 results (8192 x 8192 x 1024 179 / 158); it is
+// no longer (145 / 157), and tests/test_launch_forms.py holds that shape to the tiles.
 void big_schedule(ft_plan *pl) {
     const uint64_t M = pl->st.m, N = pl->st.n, K = pl->st.k, P = pl->num_cus;
     if (K % 64 || K < 12 * 64 || N % 8 || P == 0) return;
@@ -614,8 +615,9 @@ void big_schedule(ft_plan *pl) {
 // Matmuls may be executed in one grid of equal tiles (grid_gemm.hip), whatever tiles the program has.  Which tile: time in us =
 // first + more * (w - 1) + k-tiles * (step + step_more * (w - 1)), and for fp32 results wide + wide_more * (w - 1) for the
 // longer stores, w = tiles per CU on the busiest CU.  Fitted to 1652 launches (826 shapes, both result types, 8 to 4096 rows, 512
-// to 11008 columns, K of 768 to 6144; everything in the caches) with 23 bodies timed; the chosen body of the twelve kept is 0.9 %
-// from the fastest in the mean.
+// to 11008 columns, K of 768 to 6144; everything in the caches) with 23 bodies timed; the chosen body of the twelve kept was 0.9 %
+// from the fastest in the mean.  It ranks bodies: launches of one set of operands and C, 84 shapes with 12 to 24 k-tiles, take 0.8 to 0.98 of these times
+// with bodies 0 to 7 since arguments are preloaded and results written through, and 1.16 to 1.3 with bodies 8 to 10.
 // fp32 results take bodies that add up at least as many sums of an output as the program's tiles (gk waves along the reduce axis
 // times k_parts; to within a fiftieth of the mean, a last row of narrow tiles): the error of an fp32 sum grows with the root of
 // its terms in a row, against 64 bits 768 f16 products are off by 1.8e-7 in one sum, 1.3e-7 in two and 1.0e-7 in four.  (Of 16-bit
@@ -638,18 +640,21 @@ void big_schedule(ft_plan *pl) {
 //     (648 x 11008 x 4096 78.9 / 86.1 (71.9 / 74.2), 750 rows, 0.88 times as much, 122 / 95.1); more were not looked at;
 //   - with 16-bit results and up to 16 k-tiles, bodies of 128 x 192 and larger on less than three quarters of the CUs against tiles of
 //     128 x 128 and larger (1370 x 3072 x 768 11.7 / 14.4 (10.8 / 11.5); 12 launches 1.13 (0.99), above that line 1.00 (0.86)).
-// fp32 results keep the program's tiles in three more cases:
+// fp32 results keep the program's tiles in three more cases.  The first two were ties before the grid's arguments were preloaded and its results
+// written through; what they cost since is beside them, and tests hold forms on both sides of the first and the third:
 //   - up to 16 k-tiles, tiles of 96 x 128 and larger, and more workgroups than CUs in the program, which store while others
-//     multiply (688 x 3072 x 768 8.8 / 8.8 (8.4 / 8.2), 975 x 2304 x 768 8.7 / 8.6 (8.4 / 8.1); 1232 x 3072 x 768, whose form a test
-//     compares bit by bit with table order, would be faster, 12.4 / 11.6 (11.5 / 10.5));
-//   - fewer tiles than a third of the CUs, where little but latency is left (64 x 768 x 768 3.8 / 4.0 (3.5 / 3.3), 85 rows 4.1 / 4.0
-//     (3.6 / 3.4));
+//     multiply (688 x 3072 x 768 8.5 / 8.3 (8.5 / 8.3), 975 x 2304 x 768 8.75 / 8.6 (8.6 / 8.4), 2048 x 3072 x 768 15.0 / 14.4 (14.9 / 14.5); 1232 x 3072 x
+//     768, whose form a test compares bit by bit with table order, 12.35 / 11.0 (12.4 / 11.25));
+//   - fewer tiles than a third of the CUs, where little but latency is left (64 x 768 x 768 3.8 / 3.75 (3.5 / 3.3), 85 rows 4.0 / 3.7
+//     (3.7 / 3.25));
 //   - 32 k-tiles or more where the program splits them over workgroups or the blocks are taken: tests/test_launch_forms.py and
-//     tests/test_gpu_grid.py hold 403 x 4096 x 4096 and 429 x 3072 x 2048 to the tiles (35.8 / 28.5 (28.4 / 20.6) for the first) and 403 x 11008 x 4096
-//     to the blocks.  The others (230 launches, 1 to 4096 rows, 512 to 11008 columns, 2048 to 8192 products) take 0.76 (0.79) of the time:
-//     98 x 11008 x 4096 52.7 / 24.5, 1000 x 4096 x 4096 50.3 / 35.3 (48.4 / 32.9), 500 x 768 x 3072 10.9 / 8.9, 300 rows 9.1 / 8.0; of them one
-//     longer by more than 2 %, in the caches (350 x 1280 x 5120 19.6 / 16.9 (15.9 / 16.5)).  Two teams on tiles that cover C exactly and are larger than the grid's stay: a test
-//     compares 1600 x 768 x 3072 bit by bit with table order.
+//     tests/test_gpu_grid.py hold 403 x 4096 x 4096 and 429 x 3072 x 2048 to the tiles (30.9 / 22.3 (28.3 / 19.5), 17.3 / 11.7 (16.3 / 10.3)) and
+//     403 x 11008 x 4096 to the blocks (53.4 / 45.4 (48.0 / 41.9)).  Two teams on tiles that cover C exactly and are larger than the grid's stay as well: a test
+//     compares 1600 x 768 x 3072 bit by bit with table order (17.2 / 14.5).  With it stay the multiples of 32 from 1536 to 2016 rows of that layer, which the
+//     grid would serve a sixth to a quarter faster (1536 17.2 / 13.5, 1792 17.5 / 15.4, 2016 21.5 / 15.6), while the rows between them are in the grid.
+//     The others (230 launches, 1 to 4096 rows, 512 to 11008 columns, 2048 to 8192 products) took 0.81 (0.82) of the time when the line was set, nine longer by 2 to 12 %,
+//     and 0.76 (0.79) with the bands of grid_band, one longer: 98 x 11008 x 4096 52.7 / 24.5, 1000 x 4096 x 4096 50.3 / 35.3 (48.4 / 32.9), 500 x 768 x 3072
+//     10.9 / 8.9, 300 rows 9.1 / 8.0; that one, in the caches, 350 x 1280 x 5120 19.6 / 16.9 (15.9 / 16.5).
 struct GridCost {
     double first, more, step, step_more, wide, wide_more;
 };
@@ -734,16 +739,18 @@ uint64_t conv_tile(uint32_t P, uint32_t Q, uint32_t pixels, uint32_t lds, uint32
 }
 // 3 x 3 filters over 64 channels, stride 1 (conv_patch.hip).  Its taps are unrolled and its patch rows are one pixel's 64
 // channels; with a stride the patch holds stride^2 pixels per output (8 x 112 x 112, stride 2: 11.3 us against the gather's
-// 11.2).  Every workgroup walks the same number of tiles, so a tile of 64 * bm pixels costs rounds * (0.6 + bm): measured on
-// 8 x 224 x 224 1.9, 2.9, 4.2 and 5.7 us per round for bm = 1 .. 4.
+// 11.2).  Every workgroup walks the same number of tiles, so a tile of 64 * bm pixels costs rounds * (0.6 + bm): 8 x 224 x 224 took 1.9, 2.9,
+// 4.2 and 5.7 us per round for bm = 1 .. 4, and takes 1.7, 2.9, 3.8 and 4.9 since its results are streamed (84, 71, 66, 64 us in all).
 //
-// Where a workgroup has one tile the patches are the faster form (8 images, 128 channels: 28^2 5.1 / 6.2 us, 56^2 9.8 / 10.9; the
-// exception seen is one image with thousands of channels, 28^2 with 4096: 12.0 / 10.9).  With more, a short last round costs a whole one, which the gather's smaller tiles avoid where all of them
-// are resident at once (80^2 17.0 / 15.7, one round later 92^2 19.0 / 24.2); and an image smaller than a tile fills one
-// all the same (1000 images of 5 x 5, 384 channels: 44 / 23).  Both forms have a reduce axis of nine k-tiles, so their times
-// are estimated in us from the shapes alone: constants fitted to 1206 layers (1 to 1000 images, 2 to 400 pixels across, 8 to
-// 512 channels, both result types), where the choice below is slower than the other form by more than 3 % on 34, the
-// patches alone on 122 and up to six times.
+// Where a workgroup has one tile the patches are the faster form (us, patches / gather from HBM (and in the caches), 8 images, 128 channels, fp32 results: 28^2
+// 4.7 / 6.2 (4.5 / 6.3), 56^2 8.7 / 10.9 (7.6 / 10.5); one image of 28^2, 4096 channels, 10.2 / 10.8).  With more, a short last round costs a whole one, which
+// the gather's smaller tiles avoid where all of them are resident at once (77^2 16.6 / 14.4, 80^2 17.7 / 14.7, 84^2 16.8 / 15.4, 90^2 16.6 / 16.6; one round later
+// 92^2 17.0 / 23.7); and an image smaller than a tile fills one all the same (1000 images of 5 x 5, 384 channels: 41 / 23).  Both forms have a reduce
+// axis of nine k-tiles, so their times are estimated in us from the shapes alone: constants fitted to 1206 layers (1 to 1000 images, 2 to 400 pixels
+// across, 8 to 512 channels, both result types), where the choice below was slower than the other form by more than 3 % on 34, the patches alone on 122
+// and up to six times.  That was before results were written through the L2 and pixels found by reciprocals: patches of several rounds are now
+// estimated too long (8 x 224 x 224 91 for 64), and in the caches they are ahead at 77^2 to 90^2 too (80^2 11.8 / 14.2, 90^2 13.8 / 16.4), with 16-bit
+// results at 90^2 from HBM as well (14.0 / 15.5), and with 256 channels at 56^2 (13.8 / 14.3 (11.6 / 14.2)).
 void conv_schedule(ft_plan *pl) {
     const ft_op_desc &d = pl->op;
     const uint64_t P = pl->out_p, Q = pl->out_q, cols = ceil_div(d.c_out, 64);
@@ -843,17 +850,19 @@ namespace {
 // Batched products of one k-tile whose rows of C do not start on 64-byte blocks: whole rows per workgroup, written in address
 // order (row_runs.hip), or the program's tiles.  Rows on 64-byte blocks stay with the tiles, which write them at the same
 // rate and read B less often (160 columns: 20.7 against 24.7 us).  Otherwise the rows are faster, but for three kinds of
-// launches (2056 shapes with both forms: 8 to 320 columns, 1 to 512 rows, 24 to 768 matrices; us, rows against tiles):
-//   - less than a workgroup per CU, which tiles spread over more of them (12 x 300 x 300: 5.4 / 4.2);
+// launches, found in 2056 shapes with both forms (8 to 320 columns, 1 to 512 rows, 24 to 768 matrices) before the rows' stores were streamed; us,
+// rows against tiles, with the present stores:
+//   - less than a workgroup per CU, which tiles spread over more of them (12 x 300 x 300: 5.1 / 4.1);
 //   - more than 128 columns, where the rows make fewer than two and a half workgroups per CU and the tiles few more, and
-//     those not large: a workgroup's path through its columns is the whole time, and tiles share it out (96 x 131 x 131:
-//     5.2 / 4.8, 48 x 190 x 190: 5.4 / 4.6, 384 x 1 x 131: 4.9 / 4.0; not with larger tiles, 192 x 128 x 190: 8.5 / 9.7,
-//     48 x 512 x 258: 9.7 / 11.3);
+//     those not large: a workgroup's path through its columns is the whole time, and tiles share it out (48 x 190 x 190: 5.1 / 4.6,
+//     384 x 1 x 131: 4.9 / 4.0; a tie by now at 96 x 131 x 131, fp32 4.85 / 4.8, 16-bit 4.85 / 5.2; not with larger tiles, 192 x 128 x 190:
+//     6.2 / 9.7, 48 x 512 x 258: 7.7 / 11.1);
 //   - more than 256 columns, whose 32-row shares read all of B for about as many bytes of C: long launches of tall matrices in
-//     fp32, where the program has fewer tiles than 0.7 of the shares (768 x 512 x 300: 136 / 112), and with B as [K][N], which
-//     costs a share more, about as many tiles as shares where those are less than four per CU (96 x 270 x 270: 14.4 / 13.0; not
-//     with many tiles, 48 x 300 x 300: 9.2 / 10.1) or, in fp32, fewer tiles than shares (768 x 319 x 319: 101 / 90; with B as
-//     [N][K] 84 / 87).
+//     fp32, where the program has fewer tiles than 0.7 of the shares (768 x 512 x 300), and with B as [K][N], which
+//     costs a share more, about as many tiles as shares where those are less than four per CU (96 x 270 x 270; not
+//     with many tiles, 48 x 300 x 300: 6.7 / 10.1) or, in fp32, fewer tiles than shares (768 x 319 x 319).  With stores kept in the L2 these were 136 / 112, 14.4 /
+//     13.0 and 101 / 90; with streamed ones the rows are the faster form here too, 93 / 111, 11.3 / 12.8 and 66 / 90, and the third kind stands
+//     only until its lines are fitted again.
 bool rows_beat_tiles(const ft_plan *pl, uint64_t n, uint32_t es, bool nk) {
     const uint64_t cus = pl->num_cus, tiles = pl->st.n_tiles, N = pl->st.n, M = pl->st.m;
     if (n < cus || n >= (1u << 31)) return false;

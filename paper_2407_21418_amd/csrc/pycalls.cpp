@@ -2,8 +2,8 @@
 //
 // Small launches take 3 to 5 us of GPU time, and a pass of shape, look-up and launch took the host 4.6 to 5.3 us: 2.3 in HIP, 0.85 in the
 // look-up's ctypes call and 0.4 around the launch's, the rest in the interpreter.  Here a call reads its arguments straight from the
-// objects, look-up 0.17 us, launch 2.65, pass 3.4: 77 x 768 x 768 goes from 4.7-5.3 us to 3.75, 105 x 3072 x 768 with 16-bit results
-// from 4.65-5.05 to 4.20, which is GPU time.
+// objects, look-up 0.17 us (0.6 with the shape object that it takes), launch 2.65, pass 3.4 to 4.2 by the host's state: 77 x 768 x 768 goes
+// from 4.7-5.3 us to 3.75-4.4, 105 x 3072 x 768 with 16-bit results from 4.65-5.05 to 4.20, which is GPU time.
 // What these functions do not read themselves -- keywords, addresses that are neither int nor None, a shape of another type, a
 // library not loaded yet -- they hand to the ctypes functions of the same name in binding.py, which also define the errors.
 #define PY_SSIZE_T_CLEAN
